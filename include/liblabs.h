@@ -99,26 +99,22 @@ typedef struct labs_tabu_params {
 
 /* Launch configuration of the batched walk kernels.  Lanes per walk =
  * group_lanes / walks_per_group: 64 (one wavefront per walk: {64, 1},
- * {128, 2}, {256, 4}), 128 ({128, 1}: the walks of 64 < N <= 128 run on
- * two wavefronts each, exchanging their minima through LDS; the batch's
- * other walks run one per wavefront, two per 128-lane workgroup), or 32 /
- * 16 ({64, 2} and {128, 4}: the walks of N <= 32 run two per wavefront, 32
- * lanes each; {64, 4}: those of N <= 16 four per wavefront and those of
- * 16 < N <= 32 two; the batch's longer walks run one per wavefront, one or
- * two per workgroup).  Four wavefronts per walk, and two walks of two
- * wavefronts in one workgroup ({256, 1}, {256, 2}), are not built
+ * {128, 2}, {256, 4}), or 32 / 16 ({64, 2} and {128, 4}: the walks of
+ * N <= 32 run two per wavefront, 32 lanes each; {64, 4}: those of N <= 16
+ * four per wavefront and those of 16 < N <= 32 two; the batch's longer
+ * walks run one per wavefront, one or two per workgroup).  {128, 1} is
+ * accepted and runs as {128, 2}: a walk's step is short enough that no
+ * length gains from a second wavefront.  {256, 1} and {256, 2} are rejected
  * (LABS_E_INVAL). */
 typedef struct labs_launch {
     int32_t group_lanes;     /* 64, 128 or 256 lanes per workgroup */
     int32_t walks_per_group; /* 1, 2 or 4 */
     int32_t persistent;      /* 1: a grid sized to the device drains a
                                 longest-first work queue; 0: one walk per
-                                wavefront (or per two) of the grid */
+                                wavefront of the grid */
     int32_t groups_per_cu;   /* persistent grid = groups_per_cu x CUs (0: auto) */
-    int32_t layout;          /* walks of 64 < N <= 128: 0 default (record form
-                                on one wavefront, lag form on two), 1 lag form
-                                (t_jk rows, 18.5 KB of LDS per walk), 2 record
-                                form (sequence windows, 9.5 KB) */
+    int32_t layout;          /* 0, 1 or 2: accepted, without effect (walks of
+                                every length keep the same tables) */
 } labs_launch;               /* default (untuned): {64, 2, 0, 0, 0} when
                                 every walk has N <= 32, {64, 1, 0, 0, 0} up to
                                 N = 128, {256, 4, 0, 0, 0} above */
@@ -278,14 +274,11 @@ int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *o
 /*
  * Autotuner: times the launch configurations that apply to the length range
  * [n_min, n_max] -- {64, 1}, {128, 2}, {256, 4} (one wavefront per walk);
- * when the range reaches 64 < N <= 128, {128, 1} (two wavefronts per walk);
  * when n_min <= 32, {64, 2} and {128, 4} (two walks per wavefront), and
- * when n_min <= 16 also {64, 4} (four) -- each with both layouts of the
- * walks of 64 < N <= 128 where they are present, and each
- * as a grid of one walk per wavefront (or pair) and as a persistent queue
- * at 1, 2, 4 and 8 x 4 / (wavefronts per group) groups per CU -- on `walks`
- * random-start walks with lengths spread evenly over [n_min, n_max] and
- * parameters `p` (each: one warm-up call, then four calls back to back).
+ * when n_min <= 16 also {64, 4} (four) -- each as a grid of one walk per
+ * wavefront and as a persistent queue at 4 to 64 wavefronts per CU -- on
+ * `walks` random-start walks with lengths spread evenly over [n_min, n_max]
+ * and parameters `p` (each: one warm-up call, then four calls back to back).
  * The default runs first until the GPU is at its steady clock (at least 16
  * calls and 25 ms), and stays unless a configuration is more than 2 % faster.
  * The choice is kept for batches whose shortest and longest lengths fall in
@@ -340,12 +333,8 @@ typedef struct labs_memetic_params {
     int32_t stop_all;    /* 1: once any replica reaches target_e, every
                             replica stops at the end of the current chunk
                             (the global termination flag of Sec. IV) */
-    int32_t waves_per_replica; /* replicas with 64 < N <= 128: 1 or 2 wavefronts
-                            (two split each step's neighbours and exchange
-                            their minima: lower latency per generation, for
-                            batches too small to fill the device); 0 picks
-                            2 when those replicas number at most twice the
-                            compute units */
+    int32_t waves_per_replica; /* 0, 1 or 2: accepted, without effect (every
+                            replica runs on one wavefront per child) */
     int32_t children;    /* children per generation, 1..8 (0 means 1).  1 is
                             Alg. 1 (steady state).  B > 1 is the batched-
                             generation variant: B children are made from
@@ -357,9 +346,9 @@ typedef struct labs_memetic_params {
                             (replica, g, 64b + i/4, MUT) and walks as
                             generation g*B + b.  Targets are checked once per
                             generation; hit_gen counts generations.  For
-                            N > 128 a child's walk takes 17.7 KB of LDS, and
-                            B is further limited to what one workgroup can
-                            hold (LABS_E_INVAL beyond). */
+                            N > 128, B is further limited to what one
+                            workgroup can hold (LABS_E_INVAL beyond; all 8
+                            on the MI355X). */
     int32_t resume;      /* 1: continue the replicas this handle holds (left
                             by its last labs_memetic_run or put there by
                             labs_memetic_load) instead of drawing new

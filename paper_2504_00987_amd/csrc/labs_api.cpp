@@ -200,15 +200,9 @@ RuleParams to_rule(const labs_tabu_params &p) {
 
 int bucket_of(int n) { return std::min(LABS_MAX_N / 16 - 1, std::max(0, (n - 1) / 16)); }
 
-// Up to N = 128, one walk per 64-lane workgroup: the kernels compiled for
-// that size keep their registers low enough for four wavefronts per SIMD
-// (the two-neighbour ones need 104 VGPRs there, 136 with four walks per
-// workgroup); batches of several lengths run 10-25 % slower in the mixed
-// kernel with two or four walks per workgroup, batches of one length within
-// about 1 %.  Batches whose walks all have N <= 32 run two walks per
-// wavefront (1.35-1.45x faster at N = 32, uniform or mixed down to N = 3).
-// Longer walks are bound by LDS (18 KB per walk), and four walks per
-// 256-lane workgroup, one per SIMD of a CU, time best there.
+// Batches whose walks all have N <= 32 run two walks per wavefront, the
+// others one; one walk per 64-lane workgroup up to N = 128, four walks per
+// 256-lane workgroup above.
 labs_launch default_launch(int n_max) {
     labs_launch l;
     l.group_lanes = n_max <= 128 ? 64 : 256;
@@ -220,16 +214,14 @@ labs_launch default_launch(int n_max) {
 }
 
 // Lanes per walk 16 or 32 (several walks of N <= 32 per wavefront; longer
-// walks of the batch take one wavefront each), 64 (one wavefront) or 128
-// (two, one walk per workgroup).
+// walks of the batch take one wavefront each) or 64 (one wavefront);
+// {128, 1} runs as {128, 2}.
 const char *launch_problem(const labs_launch &l) {
     const int g = l.group_lanes, w = l.walks_per_group;
     if (g != 64 && g != 128 && g != 256) return "group_lanes must be 64, 128 or 256";
     if (w != 1 && w != 2 && w != 4) return "walks_per_group must be 1, 2 or 4";
     if (g / w > 128) return "four wavefronts per walk are not built";
-    if (g / w == 128 && w != 1)
-        return "two wavefronts per walk take one 128-lane workgroup each (a walk's barriers "
-               "are its workgroup's)";
+    if (g / w == 128 && w != 1) return "two walks per 256-lane workgroup are not built";
     if (l.persistent != 0 && l.persistent != 1) return "persistent must be 0 or 1";
     if (l.groups_per_cu < 0 || l.groups_per_cu > 64) return "groups_per_cu out of [0, 64]";
     if (l.layout < 0 || l.layout > 2) return "layout must be 0, 1 or 2";
@@ -239,15 +231,12 @@ const char *launch_problem(const labs_launch &l) {
 WalkLaunch walk_launch(const labs_handle *h, const labs_launch &l) {
     WalkLaunch w;
     const int lanes = l.group_lanes / l.walks_per_group;
-    w.split = lanes == 128;
-    w.lanes = lanes < 64 ? lanes : 64;
+    w.lanes = lanes < 64 ? lanes : 64;  // 128: one wavefront per walk, two per workgroup
     w.waves_per_group = l.group_lanes / 64;
-    w.lag = l.layout == 1 || (l.layout == 0 && w.split);
     const int cus = std::max(1, h->num_cus);
     w.groups = l.persistent
                    ? cus * (l.groups_per_cu > 0 ? l.groups_per_cu : std::max(1, 8 / w.waves_per_group))
                    : 0;
-    w.split_groups = l.persistent ? cus * (l.groups_per_cu > 0 ? l.groups_per_cu : 4) : 0;
     return w;
 }
 
@@ -638,7 +627,7 @@ int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *sta
     // The launch groups present run concurrently: the first on `s`, the
     // others on the handle's side streams, forked from and joined into `s`.
     const SideStreams &sides = h->sides;
-    const WalkGroups wg = walk_launch_groups(a.class_end, WL.split, WL.lanes);
+    const WalkGroups wg = tabu_launch_groups(a.class_end, WL.lanes);
     hipStream_t streams[kWalkClasses];
     const int n_sides = std::max(0, wg.n - 1);
     streams[0] = s;
@@ -722,28 +711,19 @@ extern "C" int labs_autotune(labs_handle *h, const labs_tabu_params *p, int32_t 
     constexpr int kReps = 4;
     constexpr float kMargin = 0.98f;
     const bool uneven = n_min != n_max;
-    // layouts matter only where walks of 64 < N <= 128 are present
-    const bool wide = n_min <= 128 && n_max > 64;
     std::vector<labs_launch> cands{default_launch(n_max)};
-    for (int layout : wide ? std::vector<int>{2, 1} : std::vector<int>{0}) {
-        for (int w : {1, 2, 4}) {
-            cands.push_back(labs_launch{64 * w, w, 0, 0, layout});
-            for (int gpc : {1, 2, 4, 8}) cands.push_back(labs_launch{64 * w, w, 1, gpc * 4 / w, layout});
-        }
-        if (wide) {
-            cands.push_back(labs_launch{128, 1, 0, 0, layout});
-            for (int gpc : {1, 2, 4, 8}) cands.push_back(labs_launch{128, 1, 1, gpc, layout});
-        }
-        // several walks per wavefront where walks of N <= 32 are present
-        // (16 lanes per walk only where N <= 16 ones are)
-        constexpr int kSub[3][2] = {{64, 2}, {128, 4}, {64, 4}};  // group lanes, walks
-        for (const auto &gw : kSub) {
-            if (n_min > gw[0] / gw[1]) continue;
-            cands.push_back(labs_launch{gw[0], gw[1], 0, 0, layout});
-            for (int gpc : {1, 2, 4, 8})
-                cands.push_back(labs_launch{gw[0], gw[1], 1, gpc * 4 / (gw[0] / 64), layout});
-        }
-    }
+    // persistent grids in wavefronts per CU (up to the 32 that fit)
+    constexpr int kWavesPerCu[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 64};
+    auto add = [&](int lanes, int walks) {
+        cands.push_back(labs_launch{lanes, walks, 0, 0, 0});
+        for (int w : kWavesPerCu) cands.push_back(labs_launch{lanes, walks, 1, w * 64 / lanes, 0});
+    };
+    for (int w : {1, 2, 4}) add(64 * w, w);
+    // several walks per wavefront where walks of N <= 32 are present
+    // (16 lanes per walk only where N <= 16 ones are)
+    constexpr int kSub[3][2] = {{64, 2}, {128, 4}, {64, 4}};  // group lanes, walks
+    for (const auto &gw : kSub)
+        if (n_min <= gw[0] / gw[1]) add(gw[0], gw[1]);
     float best_ms = 1e30f;
     labs_launch best = cands[0];
     int rc = LABS_OK, n_tried = 0;
@@ -769,9 +749,8 @@ extern "C" int labs_autotune(labs_handle *h, const labs_tabu_params *p, int32_t 
     for (size_t i = 0; i < cands.size() && rc == LABS_OK; ++i) {
         const labs_launch &c = cands[i];
         const WalkLaunch wc = walk_launch(h, c), w0 = walk_launch(h, cands[0]);
-        if (i > 0 && wc.waves_per_group == w0.waves_per_group && wc.split == w0.split &&
-            wc.lag == w0.lag && wc.lanes == w0.lanes && wc.groups == w0.groups &&
-            wc.split_groups == w0.split_groups)
+        if (i > 0 && wc.waves_per_group == w0.waves_per_group && wc.lanes == w0.lanes &&
+            wc.groups == w0.groups)
             continue;  // the same kernels as the default, timed first
         rc = run(c);
         hipEventRecord(e0, s);

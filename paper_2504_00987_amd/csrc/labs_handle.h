@@ -116,9 +116,6 @@ int check_memetic(labs_handle *h, const labs_memetic_params *p);
 // Children per generation against what the device fits (classes: bit c set
 // when a replica of memetic_class c is present).
 int check_children(labs_handle *h, int children, int classes);
-// 1 when replicas with 64 < N <= 128 should run on two wavefronts each.
-int split_wide(const labs_handle *h, int waves_per_replica, int64_t n_wide);
-
 // Bytes of device state per memetic replica with population size K.
 inline size_t memetic_state_bytes(int K) {
     return (size_t)K * (kStateWords * sizeof(uint64_t) + sizeof(int32_t)) +

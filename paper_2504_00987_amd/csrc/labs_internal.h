@@ -17,10 +17,10 @@ struct RuleParams {
     int32_t slo_num, slo_den, shi_num, shi_den;  // LABS_STEPS_RANGE bounds
 };
 
-// Length classes of stand-alone walks, longest first: a class fixes the
-// neighbours per lane (NW) and how many 16-lag chunks a window spans (NB).
-// The last two (N <= 32, N <= 16) are also the walks that fit a 32- or
-// 16-lane group of a wavefront that runs several walks.
+// Length classes of stand-alone walks, longest first: runs of the processing
+// order that one launch may cover.  The last two (N <= 32, N <= 16) are also
+// the walks that fit a 32- or 16-lane group of a wavefront that runs several
+// walks.
 constexpr int kWalkClasses = 8;
 constexpr int kClassMaxN[kWalkClasses] = {256, 193, 128, 97, 64, 49, 32, 16};
 inline int walk_class(int n) {
@@ -56,22 +56,19 @@ constexpr int kSideStreams = kWalkClasses - 1;
 // Kernel forms of a launch group.
 enum WalkKind : int {
     kKindWave = 0,    // one walk per wavefront
-    kKindSplit = 1,   // one walk of 64 < N <= 128 per two wavefronts
+    kKindSplit = 1,   // walks of 64 < N <= 128 apart from the shorter ones
     kKindGroup2 = 2,  // two walks of N <= 32 per wavefront (32 lanes each)
     kKindGroup4 = 4,  // four walks of N <= 16 per wavefront (16 lanes each)
 };
 
 // Launch groups of a batch: runs of consecutive length classes (hence of
-// consecutive positions of the processing order) that one kernel launch
-// covers, each on a stream of its own.  Both classes of N > 128, when
-// present, share one launch (the four-neighbour layout serves both); so do
-// the classes of N <= 128 when more than one is present -- or, with
-// two-wavefront walks (split), classes 2..3 (64 < N <= 128) form one group
-// and the shorter classes another.  With several walks per wavefront
-// (`lanes` = 32 or 16 lanes per walk) the walks of N <= 32 leave the
-// one-walk-per-wavefront group: with 32 lanes both short classes form one
-// group of two walks per wavefront; with 16, N <= 16 runs four per
-// wavefront and 16 < N <= 32 two.
+// consecutive positions of the processing order).  The classes of N > 128,
+// when present, form one group and those of N <= 128 another -- or, with
+// `split`, classes 2..3 (64 < N <= 128) and the shorter classes one each.
+// With several walks per wavefront (`lanes` = 32 or 16 lanes per walk) the
+// walks of N <= 32 leave the one-walk-per-wavefront group: with 32 lanes both
+// short classes form one group of two walks per wavefront; with 16, N <= 16
+// runs four per wavefront and 16 < N <= 32 two.
 struct WalkGroups {
     int n;
     int first[kWalkClasses], last[kWalkClasses], kind[kWalkClasses];
@@ -112,14 +109,32 @@ inline WalkGroups walk_launch_groups(const int64_t *class_end, bool split, int l
     return g;
 }
 
+// The launch groups of a walk batch: those above, with neighbouring
+// one-walk-per-wavefront groups in one launch (one kernel takes every length:
+// a walk's tables are 15 bytes per position, so the longest walk's scratch
+// costs the shorter ones no occupancy).
+inline WalkGroups tabu_launch_groups(const int64_t *class_end, int lanes) {
+    const WalkGroups all = walk_launch_groups(class_end, false, lanes);
+    WalkGroups g;
+    g.n = 0;
+    for (int i = 0; i < all.n; ++i) {
+        if (g.n > 0 && all.kind[i] == kKindWave && g.kind[g.n - 1] == kKindWave) {
+            g.last[g.n - 1] = all.last[i];
+            continue;
+        }
+        g.first[g.n] = all.first[i];
+        g.last[g.n] = all.last[i];
+        g.kind[g.n] = all.kind[i];
+        ++g.n;
+    }
+    return g;
+}
+
 // How labs_tabu_batch launches its walks.
 struct WalkLaunch {
-    int waves_per_group;  // wavefronts per workgroup (one-wavefront walks: that many per group)
-    bool split;           // walks of 64 < N <= 128 on two wavefronts each
-    bool lag;             // walks of 64 < N <= 128 in the lag form
+    int waves_per_group;  // wavefronts per workgroup
     int lanes;            // lanes per walk of N <= 32: 64 (one walk per wavefront), 32 or 16
-    int groups;           // persistent grid of the one-wavefront and group kernels (0: none)
-    int split_groups;     // persistent grid of the two-wavefront kernel (0: none)
+    int groups;           // persistent grid (0: none)
 };
 
 // Words of a sequence mask in the memetic state (N <= 256).
@@ -167,7 +182,6 @@ struct MemeticLaunchArgs {
     RuleParams rule;
     int32_t gens;            // generations per launch
     int32_t classes;         // bit c set: some slot is of memetic_class c
-    int32_t split_wide;      // 1: a replica with N > 64 runs on two wavefronts
     int32_t children;        // children per generation (1: Alg. 1)
     MemeticStateDev st;
     uint32_t *any_hit;       // set to 1 when a replica reaches its target
@@ -211,7 +225,7 @@ hipError_t launch_bruteforce(int n, const BruteParts &p, hipStream_t s);
 int64_t skew_brute_waves(int n);
 hipError_t launch_skew_bruteforce(int n, const BruteParts &p, hipStream_t s);
 
-// Launch group g (walk_launch_groups(a.class_end, l.split, l.lanes)) runs on
+// Launch group g (tabu_launch_groups(a.class_end, l.lanes)) runs on
 // streams[g]; a.counter must point at 32 * kWalkClasses writable uint32 (the
 // queue head of a group at 32 * its first class).
 hipError_t launch_tabu(const TabuLaunchArgs &a, const WalkLaunch &l, const hipStream_t *streams);

@@ -51,11 +51,6 @@ static MemLayout mem_layout(int pops, int K) {
 
 static_assert(kMaxChildren == LABS_MAX_CHILDREN, "kernel and ABI limits agree");
 
-int split_wide(const labs_handle *h, int waves_per_replica, int64_t n_wide) {
-    if (waves_per_replica != 0) return waves_per_replica == 2;
-    return n_wide <= 2 * (int64_t)std::max(h->num_cus, 1);
-}
-
 int check_children(labs_handle *h, int children, int classes) {
     if (children > 1 && (classes & 4) && children > h->max_children_wide)
         return fail(h, LABS_E_INVAL, "children=%d: this device fits at most %d per generation "
@@ -156,11 +151,9 @@ extern "C" int labs_memetic_run(labs_handle *h, const labs_memetic_params *p,
     }
     if (out_stride < n_max) return fail(h, LABS_E_INVAL, "out_stride=%d < N=%d", out_stride, n_max);
     int classes = 0;
-    int64_t n_wide = 0;
     for (int i = 0; i < pops; ++i) {
         const int c = memetic_class(ns_host ? ns_host[i] : n_uniform);
         classes |= 1 << c;
-        n_wide += c == 1;
     }
     const int children = std::max(1, (int)p->children);
     if ((rc = check_children(h, children, classes))) return rc;
@@ -247,7 +240,6 @@ extern "C" int labs_memetic_run(labs_handle *h, const labs_memetic_params *p,
     a.any_hit = d_flag;
     a.stop = d_flag + 1;
     a.classes = classes;
-    a.split_wide = split_wide(h, p->waves_per_replica, n_wide);
     a.children = children;
     if (resume) {
         // any_hit carries over (the global flag of the run being continued);

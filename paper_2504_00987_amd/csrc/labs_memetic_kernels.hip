@@ -2,8 +2,7 @@
 //
 //   memetic_init_kernel    random populations (Alg. 1, first two lines)
 //   memetic_advance_kernel memetic generations (Alg. 1 / Alg. 3), one replica
-//                          per workgroup of one or two wavefronts, population
-//                          resident in LDS
+//                          per wavefront, population resident in LDS
 //   memetic_batched_kernel B children per generation, one wavefront each,
 //                          from one snapshot of the population
 //   gather_best_kernel     best sequences and energies to caller buffers
@@ -17,11 +16,6 @@ namespace liblabs {
 namespace {
 
 constexpr int kMaxK = 128;
-
-// Walk form of the one-child kernels: the lag form for N <= 64, and for
-// 64 < N <= 128 when two wavefronts run a replica (few replicas per CU).
-template <int NW, int SPLIT>
-constexpr bool kAdvanceLag = NW == 1 || (NW == 2 && SPLIT == 2);
 
 
 // ---------------------------------------------------------------------------
@@ -109,22 +103,37 @@ __device__ __forceinline__ typename MaskOf<NW>::type mutation_mask(const Memetic
     return make_mask<NW>(f[0], f[1], f[2], f[3]);
 }
 
-// One replica on SPLIT wavefronts (wavefront `part` of them); every
-// wavefront runs the generation logic redundantly on wave-uniform values and
-// the walk is split between them.
-template <int NW, int SPLIT>
+// A child's walk of N <= 64 NW (NW = 4: N > 128) on one wavefront, with the
+// fewest neighbours per lane that hold it.
+template <int NW>
+__device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskOf<NW>::type &child,
+                                                     const MemeticLaunchArgs &a,
+                                                     const MemeticSlot &sl, uint32_t gen,
+                                                     uint8_t *lds) {
+    const Schedule sch = make_schedule(a.rule, N, sl.k0, sl.k1, sl.pop_id, gen);
+    if (NW == 4 && __builtin_amdgcn_readfirstlane(N) <= 192) {
+        const auto r = tabu_walk<NW == 4 ? 3 : NW>(N, child, sch, a.rule.aspiration, sl.k0, sl.k1,
+                                                   sl.pop_id, gen, lds, nullptr);
+        return {r.best, r.best_e, r.final_e};
+    }
+    return tabu_walk<NW>(N, child, sch, a.rule.aspiration, sl.k0, sl.k1, sl.pop_id, gen, lds,
+                         nullptr);
+}
+
+// One replica on one wavefront.
+template <int NW>
 __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &sl,
-                                uint64_t (*pop)[NW], int *popE, uint8_t *lds, int part) {
+                                uint64_t (*pop)[NW], int *popE, uint8_t *lds) {
     using Mask = typename MaskOf<NW>::type;
     const int lane = lane_id();
     const int N = sl.n, K = a.K, st = sl.state;
     const int64_t base = (int64_t)st * K;
-    for (int i = lane + 64 * part; i < K; i += 64 * SPLIT) {
+    for (int i = lane; i < K; i += 64) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) pop[i][w] = a.st.pop[(base + i) * kStateWords + w];
         popE[i] = a.st.popE[base + i];
     }
-    walk_sync<SPLIT>();
+    wave_sync();
     Mask best = load_mask<NW>(a.st.best + (int64_t)st * kStateWords);
     int bestE = a.st.bestE[st];
     int64_t g = a.st.gen[st];
@@ -160,18 +169,16 @@ __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &s
         }
         // Mutate: bit i flips when word i%4 of draw (pop, g, i/4, MUT) < thr.
         child = m_xor(child, mutation_mask<NW>(sl, gg, 0u, thr));
-        const Schedule sch = make_schedule(a.rule, N, sl.k0, sl.k1, sl.pop_id, gg);
-        const WalkResult<NW> r = tabu_walk<NW, false, SPLIT, WalkLds<NW>::NBIG, kAdvanceLag<NW, SPLIT>>(
-            N, child, sch, a.rule.aspiration, sl.k0, sl.k1, sl.pop_id, gg, lds, nullptr, part);
+        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, gg, lds);
         if (r.best_e < bestE) {
             bestE = r.best_e;
             best = r.best;
         }
         const int rep = (int)below(db.w2, (uint32_t)K);
-        walk_sync<SPLIT>();
+        wave_sync();
         store_mask<NW>(pop[rep], r.best);  // uniform values, every lane
         popE[rep] = r.best_e;
-        walk_sync<SPLIT>();
+        wave_sync();
         ++g;
         if (targeted && bestE <= sl.target) {
             if (hit < 0) hit = g;
@@ -179,12 +186,11 @@ __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &s
         }
     }
 
-    for (int i = lane + 64 * part; i < K; i += 64 * SPLIT) {
+    for (int i = lane; i < K; i += 64) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) a.st.pop[(base + i) * kStateWords + w] = pop[i][w];
         a.st.popE[base + i] = popE[i];
     }
-    if (part != 0) return;
     store_mask<NW>(a.st.best + (int64_t)st * kStateWords, best);  // uniform values, every lane
     a.st.bestE[st] = bestE;
     a.st.gen[st] = g;
@@ -193,25 +199,19 @@ __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &s
 }
 
 // Replicas of one length class: N <= 64 (NW = 1), 64 < N <= 128 (NW = 2) or
-// 128 < N <= 256 (NW = 4), one workgroup of SPLIT wavefronts per replica;
-// slots of the other classes and idle slots return at once.  The
-// two-wavefront form only runs when there are at most two replicas per
-// compute unit, so it is compiled for latency (all of a step's LDS reads in
-// flight at once) rather than for occupancy, and its walks take the lag form
-// (18 KB of LDS, which costs nothing at that occupancy).
-template <int NW, int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT)
-__attribute__((amdgpu_waves_per_eu(1, SPLIT == 2 ? 2 : 8))) void memetic_advance_kernel(
-    MemeticLaunchArgs a) {
+// 128 < N <= 256 (NW = 4), one wavefront per replica; slots of the other
+// classes and idle slots return at once.
+template <int NW>
+__global__ __launch_bounds__(64) void memetic_advance_kernel(MemeticLaunchArgs a) {
     __shared__ uint64_t pop[kMaxK][NW];
     __shared__ int popE[kMaxK];
-    __shared__ __attribute__((aligned(16))) uint8_t lds[walk_lds_bytes<NW, kAdvanceLag<NW, SPLIT>>()];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[WalkLds<NW>::BYTES];
     const int s = blockIdx.x;
     if (s >= a.n_slots) return;
     if (a.stop != nullptr && *a.stop != 0u) return;  // one value for the whole grid
     const MemeticSlot sl = a.slots[s];
     if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
-    memetic_replica<NW, SPLIT>(a, sl, pop, popE, lds, SPLIT == 1 ? 0 : (int)(threadIdx.x >> 6));
+    memetic_replica<NW>(a, sl, pop, popE, lds);
 }
 
 // Batched-generation variant: one workgroup of B = a.children wavefronts per
@@ -224,11 +224,7 @@ __attribute__((amdgpu_waves_per_eu(1, SPLIT == 2 ? 2 : 8))) void memetic_advance
 // holds identically, so every wavefront reaches every barrier.
 // Dynamic LDS: population [kMaxK][NW] words, energies [kMaxK], per child
 // kResWords words (mask, energy, replaced slot), then the B walk scratches.
-// Children walk in the lag form up to N = 128: a replica's workgroup of B
-// wavefronts occupies its CU whatever the LDS per walk.
 constexpr int kResWords = 8;
-template <int NW>
-constexpr bool kBatchedLag = NW <= 2;
 template <int NW>
 constexpr int batched_header() {
     return kMaxK * 8 * NW + kMaxK * 4 + kMaxChildren * kResWords * 8;
@@ -249,7 +245,7 @@ __global__ __launch_bounds__(64 * kMaxChildren) void memetic_batched_kernel(
     if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
     const int B = a.children;
     const int b = (int)(threadIdx.x >> 6);
-    uint8_t *lds = dyn_lds + batched_header<NW>() + b * walk_lds_bytes<NW, kBatchedLag<NW>>();
+    uint8_t *lds = dyn_lds + batched_header<NW>() + b * WalkLds<NW>::BYTES;
     const int N = sl.n, K = a.K, st = sl.state;
     const int64_t base = (int64_t)st * K;
     for (int i = (int)threadIdx.x; i < K; i += 64 * B) {
@@ -293,9 +289,7 @@ __global__ __launch_bounds__(64 * kMaxChildren) void memetic_batched_kernel(
         // child b's mutation words: (pop, g, 64 b + i/4, MUT)
         child = m_xor(child, mutation_mask<NW>(sl, gg, (uint32_t)(64 * b), thr));
         const uint32_t wgen = (uint32_t)(g * B + b);
-        const Schedule sch = make_schedule(a.rule, N, sl.k0, sl.k1, sl.pop_id, wgen);
-        const WalkResult<NW> r = tabu_walk<NW, false, 1, WalkLds<NW>::NBIG, kBatchedLag<NW>>(
-            N, child, sch, a.rule.aspiration, sl.k0, sl.k1, sl.pop_id, wgen, lds, nullptr);
+        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, lds);
         uint64_t *mine = res + kResWords * b;
         store_mask<NW>(mine, r.best);  // uniform values, every lane of wavefront b
         mine[4] = (uint64_t)(uint32_t)r.best_e;
@@ -390,7 +384,7 @@ namespace {
 // population plus B walk scratches.
 template <int NW>
 constexpr size_t batched_lds_bytes(int children) {
-    return batched_header<NW>() + (size_t)children * walk_lds_bytes<NW, kBatchedLag<NW>>();
+    return batched_header<NW>() + (size_t)children * WalkLds<NW>::BYTES;
 }
 
 template <int NW>
@@ -403,9 +397,7 @@ hipError_t launch_batched(const MemeticLaunchArgs &a, hipStream_t s) {
 }  // namespace
 
 int prepare_memetic_kernels() {
-    // more than 64 KB of dynamic LDS (eight children of N > 64) needs the
-    // attribute; the CU has 160 KB.  N > 128 takes 17.7 KB per child: the
-    // largest child count the device accepts is returned.
+    // raised in case the default limit of dynamic LDS is below eight children's
     hipError_t e = hipFuncSetAttribute((const void *)memetic_batched_kernel<1>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)batched_lds_bytes<1>(kMaxChildren));
@@ -435,13 +427,11 @@ hipError_t launch_memetic_class(const MemeticLaunchArgs &a, int c, hipStream_t s
         return launch_batched<4>(a, s);
     }
     if (c == 0)
-        hipLaunchKernelGGL((memetic_advance_kernel<1, 1>), grid, dim3(64), 0, s, a);
-    else if (c == 1 && a.split_wide)
-        hipLaunchKernelGGL((memetic_advance_kernel<2, 2>), grid, dim3(128), 0, s, a);
+        hipLaunchKernelGGL(memetic_advance_kernel<1>, grid, dim3(64), 0, s, a);
     else if (c == 1)
-        hipLaunchKernelGGL((memetic_advance_kernel<2, 1>), grid, dim3(64), 0, s, a);
+        hipLaunchKernelGGL(memetic_advance_kernel<2>, grid, dim3(64), 0, s, a);
     else
-        hipLaunchKernelGGL((memetic_advance_kernel<4, 1>), grid, dim3(64), 0, s, a);
+        hipLaunchKernelGGL(memetic_advance_kernel<4>, grid, dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

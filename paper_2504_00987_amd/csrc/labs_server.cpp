@@ -123,12 +123,10 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     for (int s = 0; s < max_slots; ++s) any |= owner[s] >= 0;
     if (!any) return 0;  // idle
     int classes = 0;
-    int64_t n_wide = 0;
     for (int s = 0; s < max_slots; ++s)
         if (owner[s] >= 0) {
             const int c = memetic_class(h_slots[s].n);
             classes |= 1 << c;
-            n_wide += c == 1;
         }
     const int n_init = (int)fresh.size();
     for (int i = 0; i < n_init; ++i) h_init[i] = h_slots[fresh[i]];
@@ -158,7 +156,6 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     a.n_slots = max_slots;
     a.gens = params.chunk;
     a.classes = classes;
-    a.split_wide = split_wide(h, params.waves_per_replica, n_wide);
     a.children = std::max(1, (int)params.children);
     if (e == hipSuccess) e = launch_memetic_advance(a, stream, &sides);
     if (e == hipSuccess) e = hipMemcpyAsync(h_bestE, st.bestE, max_slots * 4, hipMemcpyDeviceToHost, stream);
