@@ -477,7 +477,7 @@ __device__ __forceinline__ int pair_sum(Mask M, Mask Mr, int N, int m) {
 // and d_p = -d_p - 2 (N - 1) (undoing the move), Q_2p unchanged.  Lane j
 // reads and writes exactly the entries C_|p-j| and Q_(p+j) (lanes j and
 // 2p - j write the same value to C_k).  The common -8 is left out of the
-// stored D_j = d_j + 8 (moves made) and put back on the scalar unit.
+// stored D_j and put back on the scalar unit.
 // Lanes past the sequence have s_j = 0: they write back what they read, and
 // their D never falls to an aspiration threshold.
 //
@@ -486,7 +486,9 @@ __device__ __forceinline__ int pair_sum(Mask M, Mask Mr, int N, int m) {
 // wavefront per walk with NW neighbours per lane keeps that chain free of
 // barriers.  Against recomputing v_j from packed int8 products (the same
 // walks, MI355X): 4096 walks of N = 64 and 256 steps 131 -> 94.5 us, of
-// N = 120 and 480 steps 717 -> 269 us, of N in 129..256 3.90 -> 0.64 ms.
+// N = 120 and 480 steps 717 -> 269 us, of N in 129..256 3.90 -> 0.64 ms; with
+// the scalar bookkeeping of a step cut to what is listed below (29 scalar
+// instructions for 48 at N <= 64) 87 us, 238 us and 0.61 ms.
 //   lds    WalkLds<NW>::BYTES bytes of per-walk scratch, 16-aligned
 //   trace  with TRACE: trace[t-1] = flipped index
 // Every lane must call this with identical uniform inputs.
@@ -604,7 +606,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             // Q_2j - 1 - s_j v_j; beyond the sequence never a minimum
             D[h] = j < N ? pair_sum(M, Mr, N, 2 * j) - 1 + nr[h] * v[h] : 0x3fffffff;
             // lanes past the sequence are never admissible: infinite tenure
-            tabu[h] = j < N ? 0 : INT_MAX;
+            tabu[h] = j < N ? -1 : INT_MAX;
         }
     }
     wave_sync();
@@ -612,16 +614,15 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     for (int i = 0; i < 2 * NW; ++i) QT[lane + 64 * i] = 2 * pair_sum(M, Mr, N, lane + 64 * i);
     wave_sync();
 
-    int E = wave_sum(sq_e);
+    const int E0 = wave_sum(sq_e);
     Mask best = M;
-    int bestE = E;
-    // Aspiration: candE_j < bestE <=> d_j < ((bestE - E) >> 2) - (N - 1)
-    // (energies are all congruent mod 4), kept per move for D; without
-    // aspiration far below every key.
-    const int thr0 = aspiration ? -(N - 1) : -(1 << 29);
-    int thr = thr0;
-    uint32_t dr0 = 0u;
-    int expire = 0;  // lane l: step t0 + l plus that step's tenure
+    // Energies in units of 4 (a move changes E by 4 (N - 1 + d_p)): the best
+    // against E0, and how far the walk is above its best.  Aspiration:
+    // candE_j < bestE <=> d_j < (bestE - E) / 4 - (N - 1); without it `above`
+    // is kept far from every key.
+    int best4 = 0, above = 0;
+    const int asp0 = aspiration ? 0 : 1 << 29;
+    int asp = asp0;
     uint32_t ct[NW], qt, sy, sz;  // LDS addresses less their part in p
     const uint32_t base = lds_offset(lds);
 #pragma unroll
@@ -629,30 +630,36 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     qt = base + (uint32_t)(L::QT + 4 * lane);  // + 4p: Q_(p + lane)
     sy = base + (uint32_t)(L::SP - lane);      // + 2p: SP[2p - lane]
     sz = base + (uint32_t)(L::SP + 2 * lane);  // - p: SP[2 lane - p]
-    const uint32_t ct_base = base + (uint32_t)L::CT;
+    const uint32_t ct_base = base + (uint32_t)L::CT, sp0 = base + (uint32_t)L::SP;
 
     // Steps in blocks of 64: one Philox call per lane supplies the draws of
     // a block (read back with readlane), and the inner loop carries no
-    // refill test.
+    // refill test.  Within a block the tenures count from its start, and
+    // D_j = d_j + 8 (moves made in the block).
     for (int t0 = 1; t0 <= sch.T; t0 += 64) {
+        uint32_t dr0;
+        int expire;  // lane l: slot l plus that step's tenure
         {
             const Draw4 d = philox10(entity, gen, (uint32_t)(t0 + lane), kTagStep, k0, k1);
             dr0 = d.w0;
-            expire = t0 + lane + sch.lo + (int)below(d.w1, (uint32_t)(sch.hi - sch.lo + 1));
+            expire = lane + sch.lo + (int)below(d.w1, (uint32_t)(sch.hi - sch.lo + 1));
         }
-        const int t_end = min(sch.T, t0 + 63);
-        for (int t = t0; t <= t_end; ++t) {
-            const int slot = t - t0;
+        const int steps = min(sch.T - t0 + 1, 64);
+        int off = -(N - 1);  // 8 (moves made in the block) - (N - 1)
+        for (int slot = 0; slot < steps; ++slot) {
+            const int thr = off - asp;
             int key[NW];
 #pragma unroll
             for (int h = 0; h < NW; ++h)
-                key[h] = tabu[h] < t || D[h] < thr ? D[h] : INT_MAX;
+                key[h] = tabu[h] < slot || D[h] < thr ? D[h] : INT_MAX;
             int kmin = key[0];
 #pragma unroll
             for (int h = 1; h < NW; ++h) kmin = min(kmin, key[h]);
             const int m = wave_min(kmin);
 
-            // ties: the r-th (ascending) of the tied moves, r = (u0 * count) >> 32
+            // the chosen move: lane src of word `word` (the first word with a
+            // minimum); of several tied moves the r-th (ascending),
+            // r = (u0 * count) >> 32
             uint64_t T[NW];
             int c[NW], count = 0;
 #pragma unroll
@@ -662,47 +669,38 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
                 asm("" : "+s"(c[h]));  // 32-bit scalar arithmetic
                 count += c[h];
             }
-            int r = 0;
-            if (count > 1) r = (int)below(readlane_u(dr0, slot), (uint32_t)count);
             uint64_t tied = T[NW - 1];
             int word = NW - 1;
-            if constexpr (NW == 2) {
-                if (r < c[0]) {
-                    tied = T[0];
-                    word = 0;
-                } else {
-                    r -= c[0];
-                }
-            } else if constexpr (NW > 2) {
-                if (r < c[0]) {
-                    tied = T[0];
-                    word = 0;
-                } else if (r < c[0] + c[1]) {
-                    tied = T[1];
-                    word = 1;
-                    r -= c[0];
-                } else if (NW == 4 && r < c[0] + c[1] + c[2]) {
-                    tied = T[2];
-                    word = 2;
-                    r -= c[0] + c[1];
-                } else {
-                    r -= c[0] + c[1] + (NW == 4 ? c[2] : 0);
-                }
-            }
-            for (int i = 0; i < r; ++i) tied &= tied - 1ull;  // drop the r lowest
-            const int src = __builtin_ctzll(tied);  // lane of the move
-            const int pick = 64 * word + src;
-
-            // entries of the move (all reads before any write)
-            int nr_sel = nr[0];
 #pragma unroll
-            for (int h = 1; h < NW; ++h) nr_sel = word == h ? nr[h] : nr_sel;
-            const int nsp = readlane(nr_sel, src);
+            for (int h = NW - 2; h >= 0; --h) {
+                tied = c[h] ? T[h] : tied;
+                word = c[h] ? h : word;
+            }
+            if (__builtin_expect(count > 1, 0)) {
+                int r = (int)below(readlane_u(dr0, slot), (uint32_t)count);
+                tied = T[0];
+                word = 0;
+#pragma unroll
+                for (int h = 0; h + 1 < NW; ++h)
+                    if (word == h && r >= c[h]) {
+                        r -= c[h];
+                        tied = T[h + 1];
+                        word = h + 1;
+                    }
+                for (; r > 0; --r) tied &= tied - 1ull;  // drop the r lowest
+            }
+            const int src = __builtin_ctzll(tied);  // lane of the move
+            const int pick = NW == 1 ? src : 64 * word + src;
+
+            // entries of the move (all reads before any write); -s_p from its
+            // lane, or (several words) from the sequence in LDS
             const uint32_t qa = qt + 4u * (uint32_t)pick;
             const uint32_t ya = sy + 2u * (uint32_t)pick;
             const uint32_t za = sz - (uint32_t)pick;
+            const uint32_t pa = sp0 + (uint32_t)pick;
             uint32_t ca[NW];
             int cv[NW], qv[NW], q0[NW], yv[NW], zv[NW];
+            int vsp = 0;
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
                 ca[h] = absdiff_add_s(4u * (uint32_t)pick, ct[h], ct_base);
@@ -711,14 +709,27 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
                 yv[h] = lds_load_i8(ya - 64u * h);
                 zv[h] = lds_load_i8(za + 128u * h);
             }
-            const int tabu_new = readlane(expire, slot);  // t + tenure
-            const int gain = N - 1 + m - 8 * (t - 1);     // (E' - E) / 4
-            E += 4 * gain;
-            thr -= gain - 8;
+            if constexpr (NW > 1) vsp = lds_load_i8(pa);
+            const int gain = m - off;  // (E' - E) / 4 = N - 1 + d_p
+            off += 8;
+            above += gain;
+            asp += gain;
+            const int tabu_new = readlane(expire, slot);  // slot + tenure
+            const int d_new = off - gain;  // -d_p - 2 (N - 1), as D
+            if constexpr (NW == 1) {
+                const int nsp = readlane(nr[0], src);
+                q0[0] = qv[0];
+                move_term<true>(cv[0], qv[0], yv[0], zv[0], nr[0], nsp, D[0]);
+            } else {
+                const int nsp = -vsp >> 2;
+#pragma unroll
+                for (int h = 0; h < NW; ++h) {
+                    q0[h] = qv[h];
+                    move_term<false>(cv[h], qv[h], yv[h], zv[h], nr[h], nsp, D[h]);
+                }
+            }
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
-                q0[h] = qv[h];
-                move_term<true>(cv[h], qv[h], yv[h], zv[h], nr[h], nsp, D[h]);
                 lds_store_i32(ca[h], cv[h]);
                 lds_store_i32(qa + 256u * h, qv[h]);
             }
@@ -728,31 +739,37 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             for (int h = 0; h < NW; ++h) {
                 if (word == h) {
                     if (lane_bit(1ull << src)) {
-                        D[h] = 8 * t - gain - (N - 1);  // -d_p - 2 (N - 1), + 8 t
-                        tabu[h] = tabu_new;
                         lds_store_i32(qa + 256u * h, q0[h]);
                         lds_store_i8(za + 128u * h, 4 * nr[h]);  // 4 s_p, after the move
+                        D[h] = d_new;
+                        tabu[h] = tabu_new;
                         nr[h] = -nr[h];
                     }
                 }
             }
-            if (E < bestE) {
-                bestE = E;
-                thr = thr0 + 8 * t;
+            if (__builtin_expect(above < 0, 0)) {
+                best4 += above;
+                above = 0;
+                asp = asp0;
                 uint64_t b[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
                 for (int h = 0; h < NW; ++h) b[h] = ballot(nr[h] > 0);
                 best = make_mask<NW>(b[0], b[1], b[2], b[3]);
             }
-            if constexpr (TRACE) trace[t - 1] = (int16_t)pick;  // uniform store
+            if constexpr (TRACE) trace[t0 + slot - 1] = (int16_t)pick;  // uniform store
             wave_sync();
+        }
+#pragma unroll
+        for (int h = 0; h < NW; ++h) {
+            D[h] -= 8 * 64;
+            tabu[h] -= 64;
         }
     }
 
     WalkResult<NW> res;
     res.best = best;
-    res.best_e = bestE;
-    res.final_e = E;
+    res.best_e = E0 + 4 * best4;
+    res.final_e = E0 + 4 * (best4 + above);
     return res;
 }
 
