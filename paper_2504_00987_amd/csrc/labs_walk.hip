@@ -1,6 +1,6 @@
 // Walk kernels of liblabs for gfx950 and their launchers.
 //
-//   energy_kernel   Eq. (2) for a batch of +-1 rows, one row per wave
+//   energy_kernel   Eq. (2) for a batch of +-1 rows, 64 rows per workgroup
 //   tabu_kernel     independent tabu walks (Alg. 2 / Alg. 4), one walk per
 //                   wave, either one wave per walk or a persistent grid
 //                   draining a longest-first work queue
@@ -23,35 +23,127 @@ namespace {
 // ---------------------------------------------------------------------------
 // Energies.
 // ---------------------------------------------------------------------------
-template <int WPG>
-__global__ __launch_bounds__(64 * WPG) void energy_kernel(const int8_t *__restrict__ seqs,
-                                                          const int32_t *__restrict__ ns,
-                                                          int32_t n_uniform, int32_t stride,
-                                                          int64_t count,
-                                                          int32_t *__restrict__ out) {
-    const int lane = lane_id();
-    const int64_t b = (int64_t)blockIdx.x * WPG + (threadIdx.x >> 6);
-    if (b >= count) return;
-    const int N = ns ? ns[b] : n_uniform;
-    const int8_t *row = seqs + b * (int64_t)stride;
-    uint64_t wd[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        const int i = lane + 64 * h;
-        wd[h] = ballot(i < N && row[i] < 0);
+// Sign bits of 16 bytes (bit i set <=> byte i < 0).
+__device__ __forceinline__ uint32_t sign_bits16(const uint4 &v) {
+    auto four = [](uint32_t w, uint32_t weights, uint32_t acc) {
+        return (uint32_t)__builtin_amdgcn_udot4((w >> 7) & 0x01010101u, weights, acc, false);
+    };
+    const uint32_t lo = four(v.y, 0x80402010u, four(v.x, 0x08040201u, 0u));
+    const uint32_t hi = four(v.w, 0x80402010u, four(v.z, 0x08040201u, 0u));
+    return lo | (hi << 8);
+}
+
+// Bits [16 c, 16 c + 16) of a row's mask (bit i set <=> s_i = -1; bits past N
+// clear).  Rows may have any alignment and stride: the 16 bytes are read at
+// any address (global loads need no alignment on this target), and the last
+// chunk of a row from its last 16 bytes, so nothing past N is read.
+__device__ __forceinline__ uint32_t row_bits16(const int8_t *row, int c, int N) {
+    const int x = 16 * c;
+    if (x >= N) return 0u;
+    uint32_t bits;
+    if (N >= 16) {
+        const int at = min(x, N - 16);
+        uint4 v;
+        __builtin_memcpy(&v, row + at, 16);
+        bits = sign_bits16(v) >> (x - at);
+    } else {
+        bits = 0u;
+        for (int i = 0; i < N; ++i) bits |= (uint32_t)(row[i] < 0) << i;
     }
-    const M256 M{wd[0], wd[1], wd[2], wd[3]};
-    int acc = 0;
+    return bits & (N - x >= 16 ? 0xFFFFu : (1u << (N - x)) - 1u);
+}
+
+// Part of one row's energy in one lane: the lags k0, k0 + STEP, .. below
+// nmax (>= N), with the row's mask in W words:
+//   C_k = (N - k) - 2 popc over k <= i < N of (M ^ (M << k)).
+// M << k moves by STEP bits a lag; of lags in [32 b, 32 b + 32) the words
+// below b hold no pair.  Lags past N add nothing (N - k saturates at 0).
+template <int W, int STEP>
+__device__ __forceinline__ int lane_lags(const uint32_t *mask, int N, int nmax, int k0) {
+    static_assert(STEP < 32, "shifts stay within two words");
+    uint32_t M[W], Y[W], V[W];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const int k = lane + 1 + 64 * w;
-        if (k < N) {
-            const int c = lag_corr(M, N, k);
-            acc += c * c;
+    for (int w = 0; w < W; ++w) {
+        M[w] = mask[w];
+        const int n = N - 32 * w;  // valid bits of word w
+        V[w] = n >= 32 ? ~0u : n <= 0 ? 0u : (1u << n) - 1u;
+    }
+#pragma unroll
+    for (int w = W - 1; w >= 0; --w)
+        Y[w] = w ? __builtin_amdgcn_alignbit(M[w], M[w - 1], (uint32_t)(32 - k0)) : M[w] << k0;
+    int k = k0, e = 0;
+    uint32_t left = (uint32_t)max(N - k0, 0);  // N - k
+#pragma unroll
+    for (int b = 0; b < W; ++b) {
+        const int end = min(nmax, 32 * (b + 1));
+        for (; k < end; k += STEP) {
+            int pop = __popc((M[b] ^ Y[b]) & (V[b] & (~0u << (k & 31))));
+#pragma unroll
+            for (int w = b + 1; w < W; ++w) pop += __popc((M[w] ^ Y[w]) & V[w]);
+            const int c = mad_i24_const<-2>(pop, (int)left);
+            e = mad_i24(c, c, e);
+            left = __builtin_elementwise_sub_sat(left, (uint32_t)STEP);
+#pragma unroll
+            for (int w = W - 1; w > b; --w)
+                Y[w] = __builtin_amdgcn_alignbit(Y[w], Y[w - 1], 32 - STEP);
+            Y[b] <<= STEP;
         }
     }
-    const int E = wave_sum(acc);
-    out[b] = E;  // every lane stores the same value: no lane-0 branch
+    return e;
+}
+
+// Eq. (2) for 64 rows per workgroup: the rows' sign bits are packed into LDS
+// with 16-byte loads, then lane l of every wavefront holds row l as a bit
+// mask and the four wavefronts take every fourth lag.  Bound: VALU, three
+// instructions per 32 pairs and lag and four per lag (row l in one lane needs
+// no cross-lane sum, and a shift by a fixed number of bits is one instruction
+// a word; a row per wavefront takes twice as many).  262144 rows of N in
+// 20..128 (34 MB): 124 -> 15.9 us a call against a row per wavefront on
+// 256-bit masks.
+constexpr int kEnergyRows = 64, kEnergyWaves = 4;
+__global__ __launch_bounds__(64 * kEnergyWaves) void energy_kernel(
+    const int8_t *__restrict__ seqs, const int32_t *__restrict__ ns, int32_t n_uniform,
+    int32_t stride, int64_t count, int32_t *__restrict__ out) {
+    constexpr int kWords = 8;
+    // rows of 9 words: lanes read their rows' words without bank conflicts
+    __shared__ uint32_t mask[kEnergyRows][kWords + 1];
+    __shared__ int part[kEnergyWaves][kEnergyRows];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t r0 = (int64_t)blockIdx.x * kEnergyRows;
+    const int rows = (int)min((int64_t)kEnergyRows, count - r0);
+    const int N = lane < rows ? (ns ? ns[r0 + lane] : n_uniform) : 0;
+    const int nmax = -wave_min(-N);
+    const int words = (nmax + 31) >> 5;
+    // 2 * words chunks of 16 bytes a row
+    const int chunks = 2 * words;
+    for (int i = (int)threadIdx.x; i < kEnergyRows * chunks; i += 64 * kEnergyWaves) {
+        const int r = i / chunks, c = i - r * chunks;
+        uint32_t bits = 0u;
+        if (r < rows)
+            bits = row_bits16(seqs + (r0 + r) * (int64_t)stride, c,
+                              ns ? ns[r0 + r] : n_uniform);
+        ((uint16_t *)mask[r])[c] = (uint16_t)bits;
+    }
+    __syncthreads();
+    const uint32_t *m = mask[lane];
+    int e = 0;
+    switch (words) {  // wave-uniform
+    case 1: e = lane_lags<1, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 2: e = lane_lags<2, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 3: e = lane_lags<3, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 4: e = lane_lags<4, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 5: e = lane_lags<5, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 6: e = lane_lags<6, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    case 7: e = lane_lags<7, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    default: e = lane_lags<8, kEnergyWaves>(m, N, nmax, wave + 1); break;
+    }
+    part[wave][lane] = e;
+    __syncthreads();
+    if (wave == 0 && lane < rows) {
+#pragma unroll
+        for (int w = 1; w < kEnergyWaves; ++w) e += part[w][lane];
+        out[r0 + lane] = e;
+    }
 }
 
 
@@ -517,9 +609,9 @@ hipError_t launch_in_ranges(int64_t begin, int64_t end, int per_group, int lanes
 hipError_t launch_energy(const int8_t *seqs, const int32_t *ns, int32_t n_uniform,
                          int32_t stride, int64_t count, int32_t *out, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    constexpr int WPG = 4;
-    return launch_in_ranges(0, count, WPG, 64 * WPG, [&](int64_t b, int64_t e, unsigned grid) {
-        hipLaunchKernelGGL(energy_kernel<WPG>, dim3(grid), dim3(64 * WPG), 0, s,
+    return launch_in_ranges(0, count, kEnergyRows, 64 * kEnergyWaves,
+                            [&](int64_t b, int64_t e, unsigned grid) {
+        hipLaunchKernelGGL(energy_kernel, dim3(grid), dim3(64 * kEnergyWaves), 0, s,
                            seqs + b * (int64_t)stride, ns ? ns + b : nullptr, n_uniform, stride,
                            e - b, out + b);
     });
