@@ -45,3 +45,16 @@ def test_energy_mixed_lengths_in_one_group(lb, lo, hi, count):
     rows, dev = _packed_rows(ns, hi + 3, 5, seed=hi)
     got = lb.energy_batch(dev, ns=torch.from_numpy(ns).cuda()).cpu().numpy()
     assert np.array_equal(got, O.energy_batch(rows, ns=ns))
+
+
+@pytest.mark.parametrize("n", [3, 4, 31, 32, 62, 63, 64, 65, 66, 67, 68, 127, 128, 129, 130, 131,
+                               132, 191, 192, 193, 194, 195, 255, 256])
+def test_skew_deviation_word_edges(lb, n):
+    # around the lengths where a candidate's pairs fill whole 32-bit words,
+    # all-equal and alternating rows (the most and fewest broken pairs) included
+    rows, dev = _packed_rows([n] * 7, n + 1, 1, seed=n)
+    rows[0, :n] = 1
+    rows[1, :n] = 1 - 2 * (np.arange(n) % 2)
+    dev[:2, :n] = torch.from_numpy(rows[:2, :n]).cuda()
+    got = lb.skew_deviation(dev, n_uniform=n).cpu().numpy()
+    assert np.array_equal(got, [O.skew_deviation(r[:n]) for r in rows])
