@@ -398,10 +398,19 @@ static int bruteforce_impl(labs_handle *h, int32_t n, bool skew, int32_t *min_e,
                            int8_t *argmin) {
     DeviceGuard g(h->device);
     hipStream_t s = h->stream;
-    const int64_t waves = skew ? skew_brute_waves(n) : brute_waves(n);
-    // Workspace: [out e | out count | out code (256 B)] [part e] [part count] [part code]
+    // unrestricted searches that a bound shortens start from the best of a
+    // batch of short walks
+    const bool search = !skew && n >= kSearchMinN;
+    constexpr int kWalks = 4096, kWalkStride = 64;
+    const int64_t waves = skew ? skew_brute_waves(n) : search ? search_waves() : brute_waves(n);
+    // Workspace: [out e | out count | out code | bound (256 B)] [part e]
+    // [part count] [part code] [walk heads | walk e, e | walk sequences] [queue]
     const size_t off_e = 256, off_c = off_e + 8 * (size_t)waves, off_k = off_c + 8 * (size_t)waves;
-    int rc = ws_acquire(h, s, off_k + 8 * (size_t)waves);
+    const size_t off_w = (off_k + 8 * (size_t)waves + 255) & ~(size_t)255;
+    constexpr size_t kHeads = 32 * sizeof(uint32_t) * kWalkClasses;
+    const size_t off_q = kHeads + (size_t)kWalks * (8 + kWalkStride);
+    const size_t walk_bytes = search ? off_q + search_queue_bytes() : 0;
+    int rc = ws_acquire(h, s, off_w + walk_bytes);
     if (rc) return rc;
     char *base = (char *)h->ws.ptr;
     BruteParts p;
@@ -411,7 +420,35 @@ static int bruteforce_impl(labs_handle *h, int32_t n, bool skew, int32_t *min_e,
     p.part_e = (int32_t *)(base + off_e);
     p.part_count = (int64_t *)(base + off_c);
     p.part_code = (uint64_t *)(base + off_k);
-    hipError_t e = skew ? launch_skew_bruteforce(n, p, s) : launch_bruteforce(n, p, s);
+    hipError_t e = hipSuccess;
+    if (search) {
+        TabuLaunchArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.counter = (uint32_t *)(base + off_w);
+        a.best_e = (int32_t *)(base + off_w + kHeads);
+        a.final_e = a.best_e + kWalks;
+        a.best_seq = (int8_t *)(a.final_e + kWalks);
+        a.out_stride = kWalkStride;
+        a.n_uniform = a.n_max = n;
+        a.W = kWalks;
+        const int cls = walk_class(n);
+        for (int k = 0; k < kWalkClasses; ++k) a.class_end[k] = k >= cls ? kWalks : 0;
+        // 2N steps, tenure U[N/10, N/5], aspiration
+        a.rule.steps_rule = LABS_STEPS_MULT_N;
+        a.rule.steps_a = 2;
+        a.rule.lo_num = a.rule.hi_num = 1;
+        a.rule.lo_den = 10;
+        a.rule.hi_den = 5;
+        a.rule.aspiration = 1;
+        a.rule.slo_den = a.rule.shi_den = 1;
+        const WalkLaunch l = walk_launch(h, default_launch(n));
+        e = launch_tabu(a, l, &s);
+        if (e == hipSuccess)
+            e = launch_search(n, p, a.best_e, kWalks, (uint32_t *)(base + off_w + off_q),
+                              (int32_t *)(base + 24), s);
+    } else {
+        e = skew ? launch_skew_bruteforce(n, p, s) : launch_bruteforce(n, p, s);
+    }
     if (e != hipSuccess) return hip_fail(h, e, "exhaustive search launch");
     if ((rc = stage_acquire(h, 24))) return rc;
     e = hipMemcpyAsync(h->pin.ptr, base, 24, hipMemcpyDeviceToHost, s);

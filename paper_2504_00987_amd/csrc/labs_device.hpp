@@ -122,6 +122,17 @@ __device__ __forceinline__ int wave_sum(int v) {
     return readlane(v, 0) + readlane(v, 16) + readlane(v, 32) + readlane(v, 48);
 }
 
+// Next index of the persistent work queue, wave-uniform.  Every lane executes
+// the atomic (lane 0 adds 1, the others add 0) so that the value read back
+// with readlane is never produced under a lane-dependent branch: a
+// lane-0-only fetch lets the optimiser thread that branch into the loop's
+// other lane-0 branches, and lanes then reach the readlane before lane 0 has
+// fetched, disagreeing on the index.
+__device__ __forceinline__ uint32_t next_work(uint32_t *counter, uint32_t take = 1u) {
+    const uint32_t v = atomicAdd(counter, lane_id() == 0 ? take : 0u);
+    return readlane_u(v, 0);
+}
+
 // ---------------------------------------------------------------------------
 // Sequence masks: 64-bit for N <= 64, 128-bit for N <= 128, 256-bit for
 // N <= 256.

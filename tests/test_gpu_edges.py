@@ -58,3 +58,45 @@ def test_skew_deviation_word_edges(lb, n):
     dev[:2, :n] = torch.from_numpy(rows[:2, :n]).cuda()
     got = lb.skew_deviation(dev, n_uniform=n).cpu().numpy()
     assert np.array_equal(got, [O.skew_deviation(r[:n]) for r in rows])
+
+
+def _enumerated_min(n):
+    """(E_min, count over all 2^n, smallest code with s_0 = +1) by Eq. 1-2 on
+    every code, as plain tensor arithmetic on 64-bit integers."""
+    best, count, first = 1 << 30, 0, None
+    step = 1 << 22
+    for c0 in range(0, 1 << (n - 1), step):
+        code = torch.arange(c0, min(c0 + step, 1 << (n - 1)), device="cuda") * 2
+        bit = [1 - 2 * ((code >> i) & 1) for i in range(n)]
+        e = torch.zeros_like(code)
+        for k in range(1, n):
+            c = torch.zeros_like(code)
+            for i in range(n - k):
+                c += bit[i] * bit[i + k]
+            e += c * c
+        m = int(e.min())
+        if m <= best:
+            at = code[e == m]
+            if m < best:
+                best, count, first = m, 0, int(at[0])
+            count += 2 * at.numel()
+    return best, count, first
+
+
+# both sides of the line between enumeration and branch and bound
+@pytest.mark.parametrize("n", [23, 24, 25, 26])
+def test_exhaustive_minimum_both_methods(lb, n):
+    e, count, seq = lb.bruteforce_min(n)
+    code = sum(1 << i for i, s in enumerate(seq) if s < 0)
+    assert (e, count, code) == _enumerated_min(n)
+
+
+# odd and even lengths, 32- and 64-bit masks; values of the plain enumeration of all 2^(n-1) codes
+@pytest.mark.parametrize("n,e,count,code", [
+    (28, 50, 8, 0x4b7770e), (29, 62, 8, 0x31fd5b2), (30, 59, 16, 0x1f6d5ce),
+    (31, 67, 8, 0x52b26380), (32, 64, 8, 0x14ae326), (33, 64, 8, 0x13355a780),
+    (34, 65, 8, 0xcc01e5aa), (35, 73, 8, 0x9b2b51c)])
+def test_exhaustive_minimum_search(lb, n, e, count, code):
+    got_e, got_count, seq = lb.bruteforce_min(n)
+    assert (got_e, got_count) == (e, count)
+    assert sum(1 << i for i, s in enumerate(seq) if s < 0) == code
