@@ -375,18 +375,6 @@ __device__ __forceinline__ bool lane_bit(uint64_t mask) {
     return __builtin_amdgcn_inverse_ballot_w64(mask);
 }
 
-// Four bytes 4 s_x .. 4 s_{x+3} of a sequence given as a mask (bit set <=>
-// -1): 0x04 for +1, 0xFC for -1, 0 past the end.
-template <typename Mask>
-__device__ __forceinline__ uint32_t pack4(Mask M, int x, int N) {
-    if (x >= N) return 0u;
-    const uint32_t nib = (uint32_t)mask_lo(m_shr(M, x)) & 0xFu;
-    const int cnt = min(N - x, 4);
-    const uint32_t valid = cnt >= 4 ? 0x04040404u : (0x04040404u & ((1u << (8 * cnt)) - 1u));
-    const uint32_t ones = (nib * 0x00204081u) & 0x01010101u;  // bit b -> byte b
-    return valid | (ones * 0xF8u);
-}
-
 __device__ __forceinline__ int dot4(uint32_t a, uint32_t b, int acc) {
     return __builtin_amdgcn_sdot4((int)a, (int)b, acc, false);
 }
@@ -459,19 +447,9 @@ __device__ __forceinline__ void move_term(int &c, int &q, int y, int z, int nr, 
     q = mad_i24_const<-8>(x, q);
 }
 
-// Q_m = sum_{a + b = m} s_a s_b over ordered pairs inside the sequence, for
-// 0 <= m <= 2N - 2 (0 beyond); bit i of Mr is bit N - 1 - i of M.
-template <typename Mask>
-__device__ __forceinline__ int pair_sum(Mask M, Mask Mr, int N, int m) {
-    if (m > 2 * N - 2) return 0;
-    const bool low = m < N;
-    const int cnt = low ? m + 1 : 2 * N - 1 - m;
-    const Mask A = m_shr(low ? Mr : M, low ? N - 1 - m : m - (N - 1));
-    return cnt - 2 * m_popc(m_and(m_xor(A, low ? M : Mr), m_low(M, cnt)));
-}
-
 // Runs one walk of sch.T steps from mask M0 (bits >= N must be clear) on one
-// wavefront, lane l owning neighbours j = l + 64h, h < NW (N <= 64 NW).
+// wavefront, lane l owning neighbours j = l + 64h, h < NW (64 (NW - 1) < N <=
+// 64 NW).
 //
 // The step is O(N).  Neighbour j's key is d_j = 2 u_j - s_j v_j with
 // v_j = sum_k t_jk C_k and 2 u_j = Q_2j - 1 (candE_j = E + 4 (N - 1) + 4 d_j).
@@ -499,7 +477,9 @@ __device__ __forceinline__ int pair_sum(Mask M, Mask Mr, int N, int m) {
 // walks, MI355X): 4096 walks of N = 64 and 256 steps 131 -> 94.5 us, of
 // N = 120 and 480 steps 717 -> 269 us, of N in 129..256 3.90 -> 0.64 ms; with
 // the scalar bookkeeping of a step cut to what is listed below (29 scalar
-// instructions for 48 at N <= 64) 87 us, 238 us and 0.61 ms.
+// instructions for 48 at N <= 64) 87 us, 238 us and 0.61 ms; with the tables
+// filled from 64-bit shifts by the lane number instead of full-width variable
+// ones (a walk's start at N = 256 24 -> 5 us) the last 0.54 ms.
 //   lds    WalkLds<NW>::BYTES bytes of per-walk scratch, 16-aligned
 //   trace  with TRACE: trace[t-1] = flipped index
 // Every lane must call this with identical uniform inputs.
@@ -525,76 +505,113 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     sch.hi = __builtin_amdgcn_readfirstlane(sch_in.hi);
     const Mask M = make_mask<NW>(uniform64(mask_word(M0, 0)), uniform64(mask_word(M0, 1)),
                                  uniform64(mask_word(M0, 2)), uniform64(mask_word(M0, 3)));
-    // bit i of Mr is bit N-1-i of M
-    Mask Mr;
+    // words of M and of its reversal (bit i of R is bit N-1-i of M)
+    uint64_t Mw[NW], Rw[NW];
     {
-        uint64_t r[4] = {0ull, 0ull, 0ull, 0ull};
+        const int sh = 64 * NW - N;  // 0 .. 63
+        uint64_t b[NW];
 #pragma unroll
-        for (int h = 0; h < NW; ++h) {
-            const int i = lane + 64 * h;
-            r[h] = ballot(i < N && m_bit(M, N - 1 - i));
+        for (int w = 0; w < NW; ++w) {
+            Mw[w] = mask_word(M, w);
+            b[NW - 1 - w] = __builtin_bitreverse64(Mw[w]);
         }
-        Mr = make_mask<NW>(r[0], r[1], r[2], r[3]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            Rw[w] = (b[w] >> sh) | (w + 1 < NW ? (b[w + 1] << 1) << (63 - sh) : 0ull);
     }
     int32_t *const CT = (int32_t *)(lds + L::CT);
     int32_t *const QT = (int32_t *)(lds + L::QT);
+    int8_t *const SP = (int8_t *)(lds + L::SP);
 
-    // The tables from the masks.  C is first mirrored around zero as int8
-    // (C_k >> 1 for NW > 2, where |C_k| may reach 255), in four copies
-    // shifted by 0..3 bytes over the space of Q, so that every lane reads its
-    // window C_|i-j|, i = 0, 1, .., as aligned dwords for the v_j products.
-    constexpr bool kHalfC = NW > 2;
+    // C_s, Q_(N-1-s) and Q_(N-1+s) for s = lane + 64h from popcounts: with the
+    // reversal R, over the N - s positions i < N - s,
+    //   C_s pairs M_i, M_(i+s);  Q_(N-1-s) M_i, R_(i+s);  Q_(N-1+s) R_i, M_(i+s).
+    // Bits i >= N - s of the first operand, which meet zeros, are taken off
+    // again: the first s bits of R (of M where the operand is R).
     wave_sync();
-    for (int idx = lane; idx < 48 * NW; idx += 64) {
-        const int x = 4 * idx - 64 * NW;  // SP[x .. x+3]
-        ((uint32_t *)(lds + L::SPLO))[idx] = x < 0 ? 0u : pack4(M, x, N);
+    int C[NW], nr[NW];  // nr: -s_j, 0 past the sequence
+    int sq_e = 0;       // sum of C_k^2 over this lane's lags
+    int below_m = 0, below_r = 0;  // set bits of the words below
+#pragma unroll
+    for (int h = 0; h < NW; ++h) {
+        const int j = lane + 64 * h;
+        int pc = 0, pl = 0, ph = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            uint64_t xm = 0ull, xr = 0ull;  // words w of M >> j and R >> j
+            if (w + h < NW) {
+                xm = Mw[w + h] >> lane;
+                xr = Rw[w + h] >> lane;
+            }
+            if (w + h + 1 < NW) {
+                xm |= (Mw[w + h + 1] << 1) << (63 - lane);
+                xr |= (Rw[w + h + 1] << 1) << (63 - lane);
+            }
+            pc += __popcll(Mw[w] ^ xm);
+            pl += __popcll(Mw[w] ^ xr);
+            ph += __popcll(Rw[w] ^ xm);
+        }
+        auto below = [&](uint64_t m, int from) {  // `from` + set bits of m below this lane
+            return (int)__builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)from));
+        };
+        const int tm = below(Mw[h], below_m), tr = below(Rw[h], below_r);
+        below_m += __popcll(Mw[h]);
+        below_r += __popcll(Rw[h]);
+        const bool in = j < N;
+        C[h] = in && j > 0 ? N - j - 2 * (pc - tr) : 0;
+        sq_e += C[h] * C[h];
+        nr[h] = in ? (lane_bit(Mw[h]) ? 1 : -1) : 0;
+        if (in) {
+            QT[N - 1 - j] = 2 * (N - j - 2 * (pl - tr));
+            QT[N - 1 + j] = 2 * (N - j - 2 * (ph - tm));
+        }
+        SP[j] = (int8_t)(-4 * nr[h]);
     }
-    int sq_e = 0;  // sum of C_k^2 over this lane's lags
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {  // zeros around the sequence, 64 bytes at a time
+        const int at = lane < 16 ? -64 * NW + 64 * i + 4 * lane : 64 * NW + 64 * i + 4 * (lane - 16);
+        if (lane < 32) *(int32_t *)(SP + at) = 0;
+    }
+
+    // v_j = sum_i s_i C_|i-j|: C mirrored around zero as bytes (C_k >> 1 for
+    // NW > 2, where |C_k| may reach 255), for now in the place of C; a lane's
+    // window starts at any byte, so four dwords at a time are aligned.
+    constexpr bool kHalfC = NW > 2;
+    int8_t *const F = (int8_t *)CT;  // F[64 NW + k] = F[64 NW - k] = C_k, 0 at k = 0
+    static_assert(128 * NW + 16 <= L::QT - L::CT, "the mirrored bytes fit");
 #pragma unroll
     for (int h = 0; h < NW; ++h) {
         const int k = lane + 64 * h;
-        const int c = k > 0 && k < N ? lag_corr(M, N, k) : 0;
-        CT[k] = 2 * c;
-        sq_e += c * c;
+        const int8_t c = (int8_t)(kHalfC ? C[h] >> 1 : C[h]);
+        F[64 * NW + k] = c;
+        F[64 * NW - k] = c;
     }
     wave_sync();
-    // F[x] = C_|x - 64 NW| (0 at lag 0), copy r at dword 32 NW r holding
-    // F[r ..]
-#pragma unroll
-    for (int i = 0; i < 2 * NW; ++i) {
-        const int dw = lane + 64 * i;
-        const int r = dw / (32 * NW), x = 4 * (dw - 32 * NW * r) + r - 64 * NW;
-        uint32_t w = 0u;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int k = x + b < 0 ? -(x + b) : x + b;
-            const int c = k < 64 * NW ? CT[k] : 0;
-            w |= (uint32_t)((kHalfC ? c >> 2 : c >> 1) & 0xFF) << (8 * b);
-        }
-        ((uint32_t *)QT)[dw] = w;
-    }
-    wave_sync();
-    int D[NW], nr[NW], tabu[NW];  // nr: -s_j, 0 past the sequence
+    int D[NW], tabu[NW];
     {
         int v[NW];
         const uint32_t *win[NW];
+        uint32_t last[NW];
 #pragma unroll
         for (int h = 0; h < NW; ++h) {
-            const int j = lane + 64 * h;
-            const int x0 = 64 * NW - j;  // C_|i-j| = F[x0 + i]
-            win[h] = (const uint32_t *)QT + 32 * NW * (x0 & 3) + (x0 >> 2);
+            win[h] = (const uint32_t *)F + ((64 * NW - 64 * h - lane) >> 2);
+            last[h] = win[h][0];
             v[h] = 0;
         }
-        const uint4 *const S16 = (const uint4 *)(lds + L::SP);
+        const uint32_t shift = (uint32_t)(-lane) & 3u;
+        const uint4 *const S16 = (const uint4 *)SP;
         for (int i = 0; i < N; i += 16) {
             const uint4 s = S16[i >> 4];
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
                 const uint32_t *w = win[h] + (i >> 2);
-                v[h] = dot4(w[0], s.x, v[h]);
-                v[h] = dot4(w[1], s.y, v[h]);
-                v[h] = dot4(w[2], s.z, v[h]);
-                v[h] = dot4(w[3], s.w, v[h]);
+                const uint32_t a = w[1], b = w[2], c = w[3], d = w[4];
+                v[h] = dot4(__builtin_amdgcn_alignbyte(a, last[h], shift), s.x, v[h]);
+                v[h] = dot4(__builtin_amdgcn_alignbyte(b, a, shift), s.y, v[h]);
+                v[h] = dot4(__builtin_amdgcn_alignbyte(c, b, shift), s.z, v[h]);
+                v[h] = dot4(__builtin_amdgcn_alignbyte(d, c, shift), s.w, v[h]);
+                last[h] = d;
             }
         }
         // parity part of v_j where the products took C_k >> 1 = (C_k -
@@ -603,26 +620,29 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
         int S0 = 0, S1 = 0;
         if constexpr (kHalfC) {
             constexpr uint64_t kEven = 0x5555555555555555ull;
-            const M256 ev{kEven, kEven, kEven, kEven};
-            S0 = (N + 1) / 2 - 2 * m_popc(m_and(M, ev));
-            S1 = N / 2 - 2 * m_popc(m_and(M, m_not(ev)));
+            S0 = (N + 1) / 2;
+            S1 = N / 2;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                S0 -= 2 * __popcll(Mw[w] & kEven);
+                S1 -= 2 * __popcll(Mw[w] & ~kEven);
+            }
         }
         const int Sq = ((lane + N - 1) & 1) ? S1 : S0;  // the same for lane + 64h
 #pragma unroll
         for (int h = 0; h < NW; ++h) {
             const int j = lane + 64 * h;
-            nr[h] = j < N ? (lane_bit(mask_word(M, h)) ? 1 : -1) : 0;
             v[h] >>= 2;  // the spins of SP are scaled by 4
             if constexpr (kHalfC) v[h] = 2 * v[h] + Sq + ((N & 1) ? nr[h] : 0);
             // Q_2j - 1 - s_j v_j; beyond the sequence never a minimum
-            D[h] = j < N ? pair_sum(M, Mr, N, 2 * j) - 1 + nr[h] * v[h] : 0x3fffffff;
+            D[h] = j < N ? (QT[2 * j] >> 1) - 1 + nr[h] * v[h] : 0x3fffffff;
             // lanes past the sequence are never admissible: infinite tenure
             tabu[h] = j < N ? -1 : INT_MAX;
         }
     }
     wave_sync();
 #pragma unroll
-    for (int i = 0; i < 2 * NW; ++i) QT[lane + 64 * i] = 2 * pair_sum(M, Mr, N, lane + 64 * i);
+    for (int h = 0; h < NW; ++h) CT[lane + 64 * h] = 2 * C[h];
     wave_sync();
 
     const int E0 = wave_sum(sq_e);
