@@ -434,17 +434,34 @@ __device__ __forceinline__ int mul_i24_s(int a, int b) {  // b wave-uniform
 }
 
 // One neighbour's part of a move at p (see tabu_walk): c = 2 C_|p-j|,
-// q = 2 Q_(p+j), y = 4 s_(2p-j), z = 4 s_(2j-p), nr = -s_j, nsp = -s_p
-// (wave-uniform when UNIFORM).  Returns the new c and q and adds the change
-// to D_j: seven instructions.
-template <bool UNIFORM>
-__device__ __forceinline__ void move_term(int &c, int &q, int y, int z, int nr, int nsp, int &D) {
-    const int x = UNIFORM ? mul_i24_s(nr, nsp) : mul_i24(nr, nsp);
-    const int e = UNIFORM ? mad_i24_s(y, nsp, c) : mad_i24(y, nsp, c);  // 2 C_k - 4y
+// q = 2 Q_(p+j), y = 4 s_(2p-j), z = 4 s_(2j-p), nsp = -s_p, nsp4 = -4 s_p
+// (wave-uniform) and x = 4 s_p s_j.  Adds the change of 4 D_j and returns
+// e = 2 C_k - 4y; the entries' new values are e - x and q - 2x.
+__device__ __forceinline__ void move_score(int c, int q, int y, int z, int nsp, int nsp4, int x,
+                                           int &D, int &e) {
+    e = mad_i24_s(y, nsp, c);
     D = mad_i24(x, c + e + q, D);
-    D = UNIFORM ? mad_i24_s(z, nsp, D) : mad_i24(z, nsp, D);
-    c = mad_i24_const<-4>(x, e);
-    q = mad_i24_const<-8>(x, q);
+    D = mad_i24_s(z, nsp4, D);
+}
+
+// The moved position, the one lane of `bit`: -4 s_p (nr) stored as its new
+// spin at LDS offset za and negated, x = 0, and D and tabu set to wave-uniform
+// values.  (A masked block without a branch, so that the step stays one run
+// of instructions.)
+__device__ __forceinline__ void set_moved(uint64_t bit, uint32_t za, int d_new, int tabu_new,
+                                          int &nr, int &x, int &D, int &tabu) {
+    uint64_t all;
+    asm volatile(
+        "s_and_saveexec_b64 %0, %5\n\t"
+        "ds_write_b8 %6, %1\n\t"
+        "v_mov_b32 %2, 0\n\t"
+        "v_mov_b32 %3, %7\n\t"
+        "v_mov_b32 %4, %8\n\t"
+        "v_sub_u32 %1, 0, %1\n\t"
+        "s_mov_b64 exec, %0"
+        : "=&s"(all), "+v"(nr), "+v"(x), "+v"(D), "+v"(tabu)
+        : "s"(bit), "v"(za), "s"(d_new), "s"(tabu_new)
+        : "memory", "scc");
 }
 
 // Runs one walk of sch.T steps from mask M0 (bits >= N must be clear) on one
@@ -471,15 +488,13 @@ __device__ __forceinline__ void move_term(int &c, int &q, int y, int z, int nr, 
 // their D never falls to an aspiration threshold.
 //
 // Bound: the instructions a wavefront issues and, with few wavefronts, one
-// chain of an LDS round trip, a wavefront minimum and the scalar pick.  One
-// wavefront per walk with NW neighbours per lane keeps that chain free of
-// barriers.  Against recomputing v_j from packed int8 products (the same
-// walks, MI355X): 4096 walks of N = 64 and 256 steps 131 -> 94.5 us, of
-// N = 120 and 480 steps 717 -> 269 us, of N in 129..256 3.90 -> 0.64 ms; with
-// the scalar bookkeeping of a step cut to what is listed below (29 scalar
-// instructions for 48 at N <= 64) 87 us, 238 us and 0.61 ms; with the tables
-// filled from 64-bit shifts by the lane number instead of full-width variable
-// ones (a walk's start at N = 256 24 -> 5 us) the last 0.54 ms.
+// chain of an LDS round trip, a wavefront minimum and the scalar pick.  So the
+// moved position is dealt with while the entries are on their way, and the
+// entries' new values are stored in the wait states of the minimum.  One
+// wavefront per walk with NW neighbours per lane keeps the chain free of
+// barriers.  Measured (MI355X, a call; recomputing v_j from packed int8
+// products -> this): 4096 walks of N = 64 and 256 steps 131 -> 82.7 us, of
+// N = 120 and 480 steps 717 -> 235 us, of N in 129..256 3.90 -> 0.53 ms.
 //   lds    WalkLds<NW>::BYTES bytes of per-walk scratch, 16-aligned
 //   trace  with TRACE: trace[t-1] = flipped index
 // Every lane must call this with identical uniform inputs.
@@ -529,7 +544,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     // Bits i >= N - s of the first operand, which meet zeros, are taken off
     // again: the first s bits of R (of M where the operand is R).
     wave_sync();
-    int C[NW], nr[NW];  // nr: -s_j, 0 past the sequence
+    int C[NW], nr[NW];  // nr: -4 s_j, 0 past the sequence
     int sq_e = 0;       // sum of C_k^2 over this lane's lags
     int below_m = 0, below_r = 0;  // set bits of the words below
 #pragma unroll
@@ -561,12 +576,12 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
         const bool in = j < N;
         C[h] = in && j > 0 ? N - j - 2 * (pc - tr) : 0;
         sq_e += C[h] * C[h];
-        nr[h] = in ? (lane_bit(Mw[h]) ? 1 : -1) : 0;
+        nr[h] = in ? (lane_bit(Mw[h]) ? 4 : -4) : 0;
         if (in) {
             QT[N - 1 - j] = 2 * (N - j - 2 * (pl - tr));
             QT[N - 1 + j] = 2 * (N - j - 2 * (ph - tm));
         }
-        SP[j] = (int8_t)(-4 * nr[h]);
+        SP[j] = (int8_t)-nr[h];
     }
 #pragma unroll
     for (int i = 0; i < NW; ++i) {  // zeros around the sequence, 64 bytes at a time
@@ -633,9 +648,9 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
         for (int h = 0; h < NW; ++h) {
             const int j = lane + 64 * h;
             v[h] >>= 2;  // the spins of SP are scaled by 4
-            if constexpr (kHalfC) v[h] = 2 * v[h] + Sq + ((N & 1) ? nr[h] : 0);
-            // Q_2j - 1 - s_j v_j; beyond the sequence never a minimum
-            D[h] = j < N ? (QT[2 * j] >> 1) - 1 + nr[h] * v[h] : 0x3fffffff;
+            if constexpr (kHalfC) v[h] = 2 * v[h] + Sq + ((N & 1) ? nr[h] >> 2 : 0);
+            // 4 (Q_2j - 1 - s_j v_j); beyond the sequence never a minimum
+            D[h] = j < N ? 2 * QT[2 * j] - 4 + nr[h] * v[h] : 0x3fffffff;
             // lanes past the sequence are never admissible: infinite tenure
             tabu[h] = j < N ? -1 : INT_MAX;
         }
@@ -647,11 +662,10 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
 
     const int E0 = wave_sum(sq_e);
     Mask best = M;
-    // Energies in units of 4 (a move changes E by 4 (N - 1 + d_p)): the best
-    // against E0, and how far the walk is above its best.  Aspiration:
-    // candE_j < bestE <=> d_j < (bestE - E) / 4 - (N - 1); without it `above`
-    // is kept far from every key.
-    int best4 = 0, above = 0;
+    // The best against E0, and how far the walk is above its best.
+    // Aspiration: candE_j < bestE <=> 4 d_j < bestE - E - 4 (N - 1); without
+    // it `asp` is kept far from every key.
+    int best_d = 0, above = 0;
     const int asp0 = aspiration ? 0 : 1 << 29;
     int asp = asp0;
     uint32_t ct[NW], qt, sy, sz;  // LDS addresses less their part in p
@@ -661,12 +675,31 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     qt = base + (uint32_t)(L::QT + 4 * lane);  // + 4p: Q_(p + lane)
     sy = base + (uint32_t)(L::SP - lane);      // + 2p: SP[2p - lane]
     sz = base + (uint32_t)(L::SP + 2 * lane);  // - p: SP[2 lane - p]
-    const uint32_t ct_base = base + (uint32_t)L::CT, sp0 = base + (uint32_t)L::SP;
+    const uint32_t ct_base = base + (uint32_t)L::CT;
+
+    // The least admissible key and the lanes that hold it, for the coming step.
+    int m;
+    uint64_t T[NW];
+    auto keys = [&](int slot, int thr, int *key) {
+        int kmin = INT_MAX;
+#pragma unroll
+        for (int h = 0; h < NW; ++h) {
+            key[h] = tabu[h] < slot || D[h] < thr ? D[h] : INT_MAX;
+            kmin = h ? min(kmin, key[h]) : key[h];
+        }
+        return kmin;
+    };
+    {
+        int key[NW];
+        m = wave_min(keys(0, -4 * (N - 1) - asp, key));
+#pragma unroll
+        for (int h = 0; h < NW; ++h) T[h] = ballot(key[h] == m);
+    }
 
     // Steps in blocks of 64: one Philox call per lane supplies the draws of
     // a block (read back with readlane), and the inner loop carries no
     // refill test.  Within a block the tenures count from its start, and
-    // D_j = d_j + 8 (moves made in the block).
+    // D_j = 4 d_j + 32 (moves made in the block).
     for (int t0 = 1; t0 <= sch.T; t0 += 64) {
         uint32_t dr0;
         int expire;  // lane l: slot l plus that step's tenure
@@ -675,27 +708,16 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             dr0 = d.w0;
             expire = lane + sch.lo + (int)below(d.w1, (uint32_t)(sch.hi - sch.lo + 1));
         }
-        const int steps = min(sch.T - t0 + 1, 64);
-        int off = -(N - 1);  // 8 (moves made in the block) - (N - 1)
-        for (int slot = 0; slot < steps; ++slot) {
-            const int thr = off - asp;
-            int key[NW];
-#pragma unroll
-            for (int h = 0; h < NW; ++h)
-                key[h] = tabu[h] < slot || D[h] < thr ? D[h] : INT_MAX;
-            int kmin = key[0];
-#pragma unroll
-            for (int h = 1; h < NW; ++h) kmin = min(kmin, key[h]);
-            const int m = wave_min(kmin);
-
+        const int steps = __builtin_amdgcn_readfirstlane(min(sch.T - t0 + 1, 64));
+        int off = -4 * (N - 1);  // 32 (moves made in the block) - 4 (N - 1)
+        int slot = 0;
+        do {
             // the chosen move: lane src of word `word` (the first word with a
             // minimum); of several tied moves the r-th (ascending),
             // r = (u0 * count) >> 32
-            uint64_t T[NW];
             int c[NW], count = 0;
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
-                T[h] = ballot(key[h] == m);
                 c[h] = __popcll(T[h]);
                 asm("" : "+s"(c[h]));  // 32-bit scalar arithmetic
                 count += c[h];
@@ -723,15 +745,12 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             const int src = __builtin_ctzll(tied);  // lane of the move
             const int pick = NW == 1 ? src : 64 * word + src;
 
-            // entries of the move (all reads before any write); -s_p from its
-            // lane, or (several words) from the sequence in LDS
+            // entries of the move (all reads before any write)
             const uint32_t qa = qt + 4u * (uint32_t)pick;
             const uint32_t ya = sy + 2u * (uint32_t)pick;
             const uint32_t za = sz - (uint32_t)pick;
-            const uint32_t pa = sp0 + (uint32_t)pick;
             uint32_t ca[NW];
-            int cv[NW], qv[NW], q0[NW], yv[NW], zv[NW];
-            int vsp = 0;
+            int cv[NW], qv[NW], yv[NW], zv[NW], e[NW], x[NW];
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
                 ca[h] = absdiff_add_s(4u * (uint32_t)pick, ct[h], ct_base);
@@ -739,47 +758,32 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
                 qv[h] = lds_load_i32(qa + 256u * h);
                 yv[h] = lds_load_i8(ya - 64u * h);
                 zv[h] = lds_load_i8(za + 128u * h);
+                asm("" : "+v"(yv[h]), "+v"(zv[h]));  // one sign-extending load each
             }
-            if constexpr (NW > 1) vsp = lds_load_i8(pa);
-            const int gain = m - off;  // (E' - E) / 4 = N - 1 + d_p
-            off += 8;
+
+            // While they are on their way: energies, the best, and all of the
+            // moved position: its new spin, tenure and key 4 (-d_p - 2 (N -
+            // 1)); with x = 0 its entry Q_2p stays, and the update below
+            // changes its D by z nsp4 = -16.
+            const int gain = m - off;  // E' - E = 4 (N - 1 + d_p)
+            off += 32;
             above += gain;
             asp += gain;
             const int tabu_new = readlane(expire, slot);  // slot + tenure
-            const int d_new = off - gain;  // -d_p - 2 (N - 1), as D
-            if constexpr (NW == 1) {
-                const int nsp = readlane(nr[0], src);
-                q0[0] = qv[0];
-                move_term<true>(cv[0], qv[0], yv[0], zv[0], nr[0], nsp, D[0]);
-            } else {
-                const int nsp = -vsp >> 2;
+            const int d_new = off - gain + 16;
+            const uint64_t bit = 1ull << src;
+            int nsp4 = 0;
 #pragma unroll
-                for (int h = 0; h < NW; ++h) {
-                    q0[h] = qv[h];
-                    move_term<false>(cv[h], qv[h], yv[h], zv[h], nr[h], nsp, D[h]);
+            for (int h = 0; h < NW; ++h)
+                if (NW == 1 || word == h) {
+                    nsp4 = readlane(nr[h], src);
+#pragma unroll
+                    for (int g = 0; g < NW; ++g) x[g] = mul_i24_s(nr[g], nsp4 >> 2);
+                    set_moved(bit, za + 128u * h, d_new, tabu_new, nr[h], x[h], D[h], tabu[h]);
                 }
-            }
-#pragma unroll
-            for (int h = 0; h < NW; ++h) {
-                lds_store_i32(ca[h], cv[h]);
-                lds_store_i32(qa + 256u * h, qv[h]);
-            }
-            // the moved position: its own key, spin and tenure; Q_2p is
-            // unchanged
-#pragma unroll
-            for (int h = 0; h < NW; ++h) {
-                if (word == h) {
-                    if (lane_bit(1ull << src)) {
-                        lds_store_i32(qa + 256u * h, q0[h]);
-                        lds_store_i8(za + 128u * h, 4 * nr[h]);  // 4 s_p, after the move
-                        D[h] = d_new;
-                        tabu[h] = tabu_new;
-                        nr[h] = -nr[h];
-                    }
-                }
-            }
+            const int nsp = nsp4 >> 2;
             if (__builtin_expect(above < 0, 0)) {
-                best4 += above;
+                best_d += above;
                 above = 0;
                 asp = asp0;
                 uint64_t b[4] = {0ull, 0ull, 0ull, 0ull};
@@ -788,19 +792,51 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
                 best = make_mask<NW>(b[0], b[1], b[2], b[3]);
             }
             if constexpr (TRACE) trace[t0 + slot - 1] = (int16_t)pick;  // uniform store
+            ++slot;
+
+#pragma unroll
+            for (int h = 0; h < NW; ++h)
+                move_score(cv[h], qv[h], yv[h], zv[h], nsp, nsp4, x[h], D[h], e[h]);
+            // the next key; the wait states of the wavefront minimum take the
+            // entries' new values
+            int key[NW];
+            int v = keys(slot, off - asp, key);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < NW; ++h) lds_store_i32(ca[h], e[h] - x[h]);
+            __builtin_amdgcn_sched_barrier(0);
+            v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_1032, 0xf, 0xf, true));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < NW; ++h) qv[h] = mad_i24_const<-2>(x[h], qv[h]);
+            lds_store_i32(qa, qv[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_2301, 0xf, 0xf, true));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 1; h < NW; ++h) lds_store_i32(qa + 256u * h, qv[h]);
+            __builtin_amdgcn_sched_barrier(0);
+            v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_HALF_MIRROR, 0xf, 0xf, true));
+            v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true));
+            v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, LABS_DPP_ROW_BCAST15, 0xa, 0xf, false));
+            v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, LABS_DPP_ROW_BCAST31, 0xc, 0xf, false));
+            m = readlane(v, 63);
+#pragma unroll
+            for (int h = 0; h < NW; ++h) T[h] = ballot(key[h] == m);
             wave_sync();
-        }
+        } while (slot < steps);
+        m -= 32 * 64;
 #pragma unroll
         for (int h = 0; h < NW; ++h) {
-            D[h] -= 8 * 64;
+            D[h] -= 32 * 64;
             tabu[h] -= 64;
         }
     }
 
     WalkResult<NW> res;
     res.best = best;
-    res.best_e = E0 + 4 * best4;
-    res.final_e = E0 + 4 * (best4 + above);
+    res.best_e = E0 + best_d;
+    res.final_e = E0 + best_d + above;
     return res;
 }
 

@@ -342,17 +342,17 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             const int k = i < j ? j - i : i - j;
             v += (int)SP[i] * CT[k];
         }
-        nr[h] = j < N ? (((M >> j) & 1u) ? 1 : -1) : 0;
+        nr[h] = j < N ? (((M >> j) & 1u) ? 4 : -4) : 0;
         // past the sequence: never a minimum, never admissible
-        D[h] = j < N ? pairs(2 * j) - 1 + nr[h] * (v >> 3) : 0x3fffffff;
+        D[h] = j < N ? 4 * pairs(2 * j) - 4 + nr[h] * (v >> 3) : 0x3fffffff;
         tabu[h] = j < N ? 0 : INT_MAX;
     }
     uint32_t P = ~M;  // bit i set <=> s_i = +1
     uint32_t best = P;
-    const int N1 = N - 1;
-    int e4 = 0;      // (E - E0) / 4
-    int b4 = 0;      // its minimum over the walk
-    const int thr0 = a.rule.aspiration ? -N1 : -(1 << 29);
+    const int N4 = 4 * (N - 1);
+    int ed = 0;      // E - E0
+    int bd = 0;      // its minimum over the walk
+    const int thr0 = a.rule.aspiration ? -N4 : -(1 << 29);
     int thr = thr0;  // aspiration threshold for D
     const uint32_t ct = base + (uint32_t)L::CT;
     const uint32_t qt = base + (uint32_t)(L::QT + 4 * l);
@@ -393,12 +393,13 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             const int pick = __builtin_ctz(tied);
             if (t <= sch.T) {
                 const int nsp = __builtin_amdgcn_sbfe((int)P, pick, 1) | 1;  // -s_p
+                const int nsp4 = 4 * nsp;
                 P ^= 1u << pick;
                 const uint32_t qa = qt + 4u * (uint32_t)pick;
                 const uint32_t ya = sy + 2u * (uint32_t)pick;
                 const uint32_t za = sz - (uint32_t)pick;
                 uint32_t ca[NL];
-                int cv[NL], qv[NL], q0[NL], yv[NL], zv[NL];
+                int cv[NL], qv[NL], yv[NL], zv[NL];
 #pragma unroll
                 for (int h = 0; h < NL; ++h) {
                     ca[h] = absdiff_add_v(4u * (uint32_t)pick, 4u * (uint32_t)(l + GL * h), ct);
@@ -407,33 +408,35 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
                     yv[h] = lds_load_i8(ya - (uint32_t)(GL * h));
                     zv[h] = lds_load_i8(za + (uint32_t)(2 * GL * h));
                 }
-                const int gain = N1 + m - 8 * (t - 1);  // (E' - E) / 4
-                e4 += gain;
-                thr -= gain - 8;
-                if (e4 < b4) {
-                    b4 = e4;
+                const int gain = N4 + m - 32 * (t - 1);  // E' - E
+                ed += gain;
+                thr -= gain - 32;
+                if (ed < bd) {
+                    bd = ed;
                     best = P;
-                    thr = thr0 + 8 * t;
+                    thr = thr0 + 32 * t;
                 }
                 if constexpr (TRACE) {
                     if (l == 0) a.trace[w * (int64_t)a.trace_stride + t - 1] = (int16_t)pick;
                 }
 #pragma unroll
                 for (int h = 0; h < NL; ++h) {
-                    q0[h] = qv[h];
-                    move_term<false>(cv[h], qv[h], yv[h], zv[h], nr[h], nsp, D[h]);
-                    lds_store_i32(ca[h], cv[h]);
-                    lds_store_i32(qa + 4u * GL * h, qv[h]);
+                    const int x = mul_i24(nr[h], nsp);
+                    const int e = mad_i24(yv[h], nsp, cv[h]);
+                    D[h] = mad_i24(x, cv[h] + e + qv[h], D[h]);
+                    D[h] = mad_i24(zv[h], nsp4, D[h]);
+                    lds_store_i32(ca[h], e - x);
+                    lds_store_i32(qa + 4u * GL * h, mad_i24_const<-2>(x, qv[h]));
                 }
                 // the moved position: its own key, spin and tenure; Q_2p is
                 // unchanged
 #pragma unroll
                 for (int h = 0; h < NL; ++h) {
                     if (l + GL * h == pick) {
-                        D[h] = 8 * t - gain - N1;  // -d_p - 2 (N - 1), + 8 t
+                        D[h] = 32 * t - gain - N4;  // 4 (-d_p - 2 (N - 1)), + 32 t
                         tabu[h] = tabu_new;
-                        lds_store_i32(qa + 4u * GL * h, q0[h]);
-                        lds_store_i8(za + (uint32_t)(2 * GL * h), 4 * nr[h]);  // 4 s_p, after the move
+                        lds_store_i32(qa + 4u * GL * h, qv[h]);
+                        lds_store_i8(za + (uint32_t)(2 * GL * h), nr[h]);  // 4 s_p, after the move
                         nr[h] = -nr[h];
                     }
                 }
@@ -446,8 +449,8 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
         for (int i = l; i < a.out_stride; i += GL)
             out[i] = i < N ? (((best >> i) & 1u) ? (int8_t)1 : (int8_t)-1) : (int8_t)0;
         if (l == 0) {
-            a.best_e[w] = E0 + 4 * b4;
-            a.final_e[w] = E0 + 4 * e4;
+            a.best_e[w] = E0 + bd;
+            a.final_e[w] = E0 + ed;
         }
     }
 }
