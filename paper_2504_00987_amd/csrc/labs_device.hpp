@@ -19,6 +19,8 @@
 #include <stdint.h>
 #include <limits.h>
 
+#include <type_traits>
+
 #include "labs_internal.h"
 
 namespace liblabs {
@@ -358,14 +360,16 @@ struct WalkResult {
 // int8 with zeros around it, SP[q] = 4 s_q for 0 <= q < N and 0 for the other
 // q in -SPAN .. 2 SPAN - 1, which covers every 2j - p and 2p - j of two
 // positions j, p < SPAN.  (With these factors one number, -s_p, scales every
-// term of a move.)  15 SPAN bytes: occupancy is never bound by LDS.
+// term of a move.)  15 SPAN bytes: occupancy is never bound by LDS.  (Spins
+// as whole words, with fewer loads for several neighbours per lane, cost 3
+// to 8 % on full devices: the stride-two reads of 2j - p meet in the banks.)
 template <int SPAN>
 struct WalkTables {
     static constexpr int CT = 0;
     static constexpr int QT = CT + 4 * SPAN;
     static constexpr int SPLO = QT + 8 * SPAN, SP = SPLO + SPAN;
     static constexpr int BYTES = SP + 2 * SPAN;
-    static_assert(BYTES % 16 == 0 && SP % 16 == 0, "16-byte aligned walks and spins");
+    static_assert(BYTES % 16 == 0, "16-byte aligned walks");
 };
 template <int NW>
 using WalkLds = WalkTables<64 * NW>;
@@ -444,23 +448,24 @@ __device__ __forceinline__ void move_score(int c, int q, int y, int z, int nsp, 
     D = mad_i24_s(z, nsp4, D);
 }
 
-// The moved position, the one lane of `bit`: -4 s_p (nr) stored as its new
-// spin at LDS offset za and negated, x = 0, and D and tabu set to wave-uniform
-// values.  (A masked block without a branch, so that the step stays one run
-// of instructions.)
+// The moved position, the lane of `bit` (none if 0): -4 s_p (nr) stored as its
+// new spin at LDS offset za + OFF and negated, x = 0, and D and tabu set to
+// wave-uniform values.  (A masked block without a branch, so that the step
+// stays one run of instructions.)
+template <int OFF>
 __device__ __forceinline__ void set_moved(uint64_t bit, uint32_t za, int d_new, int tabu_new,
                                           int &nr, int &x, int &D, int &tabu) {
     uint64_t all;
     asm volatile(
         "s_and_saveexec_b64 %0, %5\n\t"
-        "ds_write_b8 %6, %1\n\t"
+        "ds_write_b8 %6, %1 offset:%9\n\t"
         "v_mov_b32 %2, 0\n\t"
         "v_mov_b32 %3, %7\n\t"
         "v_mov_b32 %4, %8\n\t"
         "v_sub_u32 %1, 0, %1\n\t"
         "s_mov_b64 exec, %0"
         : "=&s"(all), "+v"(nr), "+v"(x), "+v"(D), "+v"(tabu)
-        : "s"(bit), "v"(za), "s"(d_new), "s"(tabu_new)
+        : "s"(bit), "v"(za), "s"(d_new), "s"(tabu_new), "n"(OFF)
         : "memory", "scc");
 }
 
@@ -582,11 +587,8 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             QT[N - 1 + j] = 2 * (N - j - 2 * (ph - tm));
         }
         SP[j] = (int8_t)-nr[h];
-    }
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {  // zeros around the sequence, 64 bytes at a time
-        const int at = lane < 16 ? -64 * NW + 64 * i + 4 * lane : 64 * NW + 64 * i + 4 * (lane - 16);
-        if (lane < 32) *(int32_t *)(SP + at) = 0;
+        SP[j - 64 * NW] = 0;
+        SP[j + 64 * NW] = 0;
     }
 
     // v_j = sum_i s_i C_|i-j|: C mirrored around zero as bytes (C_k >> 1 for
@@ -594,13 +596,15 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     // window starts at any byte, so four dwords at a time are aligned.
     constexpr bool kHalfC = NW > 2;
     int8_t *const F = (int8_t *)CT;  // F[64 NW + k] = F[64 NW - k] = C_k, 0 at k = 0
-    static_assert(128 * NW + 16 <= L::QT - L::CT, "the mirrored bytes fit");
+    int8_t *const S8 = F + 128 * NW + 16;  // s_i as bytes, 0 past the sequence
+    static_assert(128 * NW + 16 + 64 * NW <= L::QT - L::CT, "both fit");
 #pragma unroll
     for (int h = 0; h < NW; ++h) {
         const int k = lane + 64 * h;
         const int8_t c = (int8_t)(kHalfC ? C[h] >> 1 : C[h]);
         F[64 * NW + k] = c;
         F[64 * NW - k] = c;
+        S8[k] = (int8_t)(-nr[h] >> 2);
     }
     wave_sync();
     int D[NW], tabu[NW];
@@ -615,7 +619,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             v[h] = 0;
         }
         const uint32_t shift = (uint32_t)(-lane) & 3u;
-        const uint4 *const S16 = (const uint4 *)SP;
+        const uint4 *const S16 = (const uint4 *)S8;
         for (int i = 0; i < N; i += 16) {
             const uint4 s = S16[i >> 4];
 #pragma unroll
@@ -647,7 +651,6 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
 #pragma unroll
         for (int h = 0; h < NW; ++h) {
             const int j = lane + 64 * h;
-            v[h] >>= 2;  // the spins of SP are scaled by 4
             if constexpr (kHalfC) v[h] = 2 * v[h] + Sq + ((N & 1) ? nr[h] >> 2 : 0);
             // 4 (Q_2j - 1 - s_j v_j); beyond the sequence never a minimum
             D[h] = j < N ? 2 * QT[2 * j] - 4 + nr[h] * v[h] : 0x3fffffff;
@@ -668,14 +671,14 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
     int best_d = 0, above = 0;
     const int asp0 = aspiration ? 0 : 1 << 29;
     int asp = asp0;
-    uint32_t ct[NW], qt, sy, sz;  // LDS addresses less their part in p
-    const uint32_t base = lds_offset(lds);
+    // LDS addresses less their part in p
+    const uint32_t base = lds_offset(lds), ct_base = base + (uint32_t)L::CT;
+    uint32_t ct[NW];
 #pragma unroll
     for (int h = 0; h < NW; ++h) ct[h] = (uint32_t)(4 * (lane + 64 * h));
-    qt = base + (uint32_t)(L::QT + 4 * lane);  // + 4p: Q_(p + lane)
-    sy = base + (uint32_t)(L::SP - lane);      // + 2p: SP[2p - lane]
-    sz = base + (uint32_t)(L::SP + 2 * lane);  // - p: SP[2 lane - p]
-    const uint32_t ct_base = base + (uint32_t)L::CT;
+    const uint32_t qt = base + (uint32_t)(L::QT + 4 * lane);  // + 4p: Q_(p + lane)
+    const uint32_t sy = base + (uint32_t)(L::SP - lane - 64 * (NW - 1));  // + 2p: last word's SP[2p - j]
+    const uint32_t sz = base + (uint32_t)(L::SP + 2 * lane);  // - p: SP[2 lane - p]
 
     // The least admissible key and the lanes that hold it, for the coming step.
     int m;
@@ -712,9 +715,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
         int off = -4 * (N - 1);  // 32 (moves made in the block) - 4 (N - 1)
         int slot = 0;
         do {
-            // the chosen move: lane src of word `word` (the first word with a
-            // minimum); of several tied moves the r-th (ascending),
-            // r = (u0 * count) >> 32
+            // of several tied moves keep the r-th (ascending), r = (u0 * count) >> 32
             int c[NW], count = 0;
 #pragma unroll
             for (int h = 0; h < NW; ++h) {
@@ -722,76 +723,92 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
                 asm("" : "+s"(c[h]));  // 32-bit scalar arithmetic
                 count += c[h];
             }
-            uint64_t tied = T[NW - 1];
-            int word = NW - 1;
-#pragma unroll
-            for (int h = NW - 2; h >= 0; --h) {
-                tied = c[h] ? T[h] : tied;
-                word = c[h] ? h : word;
-            }
             if (__builtin_expect(count > 1, 0)) {
                 int r = (int)below(readlane_u(dr0, slot), (uint32_t)count);
-                tied = T[0];
-                word = 0;
+                bool found = false;
 #pragma unroll
-                for (int h = 0; h + 1 < NW; ++h)
-                    if (word == h && r >= c[h]) {
-                        r -= c[h];
-                        tied = T[h + 1];
-                        word = h + 1;
+                for (int h = 0; h < NW; ++h) {
+                    const bool here = !found && (h == NW - 1 || r < c[h]);
+                    if (here) {
+                        uint64_t t = T[h];
+                        for (; r > 0; --r) t &= t - 1ull;  // drop the r lowest
+                        T[h] = t & (0ull - t);
+                    } else {
+                        r -= found ? 0 : c[h];
+                        T[h] = 0ull;
                     }
-                for (; r > 0; --r) tied &= tied - 1ull;  // drop the r lowest
+                    found |= here;
+                }
             }
-            const int src = __builtin_ctzll(tied);  // lane of the move
-            const int pick = NW == 1 ? src : 64 * word + src;
-
-            // entries of the move (all reads before any write)
-            const uint32_t qa = qt + 4u * (uint32_t)pick;
-            const uint32_t ya = sy + 2u * (uint32_t)pick;
-            const uint32_t za = sz - (uint32_t)pick;
-            uint32_t ca[NW];
-            int cv[NW], qv[NW], yv[NW], zv[NW], e[NW], x[NW];
-#pragma unroll
-            for (int h = 0; h < NW; ++h) {
-                ca[h] = absdiff_add_s(4u * (uint32_t)pick, ct[h], ct_base);
-                cv[h] = lds_load_i32(ca[h]);
-                qv[h] = lds_load_i32(qa + 256u * h);
-                yv[h] = lds_load_i8(ya - 64u * h);
-                zv[h] = lds_load_i8(za + 128u * h);
-                asm("" : "+v"(yv[h]), "+v"(zv[h]));  // one sign-extending load each
-            }
-
-            // While they are on their way: energies, the best, and all of the
-            // moved position: its new spin, tenure and key 4 (-d_p - 2 (N -
-            // 1)); with x = 0 its entry Q_2p stays, and the update below
-            // changes its D by z nsp4 = -16.
             const int gain = m - off;  // E' - E = 4 (N - 1 + d_p)
             off += 32;
             above += gain;
             asp += gain;
-            const int tabu_new = readlane(expire, slot);  // slot + tenure
-            const int d_new = off - gain + 16;
-            const uint64_t bit = 1ull << src;
-            int nsp4 = 0;
-#pragma unroll
-            for (int h = 0; h < NW; ++h)
-                if (NW == 1 || word == h) {
-                    nsp4 = readlane(nr[h], src);
-#pragma unroll
-                    for (int g = 0; g < NW; ++g) x[g] = mul_i24_s(nr[g], nsp4 >> 2);
-                    set_moved(bit, za + 128u * h, d_new, tabu_new, nr[h], x[h], D[h], tabu[h]);
-                }
-            const int nsp = nsp4 >> 2;
             if (__builtin_expect(above < 0, 0)) {
                 best_d += above;
                 above = 0;
                 asp = asp0;
                 uint64_t b[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
-                for (int h = 0; h < NW; ++h) b[h] = ballot(nr[h] > 0);
+                for (int h = 0; h < NW; ++h) b[h] = ballot(nr[h] > 0) ^ T[h];
                 best = make_mask<NW>(b[0], b[1], b[2], b[3]);
             }
-            if constexpr (TRACE) trace[t0 + slot - 1] = (int16_t)pick;  // uniform store
+
+            // All of the moved position p (the lane of T's one bit): its new
+            // spin, its tenure and its key 4 (-d_p - 2 (N - 1)).  With x = 0
+            // its entry Q_2p stays, and the update below changes its D by
+            // z nsp4: -16 with the old spin (one neighbour per lane: set
+            // while the entries are on their way), +16 with the new one
+            // (several: branches, ahead of the reads).
+            int x[NW], nsp4, nsp, p, tabu_new;  // tabu_new: slot + tenure
+            uint32_t za;
+            if constexpr (NW > 1) tabu_new = readlane(expire, slot);
+            auto at = [&](auto H) {
+                p = 64 * decltype(H)::value + __builtin_ctzll(T[decltype(H)::value]);
+                za = sz - (uint32_t)p;
+            };
+            auto moved = [&](auto H) {
+                constexpr int h = decltype(H)::value;
+                if constexpr (NW == 1) tabu_new = readlane(expire, slot);
+                const int d_new = off - gain + (NW == 1 ? 16 : -16);
+                nsp4 = readlane(nr[h], p - 64 * h);
+                nsp = nsp4 >> 2;
+#pragma unroll
+                for (int g = 0; g < NW; ++g) x[g] = mul_i24_s(nr[g], nsp);
+                set_moved<128 * h>(T[h], za, d_new, tabu_new, nr[h], x[h], D[h], tabu[h]);
+            };
+            auto both = [&](auto H) {
+                at(H);
+                moved(H);
+            };
+            using std::integral_constant;
+            if constexpr (NW == 1)
+                at(integral_constant<int, 0>());
+            else if (T[0] != 0ull)
+                both(integral_constant<int, 0>());
+            else if (NW == 2 || T[1] != 0ull)
+                both(integral_constant<int, 1>());
+            else if (NW == 3 || T[NW > 2 ? 2 : 0] != 0ull)
+                both(integral_constant<int, NW == 2 ? 0 : 2>());
+            else
+                both(integral_constant<int, NW - 1>());
+
+            // entries of the move (all reads before any write)
+            const uint32_t qa = qt + 4u * (uint32_t)p;
+            uint32_t ya = sy + 2u * (uint32_t)p;
+            asm("" : "+v"(ya));  // one address, the words by offset
+            uint32_t ca[NW];
+            int cv[NW], qv[NW], yv[NW], zv[NW], e[NW];
+#pragma unroll
+            for (int h = 0; h < NW; ++h) {
+                ca[h] = absdiff_add_s(4u * (uint32_t)p, ct[h], ct_base);
+                cv[h] = lds_load_i32(ca[h]);
+                qv[h] = lds_load_i32(qa + 256u * h);
+                yv[h] = lds_load_i8(ya + 64u * (NW - 1 - h));
+                zv[h] = lds_load_i8(za + 128u * h);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // every load is out
+            if constexpr (NW == 1) moved(integral_constant<int, 0>());
             ++slot;
 
 #pragma unroll
@@ -823,6 +840,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             m = readlane(v, 63);
 #pragma unroll
             for (int h = 0; h < NW; ++h) T[h] = ballot(key[h] == m);
+            if constexpr (TRACE) trace[t0 + slot - 2] = (int16_t)p;  // uniform store
             wave_sync();
         } while (slot < steps);
         m -= 32 * 64;

@@ -340,7 +340,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
         int v = 0;  // 8 v_j
         for (int i = 0; i < SPAN; ++i) {
             const int k = i < j ? j - i : i - j;
-            v += (int)SP[i] * CT[k];
+            v += __mul24(SP[i], CT[k]);
         }
         nr[h] = j < N ? (((M >> j) & 1u) ? 4 : -4) : 0;
         // past the sequence: never a minimum, never admissible
@@ -356,8 +356,11 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
     int thr = thr0;  // aspiration threshold for D
     const uint32_t ct = base + (uint32_t)L::CT;
     const uint32_t qt = base + (uint32_t)(L::QT + 4 * l);
-    const uint32_t sy = base + (uint32_t)(L::SP - l);
+    const uint32_t sy = base + (uint32_t)(L::SP - (l + GL * (NL - 1)));
     const uint32_t sz = base + (uint32_t)(L::SP + 2 * l);
+    // the half and the dword of a ballot that hold this lane's group
+    const bool upper = g * GL >= 32;
+    const uint32_t half_sel = (g & 1) && GL == 16 ? 0x07060302u : 0x05040100u;
     const int T_all = -wave_min(-sch.T);  // the longest walk of the wavefront
 
     for (int t0 = 1; t0 <= T_all; t0 += GL) {
@@ -384,10 +387,21 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             const int m = group_min<GL>(kmin);
             // ties: the r-th lowest tied neighbour of the group, r from the
             // step's first draw
-            uint32_t tied = 0u;
+            uint32_t tied;
+            {
+                uint32_t w[2] = {0u, 0u};
 #pragma unroll
-            for (int h = 0; h < NL; ++h)
-                tied |= group_bits<GL>(ballot(key[h] == m), g) << (GL * h);
+                for (int h = 0; h < NL; ++h) {
+                    const uint64_t b = ballot(key[h] == m);
+                    w[h] = upper ? (uint32_t)(b >> 32) : (uint32_t)b;
+                }
+                if constexpr (GL == 32)
+                    tied = w[0];
+                else if constexpr (NL == 2)
+                    tied = __builtin_amdgcn_perm(w[1], w[0], half_sel);
+                else
+                    tied = (w[0] >> (16 * (g & 1))) & 0xffffu;
+            }
             const int r = (int)below(dr, (uint32_t)__popc(tied));
             for (int i = 0; i < r; ++i) tied &= tied - 1u;  // drop the r lowest
             const int pick = __builtin_ctz(tied);
@@ -395,9 +409,26 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
                 const int nsp = __builtin_amdgcn_sbfe((int)P, pick, 1) | 1;  // -s_p
                 const int nsp4 = 4 * nsp;
                 P ^= 1u << pick;
-                const uint32_t qa = qt + 4u * (uint32_t)pick;
-                const uint32_t ya = sy + 2u * (uint32_t)pick;
                 const uint32_t za = sz - (uint32_t)pick;
+                const int gain = N4 + m - 32 * (t - 1);  // E' - E
+                // the moved position (as in tabu_walk): x = 0 keeps Q_2p, and
+                // the update changes its D by +16 (its z is the new spin)
+                const int d_new = 32 * t - gain - N4 - 16;  // 4 (-d_p - 2 (N - 1)) + 32 t
+                int x[NL];
+#pragma unroll
+                for (int h = 0; h < NL; ++h) {
+                    x[h] = mul_i24(nr[h], nsp);
+                    if (l + GL * h == pick) {
+                        lds_store_i8(za + 2u * GL * h, nsp4);  // 4 s_p, after the move
+                        x[h] = 0;
+                        D[h] = d_new;
+                        tabu[h] = tabu_new;
+                        nr[h] = -nr[h];
+                    }
+                }
+                const uint32_t qa = qt + 4u * (uint32_t)pick;
+                uint32_t ya = sy + 2u * (uint32_t)pick;
+                asm("" : "+v"(ya));  // one address, the words by offset
                 uint32_t ca[NL];
                 int cv[NL], qv[NL], yv[NL], zv[NL];
 #pragma unroll
@@ -405,40 +436,25 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
                     ca[h] = absdiff_add_v(4u * (uint32_t)pick, 4u * (uint32_t)(l + GL * h), ct);
                     cv[h] = lds_load_i32(ca[h]);
                     qv[h] = lds_load_i32(qa + 4u * GL * h);
-                    yv[h] = lds_load_i8(ya - (uint32_t)(GL * h));
-                    zv[h] = lds_load_i8(za + (uint32_t)(2 * GL * h));
+                    yv[h] = lds_load_i8(ya + (uint32_t)(GL * (NL - 1 - h)));
+                    zv[h] = lds_load_i8(za + 2u * GL * h);
                 }
-                const int gain = N4 + m - 32 * (t - 1);  // E' - E
                 ed += gain;
                 thr -= gain - 32;
-                if (ed < bd) {
-                    bd = ed;
-                    best = P;
-                    thr = thr0 + 32 * t;
-                }
+                const bool improved = ed < bd;
+                bd = min(bd, ed);
+                best = improved ? P : best;
+                thr = improved ? thr0 + 32 * t : thr;
                 if constexpr (TRACE) {
                     if (l == 0) a.trace[w * (int64_t)a.trace_stride + t - 1] = (int16_t)pick;
                 }
 #pragma unroll
                 for (int h = 0; h < NL; ++h) {
-                    const int x = mul_i24(nr[h], nsp);
                     const int e = mad_i24(yv[h], nsp, cv[h]);
-                    D[h] = mad_i24(x, cv[h] + e + qv[h], D[h]);
+                    D[h] = mad_i24(x[h], cv[h] + e + qv[h], D[h]);
                     D[h] = mad_i24(zv[h], nsp4, D[h]);
-                    lds_store_i32(ca[h], e - x);
-                    lds_store_i32(qa + 4u * GL * h, mad_i24_const<-2>(x, qv[h]));
-                }
-                // the moved position: its own key, spin and tenure; Q_2p is
-                // unchanged
-#pragma unroll
-                for (int h = 0; h < NL; ++h) {
-                    if (l + GL * h == pick) {
-                        D[h] = 32 * t - gain - N4;  // 4 (-d_p - 2 (N - 1)), + 32 t
-                        tabu[h] = tabu_new;
-                        lds_store_i32(qa + 4u * GL * h, qv[h]);
-                        lds_store_i8(za + (uint32_t)(2 * GL * h), nr[h]);  // 4 s_p, after the move
-                        nr[h] = -nr[h];
-                    }
+                    lds_store_i32(ca[h], e - x[h]);
+                    lds_store_i32(qa + 4u * GL * h, mad_i24_const<-2>(x[h], qv[h]));
                 }
             }
             wave_sync();
