@@ -97,15 +97,14 @@ typedef struct labs_tabu_params {
 
 #define LABS_MAX_STEPS (1 << 20)
 
-/* Launch configuration of the batched walk kernels.  Lanes per walk =
- * group_lanes / walks_per_group: 64 (one wavefront per walk: {64, 1},
- * {128, 2}, {256, 4}), or 32 / 16 ({64, 2} and {128, 4}: the walks of
- * N <= 32 run two per wavefront, 32 lanes each; {64, 4}: those of N <= 16
- * four per wavefront and those of 16 < N <= 32 two; the batch's longer
- * walks run one per wavefront, one or two per workgroup).  {128, 1} is
- * accepted and runs as {128, 2}: a walk's step is short enough that no
- * length gains from a second wavefront.  {256, 1} and {256, 2} are rejected
- * (LABS_E_INVAL). */
+/* Launch configuration of the batched walk kernels.  group_lanes /
+ * walks_per_group: 64 (one walk per wavefront: {64, 1}, {128, 2}, {256, 4});
+ * 32 ({64, 2}, {128, 4}): the walks of N <= 32 run several per wavefront
+ * (four, 16 lanes and two neighbours per lane each); 16 ({64, 4}): the same,
+ * those of N <= 16 with one neighbour per lane.  A batch's longer walks run
+ * one per wavefront.  {128, 1} is accepted and runs as {128, 2}: a walk's
+ * step is short enough that no length gains from a second wavefront.
+ * {256, 1} and {256, 2} are rejected (LABS_E_INVAL). */
 typedef struct labs_launch {
     int32_t group_lanes;     /* 64, 128 or 256 lanes per workgroup */
     int32_t walks_per_group; /* 1, 2 or 4 */
@@ -115,9 +114,11 @@ typedef struct labs_launch {
     int32_t groups_per_cu;   /* persistent grid = groups_per_cu x CUs (0: auto) */
     int32_t layout;          /* 0, 1 or 2: accepted, without effect (walks of
                                 every length keep the same tables) */
-} labs_launch;               /* default (untuned): {64, 2, 0, 0, 0} when
-                                every walk has N <= 32, {64, 1, 0, 0, 0} up to
-                                N = 128, {256, 4, 0, 0, 0} above */
+} labs_launch;               /* default (untuned), with every walk N <= 16:
+                                {64, 4, 0, 0, 0} above 2048 walks; N <= 32:
+                                {64, 2, 0, 0, 0} above 4096 walks; else
+                                {64, 1, 0, 0, 0} up to N = 128 and
+                                {256, 4, 0, 0, 0} beyond */
 
 typedef struct labs_handle labs_handle;
 
@@ -268,14 +269,15 @@ int labs_tabu_batch_noalloc(labs_handle *h, const labs_tabu_params *p,
 int labs_set_launch(labs_handle *h, const labs_launch *launch);
 
 /* The launch configuration labs_tabu_batch would use for a batch whose
- * lengths span [n_min, n_max]. */
+ * lengths span [n_min, n_max] (where the default depends on their number: for
+ * a large batch). */
 int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *out);
 
 /*
  * Autotuner: times the launch configurations that apply to the length range
  * [n_min, n_max] -- {64, 1}, {128, 2}, {256, 4} (one wavefront per walk);
- * when n_min <= 32, {64, 2} and {128, 4} (two walks per wavefront), and
- * when n_min <= 16 also {64, 4} (four) -- each as a grid of one walk per
+ * when n_min <= 32, {64, 2} and {128, 4}, and when n_min <= 16 also {64, 4}
+ * (several walks per wavefront) -- each as a grid of one walk per
  * wavefront and as a persistent queue at 4 to 64 wavefronts per CU -- on
  * `walks` random-start walks with lengths spread evenly over [n_min, n_max]
  * and parameters `p` (each: one warm-up call, then four calls back to back).

@@ -200,21 +200,25 @@ RuleParams to_rule(const labs_tabu_params &p) {
 
 int bucket_of(int n) { return std::min(LABS_MAX_N / 16 - 1, std::max(0, (n - 1) / 16)); }
 
-// Batches whose walks all have N <= 32 run two walks per wavefront, the
-// others one; one walk per 64-lane workgroup up to N = 128, four walks per
-// 256-lane workgroup above.
-labs_launch default_launch(int n_max) {
+// One walk per wavefront and 64-lane workgroup up to N = 128, four walks per
+// 256-lane workgroup above; batches whose walks all have N <= 32 run four per
+// wavefront once they are large enough to keep the device busy that way.  Time
+// of a step (MI355X), one walk per wavefront against four: N = 32 210 and 300
+// ns at 1024 walks, 298 and 316 at 4096, 480 and 364 at 8192; N = 16 230 and
+// 241 ns at 2048 walks, 309 and 238 at 4096.
+labs_launch default_launch(int n_max, int64_t walks) {
+    const bool group = n_max <= 16 ? walks > 2048 : n_max <= 32 && walks > 4096;
     labs_launch l;
     l.group_lanes = n_max <= 128 ? 64 : 256;
-    l.walks_per_group = n_max <= 32 ? 2 : n_max <= 128 ? 1 : 4;
+    l.walks_per_group = group ? (n_max <= 16 ? 4 : 2) : n_max <= 128 ? 1 : 4;
     l.persistent = 0;
     l.groups_per_cu = 0;
     l.layout = 0;
     return l;
 }
 
-// Lanes per walk 16 or 32 (several walks of N <= 32 per wavefront; longer
-// walks of the batch take one wavefront each) or 64 (one wavefront);
+// group_lanes / walks_per_group 16 or 32 (several walks of N <= 32 per
+// wavefront; longer walks of the batch take one wavefront each) or 64 (one);
 // {128, 1} runs as {128, 2}.
 const char *launch_problem(const labs_launch &l) {
     const int g = l.group_lanes, w = l.walks_per_group;
@@ -441,7 +445,7 @@ static int bruteforce_impl(labs_handle *h, int32_t n, bool skew, int32_t *min_e,
         a.rule.hi_den = 5;
         a.rule.aspiration = 1;
         a.rule.slo_den = a.rule.shi_den = 1;
-        const WalkLaunch l = walk_launch(h, default_launch(n));
+        const WalkLaunch l = walk_launch(h, default_launch(n, kWalks));
         e = launch_tabu(a, l, &s);
         if (e == hipSuccess)
             e = launch_search(n, p, a.best_e, kWalks, (uint32_t *)(base + off_w + off_q),
@@ -519,7 +523,7 @@ int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *o
     h->last_error.clear();
     if (n_min < LABS_MIN_N || n_max > LABS_MAX_N || n_min > n_max)
         return fail(h, LABS_E_INVAL, "bad length range [%d, %d]", n_min, n_max);
-    *out = liblabs::choose_launch(h, n_min, n_max);
+    *out = liblabs::choose_launch(h, n_min, n_max, INT64_MAX);
     return LABS_OK;
 }
 
@@ -527,11 +531,11 @@ int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *o
 
 namespace liblabs {
 
-labs_launch choose_launch(labs_handle *h, int n_min, int n_max) {
+labs_launch choose_launch(labs_handle *h, int n_min, int n_max, int64_t walks) {
     if (h->has_override) return h->override_launch;
     const auto it = h->tuned.find({bucket_of(n_min), bucket_of(n_max)});
     if (it != h->tuned.end()) return it->second;
-    return default_launch(n_max);
+    return default_launch(n_max, walks);
 }
 
 // Shared body of labs_tabu_batch (also used by the autotuner).
@@ -585,7 +589,7 @@ int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *sta
     if (trace && trace_stride < tmax)
         return fail(h, LABS_E_INVAL, "trace_stride=%d < longest walk %lld", trace_stride, tmax);
 
-    const labs_launch L = force ? *force : choose_launch(h, n_min, n_max);
+    const labs_launch L = force ? *force : choose_launch(h, n_min, n_max, W);
     if (const char *why = launch_problem(L)) return fail(h, LABS_E_INVAL, "%s", why);
     const WalkLaunch WL = walk_launch(h, L);
 
@@ -748,7 +752,7 @@ extern "C" int labs_autotune(labs_handle *h, const labs_tabu_params *p, int32_t 
     constexpr int kReps = 4;
     constexpr float kMargin = 0.98f;
     const bool uneven = n_min != n_max;
-    std::vector<labs_launch> cands{default_launch(n_max)};
+    std::vector<labs_launch> cands{default_launch(n_max, walks)};
     // persistent grids in wavefronts per CU (up to the 32 that fit)
     constexpr int kWavesPerCu[] = {4, 8, 12, 16, 20, 24, 28, 32, 48, 64};
     auto add = [&](int lanes, int walks) {

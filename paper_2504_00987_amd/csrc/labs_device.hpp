@@ -464,7 +464,7 @@ __device__ __forceinline__ void set_moved(uint64_t bit, uint32_t za, int d_new, 
         "v_mov_b32 %4, %8\n\t"
         "v_sub_u32 %1, 0, %1\n\t"
         "s_mov_b64 exec, %0"
-        : "=&s"(all), "+v"(nr), "+v"(x), "+v"(D), "+v"(tabu)
+        : "=&s"(all), "+&v"(nr), "+&v"(x), "+&v"(D), "+&v"(tabu)
         : "s"(bit), "v"(za), "s"(d_new), "s"(tabu_new), "n"(OFF)
         : "memory", "scc");
 }

@@ -104,7 +104,7 @@ int stage_release(labs_handle *h, hipStream_t s);
 int check_rule(labs_handle *h, const RuleParams &r, int n);
 long long max_steps(const RuleParams &r, int n);
 RuleParams to_rule(const labs_tabu_params &p);
-labs_launch choose_launch(labs_handle *h, int n_min, int n_max);
+labs_launch choose_launch(labs_handle *h, int n_min, int n_max, int64_t walks);
 // The kernels' view of a launch configuration.
 WalkLaunch walk_launch(const labs_handle *h, const labs_launch &l);
 int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *starts,

@@ -57,8 +57,8 @@ constexpr int kSideStreams = kWalkClasses - 1;
 enum WalkKind : int {
     kKindWave = 0,    // one walk per wavefront
     kKindSplit = 1,   // walks of 64 < N <= 128 apart from the shorter ones
-    kKindGroup2 = 2,  // two walks of N <= 32 per wavefront (32 lanes each)
-    kKindGroup4 = 4,  // four walks of N <= 16 per wavefront (16 lanes each)
+    kKindGroup2 = 2,  // walks of N <= 32, four per wavefront (16 lanes, two neighbours each)
+    kKindGroup4 = 4,  // walks of N <= 16, four per wavefront (16 lanes, one neighbour each)
 };
 
 // Launch groups of a batch: runs of consecutive length classes (hence of
@@ -67,8 +67,7 @@ enum WalkKind : int {
 // `split`, classes 2..3 (64 < N <= 128) and the shorter classes one each.
 // With several walks per wavefront (`lanes` = 32 or 16 lanes per walk) the
 // walks of N <= 32 leave the one-walk-per-wavefront group: with 32 lanes both
-// short classes form one group of two walks per wavefront; with 16, N <= 16
-// runs four per wavefront and 16 < N <= 32 two.
+// short classes form one group; with 16, N <= 16 and 16 < N <= 32 one each.
 struct WalkGroups {
     int n;
     int first[kWalkClasses], last[kWalkClasses], kind[kWalkClasses];
@@ -133,7 +132,7 @@ inline WalkGroups tabu_launch_groups(const int64_t *class_end, int lanes) {
 // How labs_tabu_batch launches its walks.
 struct WalkLaunch {
     int waves_per_group;  // wavefronts per workgroup
-    int lanes;            // lanes per walk of N <= 32: 64 (one walk per wavefront), 32 or 16
+    int lanes;            // walks of N <= 32: 64 (one per wavefront), 32 or 16 (walk_launch_groups)
     int groups;           // persistent grid (0: none)
 };
 

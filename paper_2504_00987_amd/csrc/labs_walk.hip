@@ -4,7 +4,7 @@
 //   tabu_kernel     independent tabu walks (Alg. 2 / Alg. 4), one walk per
 //                   wave, either one wave per walk or a persistent grid
 //                   draining a longest-first work queue
-//   tabu_kernel_group  two or four walks of N <= 32 per wave
+//   tabu_kernel_group  four walks of N <= 32 per wave
 //   fill_u32_kernel device-side fill (queue heads, flags), capturable
 //   order_by_length_kernel  longest-first processing order built on the
 //                   device (the allocation-free entry point's lengths)
@@ -199,59 +199,32 @@ __device__ void run_tabu_item(const TabuLaunchArgs &a, int64_t w, int N, uint8_t
 // ---------------------------------------------------------------------------
 // Several walks per wavefront (N <= 32).
 // ---------------------------------------------------------------------------
-// A wavefront runs G = 64 / GL walks of N <= GL NL at once, lane l of a group
-// of GL owning neighbours j = l + GL h, h < NL.  The step is tabu_walk's, with
-// every per-walk quantity (the sequence mask, the energy, the best, the
-// chosen move, the schedule) held per lane for the lane's own walk instead of
-// in scalar registers, and the minimum taken within each group of lanes.
-// Walks of different lengths share the step loop; a walk past its last step,
-// or a group past the end of the range, takes no move.
+// A wavefront runs four walks of N <= 16 NL (NL = 1 or 2) at once, lane l of
+// a group of 16 owning neighbours j = l + 16h, h < NL.  The step is
+// tabu_walk's, with every per-walk quantity (the sequence mask, the energy,
+// the best, the chosen move, the schedule) held per lane for the lane's own
+// walk instead of in scalar registers, and the minimum taken within each
+// group of lanes.  Walks of different lengths share the step loop; a walk past
+// its last step takes no move.  Bound: VALU on a full device (72 instructions
+// a step of four walks); 16 lanes with two neighbours each share the per-walk
+// work over half the lanes of 32 with one: 16384 walks of N = 32 and 128 steps
+// 104 -> 80 us a call.
+constexpr int kGroupLanes = 16;
 
-// The two 16-lane rows of each 32-lane half, every lane receiving both:
-// v_permlane16_swap with the value as both operands swaps the odd rows of
-// one copy with the even rows of the other, so one copy holds rows 0, 0,
-// 2, 2 and the other 1, 1, 3, 3 (a register exchange, no LDS trip).
-__device__ __forceinline__ void row_pair(int v, int &a, int &b) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-    a = (int)r[0];
-    b = (int)r[1];
-}
-
-// Minimum and sum over each group of GL = 16 or 32 consecutive lanes, every
-// lane receiving its group's value: row (16-lane) reductions by DPP, then,
-// for GL = 32, the two rows of a group combined.
-template <int GL>
+// Minimum and sum over each row of 16 lanes by DPP, every lane receiving its
+// row's value.
 __device__ __forceinline__ int group_min(int v) {
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_1032, 0xf, 0xf, true));
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_2301, 0xf, 0xf, true));
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_HALF_MIRROR, 0xf, 0xf, true));
-    v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true));
-    if constexpr (GL == 32) {
-        int a, b;
-        row_pair(v, a, b);
-        v = min(a, b);
-    }
-    return v;
+    return min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true));
 }
 
-template <int GL>
 __device__ __forceinline__ int group_sum(int v) {
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_1032, 0xf, 0xf, true);
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_2301, 0xf, 0xf, true);
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_HALF_MIRROR, 0xf, 0xf, true);
-    v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true);
-    if constexpr (GL == 32) {
-        int a, b;
-        row_pair(v, a, b);
-        v = a + b;
-    }
-    return v;
-}
-
-// Group g's GL bits of a wave-wide ballot.
-template <int GL>
-__device__ __forceinline__ uint32_t group_bits(uint64_t m, int g) {
-    return (uint32_t)(m >> (GL * g)) & (GL == 32 ? 0xffffffffu : 0xffffu);
+    return v + __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true);
 }
 
 // |a - b| + c in one instruction, every operand per lane.
@@ -261,18 +234,31 @@ __device__ __forceinline__ uint32_t absdiff_add_v(uint32_t a, uint32_t b, uint32
     return d;
 }
 
-// The value v of lane `src` (any lane of the wavefront), per lane.
-__device__ __forceinline__ int lane_value(int v, int src) {
-    return __builtin_amdgcn_ds_bpermute(src << 2, v);
+// set_moved for the moved positions of all groups, the lanes of `at`, with
+// per-lane values.
+template <int OFF>
+__device__ __forceinline__ void set_moved_v(uint64_t at, uint32_t za, int d_new, int tabu_new,
+                                            int &nr, int &x, int &D, int &tabu) {
+    uint64_t all;
+    asm volatile(
+        "s_and_saveexec_b64 %0, %5\n\t"
+        "ds_write_b8 %6, %1 offset:%9\n\t"
+        "v_mov_b32 %2, 0\n\t"
+        "v_mov_b32 %3, %7\n\t"
+        "v_mov_b32 %4, %8\n\t"
+        "v_sub_u32 %1, 0, %1\n\t"
+        "s_mov_b64 exec, %0"
+        : "=&s"(all), "+&v"(nr), "+&v"(x), "+&v"(D), "+&v"(tabu)
+        : "s"(at), "v"(za), "v"(d_new), "v"(tabu_new), "n"(OFF)
+        : "memory", "scc");
 }
 
-// Walks at processing-order positions pos0 .. pos0 + 64 / GL - 1 (those below
-// `end`), all of N <= GL NL <= 32, on one wavefront; `lds` holds 64 / GL walks'
-// tables.  Results as the one-walk-per-wavefront form writes them.
-template <int GL, int NL, bool TRACE>
+// Walks at processing-order positions pos0 .. pos0 + 3 (those below `end`),
+// all of N <= 16 NL, on one wavefront; `lds` holds four walks' tables.  Results as the one-walk-per-wavefront form writes them.
+template <int NL, bool TRACE>
 __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t end,
                                 uint8_t *lds_wave) {
-    constexpr int SPAN = GL * NL;
+    constexpr int GL = kGroupLanes, SPAN = GL * NL;
     static_assert(SPAN <= 32, "one-word masks");
     using L = WalkTables<SPAN>;
     const int lane = lane_id();
@@ -294,7 +280,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
 #pragma unroll
         for (int h = 0; h < NL; ++h) {
             const int j = l + GL * h;
-            M |= group_bits<GL>(ballot(j < N && row[j] < 0), g) << (GL * h);
+            M |= ((uint32_t)(ballot(j < N && row[j] < 0) >> (GL * g)) & 0xffffu) << (GL * h);
         }
     } else {
         const Draw4 d = philox10((uint32_t)w, 0u, 0u, kTagStart, a.k0, a.k1);
@@ -328,7 +314,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
         const int x = l + GL * i - SPAN;
         SP[x] = x >= 0 && x < N ? (((M >> x) & 1u) ? (int8_t)-4 : (int8_t)4) : (int8_t)0;
     }
-    const int E0 = group_sum<GL>(sq_e);
+    const int E0 = group_sum(sq_e);
     wave_sync();
 
     // D_j = Q_2j - 1 - s_j v_j, v_j = sum_i s_i C_|i-j|
@@ -349,19 +335,25 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
     }
     uint32_t P = ~M;  // bit i set <=> s_i = +1
     uint32_t best = P;
+    int ed = 0;  // E - E0
+    int bd = 0;  // its minimum over the walk
     const int N4 = 4 * (N - 1);
-    int ed = 0;      // E - E0
-    int bd = 0;      // its minimum over the walk
-    const int thr0 = a.rule.aspiration ? -N4 : -(1 << 29);
-    int thr = thr0;  // aspiration threshold for D
+    // minus N4, and far below every key without aspiration
+    const int asp4 = -N4 - (a.rule.aspiration ? 0 : 1 << 29);
+    int thr = asp4;  // aspiration threshold for D
     const uint32_t ct = base + (uint32_t)L::CT;
     const uint32_t qt = base + (uint32_t)(L::QT + 4 * l);
     const uint32_t sy = base + (uint32_t)(L::SP - (l + GL * (NL - 1)));
     const uint32_t sz = base + (uint32_t)(L::SP + 2 * l);
-    // the half and the dword of a ballot that hold this lane's group
-    const bool upper = g * GL >= 32;
-    const uint32_t half_sel = (g & 1) && GL == 16 ? 0x07060302u : 0x05040100u;
-    const int T_all = -wave_min(-sch.T);  // the longest walk of the wavefront
+    uint32_t ct4[NL];
+#pragma unroll
+    for (int h = 0; h < NL; ++h) ct4[h] = 4u * (uint32_t)(l + GL * h);
+    const uint32_t group_at = (uint32_t)(GL * g);  // of a ballot
+    const int src0 = 4 * GL * g;                   // byte address of the group's first lane
+    const int T_all = -wave_min(-sch.T);           // the longest walk of the wavefront
+    // the shortest one: no walk ends before (a group without a walk runs
+    // along in its own tables and stores nothing)
+    const int T_each = wave_min(live ? sch.T : INT_MAX);
 
     for (int t0 = 1; t0 <= T_all; t0 += GL) {
         // lane l of a group: the draws of its walk's step t0 + l
@@ -372,11 +364,10 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             dr0 = d.w0;
             expire = t0 + l + sch.lo + (int)below(d.w1, (uint32_t)(sch.hi - sch.lo + 1));
         }
-        const int t_end = min(T_all, t0 + GL - 1);
-        for (int t = t0; t <= t_end; ++t) {
-            const int src = g * GL + (t - t0);  // the lane holding this step's draws
-            const uint32_t dr = (uint32_t)lane_value((int)dr0, src);
-            const int tabu_new = lane_value(expire, src);
+        auto step = [&](const int t, auto every) {
+            const int src = src0 + 4 * (t - t0);  // the lane holding this step's draws
+            const uint32_t dr = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)dr0);
+            const int tabu_new = __builtin_amdgcn_ds_bpermute(src, expire);
             int key[NL];
 #pragma unroll
             for (int h = 0; h < NL; ++h)
@@ -384,79 +375,81 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             int kmin = key[0];
 #pragma unroll
             for (int h = 1; h < NL; ++h) kmin = min(kmin, key[h]);
-            const int m = group_min<GL>(kmin);
+            const int m = group_min(kmin);
             // ties: the r-th lowest tied neighbour of the group, r from the
             // step's first draw
-            uint32_t tied;
-            {
-                uint32_t w[2] = {0u, 0u};
+            uint32_t tied = (uint32_t)(ballot(key[0] == m) >> group_at);
+            if constexpr (NL == 2)
+                tied = __builtin_amdgcn_perm((uint32_t)(ballot(key[1] == m) >> group_at), tied,
+                                             0x05040100u);
+            else
+                tied &= 0xffffu;
+            int r = (int)below(dr, (uint32_t)__popc(tied));
+            while (r > 0) {  // drop the r lowest
+                tied &= tied - 1u;
+                --r;
+            }
+            const uint32_t pick = (uint32_t)__builtin_ctz(tied);
+            if (!decltype(every)::value && t > sch.T) return;
+
+            const int nsp = __builtin_amdgcn_sbfe((int)P, pick, 1) | 1;  // -s_p
+            const int nsp4 = 4 * nsp;
+            P ^= 1u << pick;
+            const uint32_t za = sz - pick;
+            const int off = N4 - 32 * (t - 1);
+            const int gain = m + off;  // E' - E
+            // the moved position (as in tabu_walk): x = 0 keeps Q_2p, and
+            // the update changes its D by +16 (its z is the new spin)
+            const int d_new = 16 - gain - off;  // 4 (-d_p - 2 (N - 1)) + 32 t - 16
+            int x[NL];
 #pragma unroll
-                for (int h = 0; h < NL; ++h) {
-                    const uint64_t b = ballot(key[h] == m);
-                    w[h] = upper ? (uint32_t)(b >> 32) : (uint32_t)b;
-                }
-                if constexpr (GL == 32)
-                    tied = w[0];
-                else if constexpr (NL == 2)
-                    tied = __builtin_amdgcn_perm(w[1], w[0], half_sel);
+            for (int h = 0; h < NL; ++h) {
+                x[h] = mul_i24(nr[h], nsp);
+                const uint64_t at = ballot(l + GL * h == (int)pick);
+                if (h == 0)
+                    set_moved_v<0>(at, za, d_new, tabu_new, nr[h], x[h], D[h], tabu[h]);
                 else
-                    tied = (w[0] >> (16 * (g & 1))) & 0xffffu;
+                    set_moved_v<2 * GL>(at, za, d_new, tabu_new, nr[h], x[h], D[h], tabu[h]);
             }
-            const int r = (int)below(dr, (uint32_t)__popc(tied));
-            for (int i = 0; i < r; ++i) tied &= tied - 1u;  // drop the r lowest
-            const int pick = __builtin_ctz(tied);
-            if (t <= sch.T) {
-                const int nsp = __builtin_amdgcn_sbfe((int)P, pick, 1) | 1;  // -s_p
-                const int nsp4 = 4 * nsp;
-                P ^= 1u << pick;
-                const uint32_t za = sz - (uint32_t)pick;
-                const int gain = N4 + m - 32 * (t - 1);  // E' - E
-                // the moved position (as in tabu_walk): x = 0 keeps Q_2p, and
-                // the update changes its D by +16 (its z is the new spin)
-                const int d_new = 32 * t - gain - N4 - 16;  // 4 (-d_p - 2 (N - 1)) + 32 t
-                int x[NL];
+            const uint32_t qa = qt + 4u * pick;
+            uint32_t ya = sy + 2u * pick;
+            asm("" : "+v"(ya));  // one address, the words by offset
+            uint32_t ca[NL];
+            int cv[NL], qv[NL], yv[NL], zv[NL];
 #pragma unroll
-                for (int h = 0; h < NL; ++h) {
-                    x[h] = mul_i24(nr[h], nsp);
-                    if (l + GL * h == pick) {
-                        lds_store_i8(za + 2u * GL * h, nsp4);  // 4 s_p, after the move
-                        x[h] = 0;
-                        D[h] = d_new;
-                        tabu[h] = tabu_new;
-                        nr[h] = -nr[h];
-                    }
-                }
-                const uint32_t qa = qt + 4u * (uint32_t)pick;
-                uint32_t ya = sy + 2u * (uint32_t)pick;
-                asm("" : "+v"(ya));  // one address, the words by offset
-                uint32_t ca[NL];
-                int cv[NL], qv[NL], yv[NL], zv[NL];
-#pragma unroll
-                for (int h = 0; h < NL; ++h) {
-                    ca[h] = absdiff_add_v(4u * (uint32_t)pick, 4u * (uint32_t)(l + GL * h), ct);
-                    cv[h] = lds_load_i32(ca[h]);
-                    qv[h] = lds_load_i32(qa + 4u * GL * h);
-                    yv[h] = lds_load_i8(ya + (uint32_t)(GL * (NL - 1 - h)));
-                    zv[h] = lds_load_i8(za + 2u * GL * h);
-                }
-                ed += gain;
-                thr -= gain - 32;
-                const bool improved = ed < bd;
-                bd = min(bd, ed);
-                best = improved ? P : best;
-                thr = improved ? thr0 + 32 * t : thr;
-                if constexpr (TRACE) {
-                    if (l == 0) a.trace[w * (int64_t)a.trace_stride + t - 1] = (int16_t)pick;
-                }
-#pragma unroll
-                for (int h = 0; h < NL; ++h) {
-                    const int e = mad_i24(yv[h], nsp, cv[h]);
-                    D[h] = mad_i24(x[h], cv[h] + e + qv[h], D[h]);
-                    D[h] = mad_i24(zv[h], nsp4, D[h]);
-                    lds_store_i32(ca[h], e - x[h]);
-                    lds_store_i32(qa + 4u * GL * h, mad_i24_const<-2>(x[h], qv[h]));
-                }
+            for (int h = 0; h < NL; ++h) {
+                ca[h] = absdiff_add_v(4u * pick, ct4[h], ct);
+                cv[h] = lds_load_i32(ca[h]);
+                qv[h] = lds_load_i32(qa + 4u * GL * h);
+                yv[h] = lds_load_i8(ya + (uint32_t)(GL * (NL - 1 - h)));
+                zv[h] = lds_load_i8(za + 2u * GL * h);
             }
+            __builtin_amdgcn_sched_barrier(0);  // every load is out
+            ed += gain;
+            best = ed < bd ? P : best;
+            bd = min(bd, ed);
+            thr = bd - ed + (asp4 + 32 * t);
+            if constexpr (TRACE) {
+                if (l == 0 && live) a.trace[w * (int64_t)a.trace_stride + t - 1] = (int16_t)pick;
+            }
+#pragma unroll
+            for (int h = 0; h < NL; ++h) {
+                const int e = mad_i24(yv[h], nsp, cv[h]);
+                D[h] = mad_i24(x[h], cv[h] + e + qv[h], D[h]);
+                D[h] = mad_i24(zv[h], nsp4, D[h]);
+                lds_store_i32(ca[h], e - x[h]);
+                lds_store_i32(qa + 4u * GL * h, mad_i24_const<-2>(x[h], qv[h]));
+            }
+        };
+        int t = t0;
+        const int end = __builtin_amdgcn_readfirstlane(min(T_all, t0 + GL - 1));
+        const int each = min(T_each, end);
+        for (; t <= each; ++t) {
+            step(t, std::true_type());
+            wave_sync();
+        }
+        for (; t <= end; ++t) {
+            step(t, std::false_type());
             wave_sync();
         }
     }
@@ -471,23 +464,23 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
     }
 }
 
-// Walks of N <= GL NL at positions [begin, end), 64 / GL per wavefront and
-// WAVES wavefronts per workgroup.  PERSIST: a grid sized to the device takes
-// a wavefront's positions at a time from the queue head `counter`; otherwise
-// one wavefront per 64 / GL positions.
-template <int GL, int NL, int WAVES, bool PERSIST, bool TRACE>
+// Walks of N <= 16 NL at positions [begin, end), four per wavefront and WAVES
+// wavefronts per workgroup.  PERSIST: a grid sized to the device takes four
+// positions at a time from the queue head `counter`; otherwise one wavefront
+// per four positions.
+template <int NL, int WAVES, bool PERSIST, bool TRACE>
 __global__ __launch_bounds__(64 * WAVES) void tabu_kernel_group(TabuLaunchArgs a, int64_t begin,
                                                                 int64_t end, uint32_t *counter) {
-    constexpr int G = 64 / GL;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES][G * WalkTables<GL * NL>::BYTES];
+    constexpr int G = 64 / kGroupLanes;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES][G * WalkTables<kGroupLanes * NL>::BYTES];
     uint8_t *lds = lds_all[threadIdx.x >> 6];
     if constexpr (PERSIST) {
         for (int64_t pos = begin + next_work(counter, G); pos < end;
              pos = begin + next_work(counter, G))
-            run_group_walks<GL, NL, TRACE>(a, pos, end, lds);
+            run_group_walks<NL, TRACE>(a, pos, end, lds);
     } else {
         const int64_t pos = begin + ((int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6)) * G;
-        if (pos < end) run_group_walks<GL, NL, TRACE>(a, pos, end, lds);
+        if (pos < end) run_group_walks<NL, TRACE>(a, pos, end, lds);
     }
 }
 
@@ -654,37 +647,37 @@ hipError_t launch_wave(const TabuLaunchArgs &a, int64_t begin, int64_t end, int 
                               : launch_wave_t<NWMAX, WPG, false>(a, begin, end, groups, counter, s);
 }
 
-template <int GL, int NL, int WAVES, bool TRACE>
+template <int NL, int WAVES, bool TRACE>
 hipError_t launch_group_t(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
                           uint32_t *counter, hipStream_t s) {
-    constexpr int G = 64 / GL;
+    constexpr int G = 64 / kGroupLanes;
     const int64_t need = (end - begin + G * WAVES - 1) / (G * WAVES);
     if (groups > 0) {
         hipError_t e = launch_fill_u32(counter, 0u, 1, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((tabu_kernel_group<GL, NL, WAVES, true, TRACE>),
+        hipLaunchKernelGGL((tabu_kernel_group<NL, WAVES, true, TRACE>),
                            dim3((unsigned)std::min<int64_t>(groups, need)), dim3(64 * WAVES), 0, s,
                            a, begin, end, counter);
     } else {
         return launch_in_ranges(begin, end, G * WAVES, 64 * WAVES,
                                 [&](int64_t b, int64_t e, unsigned grid) {
-            hipLaunchKernelGGL((tabu_kernel_group<GL, NL, WAVES, false, TRACE>), dim3(grid),
+            hipLaunchKernelGGL((tabu_kernel_group<NL, WAVES, false, TRACE>), dim3(grid),
                                dim3(64 * WAVES), 0, s, a, b, e, counter);
         });
     }
     return hipGetLastError();
 }
 
-template <int GL, int NL, int WAVES>
+template <int NL, int WAVES>
 hipError_t launch_group(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
                         uint32_t *counter, hipStream_t s) {
     if (end <= begin) return hipSuccess;
     if constexpr (WAVES > 2) {
-        return hipErrorInvalidValue;  // 32 or 16 lanes per walk: 64- or 128-lane workgroups
+        return hipErrorInvalidValue;  // several walks per wavefront: 64- or 128-lane workgroups
     } else {
         return a.trace != nullptr
-                   ? launch_group_t<GL, NL, WAVES, true>(a, begin, end, groups, counter, s)
-                   : launch_group_t<GL, NL, WAVES, false>(a, begin, end, groups, counter, s);
+                   ? launch_group_t<NL, WAVES, true>(a, begin, end, groups, counter, s)
+                   : launch_group_t<NL, WAVES, false>(a, begin, end, groups, counter, s);
     }
 }
 
@@ -700,9 +693,9 @@ hipError_t launch_tabu_wpg(const TabuLaunchArgs &a, const WalkLaunch &l, const h
         const int64_t begin = f ? ce[f - 1] : 0, end = ce[wg.last[g]];
         uint32_t *q = a.counter + 32 * f;
         if (kind == kKindGroup2)
-            e = launch_group<32, 1, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_group<2, WPG>(a, begin, end, l.groups, q, st[g]);
         else if (kind == kKindGroup4)
-            e = launch_group<16, 1, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_group<1, WPG>(a, begin, end, l.groups, q, st[g]);
         else if (kClassMaxN[f] <= 64)
             e = launch_wave<1, WPG>(a, begin, end, l.groups, q, st[g]);
         else if (kClassMaxN[f] <= 128)
