@@ -45,11 +45,13 @@ __device__ __forceinline__ Draw4 philox10(uint32_t x0, uint32_t x1, uint32_t x2,
                                           uint32_t x3, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t a0 = x0, a2 = x2;
-        x0 = __umulhi(0xCD9E8D57u, a2) ^ x1 ^ k0;
-        x2 = __umulhi(0xD2511F53u, a0) ^ x3 ^ k1;
-        x1 = 0xCD9E8D57u * a2;
-        x3 = 0xD2511F53u * a0;
+        // one 64-bit product each instead of its halves apart: the multiplies
+        // are quarter-rate and a call is one chain of ten rounds
+        const uint64_t p2 = (uint64_t)0xCD9E8D57u * x2, p0 = (uint64_t)0xD2511F53u * x0;
+        x0 = (uint32_t)(p2 >> 32) ^ x1 ^ k0;
+        x2 = (uint32_t)(p0 >> 32) ^ x3 ^ k1;
+        x1 = (uint32_t)p2;
+        x3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -298,8 +300,8 @@ struct Schedule {
     int T, lo, hi;
 };
 
-__device__ __forceinline__ Schedule make_schedule(const RuleParams &r, int N, uint32_t k0,
-                                                  uint32_t k1, uint32_t entity, uint32_t gen) {
+// `draw` is word 0 of the walk's LEN draw (unused where the rule draws none).
+__device__ __forceinline__ Schedule make_schedule(const RuleParams &r, int N, uint32_t draw) {
     Schedule s;
     if (r.steps_rule == 0) {
         s.T = r.steps_a;
@@ -312,8 +314,7 @@ __device__ __forceinline__ Schedule make_schedule(const RuleParams &r, int N, ui
             lo = r.slo_num * N / r.slo_den;
             span = r.shi_num * N / r.shi_den - lo + 1;
         }
-        const Draw4 d = philox10(entity, gen, 0u, kTagLen, k0, k1);
-        s.T = lo + (int)below(d.w0, (uint32_t)span);
+        s.T = lo + (int)below(draw, (uint32_t)span);
     }
     if (r.tenure_rule == 0) {
         s.lo = r.lo_num * N / r.lo_den + r.lo_add;
@@ -334,15 +335,90 @@ __device__ __forceinline__ int lag_corr(Mask M, int N, int k) {
     return (N - k) - 2 * m_popc(m_and(m_xor(M, m_shr(M, k)), m_low(M, N - k)));
 }
 
-// Energy of one mask computed by a single lane (lane-serial, O(N) popcounts).
-template <typename Mask>
-__device__ __forceinline__ int lane_energy(Mask M, int N) {
-    int e = 0;
-    for (int k = 1; k < N; ++k) {
-        const int c = lag_corr(M, N, k);
-        e += c * c;
+// a * b + c of 24-bit factors (signed), a full-rate instruction: the
+// compiler turns products of spins into shifts, masks and the quarter-rate
+// 32-bit multiply.
+__device__ __forceinline__ int mad_i24(int a, int b, int c) {
+    int d;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+template <int B>
+__device__ __forceinline__ int mad_i24_const(int a, int c) {
+    static_assert(B >= -16 && B <= 64, "an inline constant");
+    int d;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "n"(B), "v"(c));
+    return d;
+}
+__device__ __forceinline__ int mad_i24_s(int a, int b, int c) {  // b wave-uniform
+    int d;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ int mul_i24(int a, int b) {
+    int d;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ int mul_i24_s(int a, int b) {  // b wave-uniform
+    int d;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "s"(b), "v"(a));
+    return d;
+}
+
+// Part of one row's energy in one lane: the lags k0, k0 + STEP, .. below
+// nmax (>= N), with the row's mask in W words:
+//   C_k = (N - k) - 2 popc over k <= i < N of (M ^ (M << k)).
+// M << k moves by STEP bits a lag; of lags in [32 b, 32 b + 32) the words
+// below b hold no pair.  Lags past N add nothing (N - k saturates at 0).
+template <int W, int STEP>
+__device__ __forceinline__ int lane_lags(const uint32_t *mask, int N, int nmax, int k0) {
+    static_assert(STEP < 32, "shifts stay within two words");
+    uint32_t M[W], Y[W], V[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        M[w] = mask[w];
+        const int n = N - 32 * w;  // valid bits of word w
+        V[w] = n >= 32 ? ~0u : n <= 0 ? 0u : (1u << n) - 1u;
+    }
+#pragma unroll
+    for (int w = W - 1; w >= 0; --w)
+        Y[w] = w ? __builtin_amdgcn_alignbit(M[w], M[w - 1], (uint32_t)(32 - k0)) : M[w] << k0;
+    int k = k0, e = 0;
+    uint32_t left = (uint32_t)max(N - k0, 0);  // N - k
+#pragma unroll
+    for (int b = 0; b < W; ++b) {
+        const int end = min(nmax, 32 * (b + 1));
+        for (; k < end; k += STEP) {
+            int pop = __popc((M[b] ^ Y[b]) & (V[b] & (~0u << (k & 31))));
+#pragma unroll
+            for (int w = b + 1; w < W; ++w) pop += __popc((M[w] ^ Y[w]) & V[w]);
+            const int c = mad_i24_const<-2>(pop, (int)left);
+            e = mad_i24(c, c, e);
+            left = __builtin_elementwise_sub_sat(left, (uint32_t)STEP);
+#pragma unroll
+            for (int w = W - 1; w > b; --w)
+                Y[w] = __builtin_amdgcn_alignbit(Y[w], Y[w - 1], 32 - STEP);
+            Y[b] <<= STEP;
+        }
     }
     return e;
+}
+
+// lane_lags with the mask in `words` (wave-uniform) words.
+template <int STEP>
+__device__ __forceinline__ int lane_energy(int words, const uint32_t *mask, int N, int nmax,
+                                           int k0) {
+    switch (words) {
+    case 1: return lane_lags<1, STEP>(mask, N, nmax, k0);
+    case 2: return lane_lags<2, STEP>(mask, N, nmax, k0);
+    case 3: return lane_lags<3, STEP>(mask, N, nmax, k0);
+    case 4: return lane_lags<4, STEP>(mask, N, nmax, k0);
+    case 5: return lane_lags<5, STEP>(mask, N, nmax, k0);
+    case 6: return lane_lags<6, STEP>(mask, N, nmax, k0);
+    case 7: return lane_lags<7, STEP>(mask, N, nmax, k0);
+    default: return lane_lags<8, STEP>(mask, N, nmax, k0);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -404,37 +480,6 @@ __device__ __forceinline__ void lds_store_i8(uint32_t a, int v) {
 __device__ __forceinline__ int lds_load_i32(uint32_t a) { return *(const lds_i32 *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store_i32(uint32_t a, int v) {
     *(lds_i32 *)(uintptr_t)a = v;
-}
-
-// a * b + c of 24-bit factors (signed), a full-rate instruction: the
-// compiler turns products of spins into shifts, masks and the quarter-rate
-// 32-bit multiply.
-__device__ __forceinline__ int mad_i24(int a, int b, int c) {
-    int d;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
-}
-template <int B>
-__device__ __forceinline__ int mad_i24_const(int a, int c) {
-    static_assert(B >= -16 && B <= 64, "an inline constant");
-    int d;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "n"(B), "v"(c));
-    return d;
-}
-__device__ __forceinline__ int mad_i24_s(int a, int b, int c) {  // b wave-uniform
-    int d;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
-    return d;
-}
-__device__ __forceinline__ int mul_i24(int a, int b) {
-    int d;
-    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
-    return d;
-}
-__device__ __forceinline__ int mul_i24_s(int a, int b) {  // b wave-uniform
-    int d;
-    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "s"(b), "v"(a));
-    return d;
 }
 
 // One neighbour's part of a move at p (see tabu_walk): c = 2 C_|p-j|,

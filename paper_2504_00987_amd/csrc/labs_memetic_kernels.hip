@@ -21,52 +21,58 @@ constexpr int kMaxK = 128;
 // ---------------------------------------------------------------------------
 // Memetic replicas.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t word_of(const Draw4 &d, int i) {
-    return i == 0 ? d.w0 : (i == 1 ? d.w1 : (i == 2 ? d.w2 : d.w3));
-}
-
-// Member m = lane + 64 h of the replica (K <= 128): bits 128 q .. 128 q + 127
-// are the draw (pop, m, q, INIT); its energy is computed lane-serially.
-template <typename Mask>
-__device__ __forceinline__ int init_member(const MemeticLaunchArgs &a, const MemeticSlot &sl,
-                                           int m, uint64_t wd[kStateWords]) {
-    const int N = sl.n;
-#pragma unroll
-    for (int q = 0; q < kStateWords / 2; ++q) {
-        const Draw4 d = philox10(sl.pop_id, (uint32_t)m, (uint32_t)q, kTagInit, sl.k0, sl.k1);
-        wd[2 * q] = (uint64_t)d.w0 | ((uint64_t)d.w1 << 32);
-        wd[2 * q + 1] = (uint64_t)d.w2 | ((uint64_t)d.w3 << 32);
-    }
-#pragma unroll
-    for (int h = 0; h < kStateWords; ++h) {
-        const int b = N - 64 * h;  // bits of word h inside the sequence
-        wd[h] &= b >= 64 ? ~0ull : b <= 0 ? 0ull : ((1ull << b) - 1ull);
-    }
-    return lane_energy<Mask>(make_mask<sizeof(Mask) / 8>(wd[0], wd[1], wd[2], wd[3]), N);
-}
-
-__global__ __launch_bounds__(64) void memetic_init_kernel(MemeticLaunchArgs a) {
+// Random populations, one workgroup per replica: member m = lane + 64 h
+// (K <= 128) is the bits 128 q .. 128 q + 127 of the draws (pop, m, q, INIT);
+// each of the four wavefronts takes every fourth lag of every member's
+// energy, a member per lane.  (One wavefront with all lags: 33 us at K = 100,
+// N = 120.)
+constexpr int kInitWaves = 4;
+__global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLaunchArgs a) {
+    __shared__ int part[kInitWaves][kMaxK];
     const int s = blockIdx.x;
     if (s >= a.n_slots) return;
     const MemeticSlot sl = a.slots[s];
     if (sl.state < 0) return;
-    const int lane = lane_id();
-    const int N = sl.n, K = a.K;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int N = __builtin_amdgcn_readfirstlane(sl.n), K = a.K;
     const int64_t base = (int64_t)sl.state * K;
-    uint64_t wd[2][kStateWords] = {};
-    int e[2] = {INT_MAX, INT_MAX};
+    const int words = (N + 31) >> 5;
+    uint32_t wd[2][2 * kStateWords];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int q = 0; q < kStateWords / 2; ++q) {
+            Draw4 d = {0u, 0u, 0u, 0u};
+            if (128 * q < N && 64 * h < K)
+                d = philox10(sl.pop_id, (uint32_t)(lane + 64 * h), (uint32_t)q, kTagInit, sl.k0,
+                             sl.k1);
+            const uint32_t dw[4] = {d.w0, d.w1, d.w2, d.w3};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int b = N - 32 * (4 * q + i);  // bits of the word inside the sequence
+                wd[h][4 * q + i] = dw[i] & (b >= 32 ? ~0u : b <= 0 ? 0u : (1u << b) - 1u);
+            }
+        }
+        part[wave][lane + 64 * h] =
+            64 * h < K ? lane_energy<kInitWaves>(words, wd[h], N, N, wave + 1) : 0;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    int e[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int m = lane + 64 * h;
+        e[h] = 0;
+#pragma unroll
+        for (int w = 0; w < kInitWaves; ++w) e[h] += part[w][m];
         if (m < K) {
-            const int c = memetic_class(N);
-            e[h] = c == 0 ? init_member<uint64_t>(a, sl, m, wd[h])
-                 : c == 1 ? init_member<M128>(a, sl, m, wd[h])
-                          : init_member<M256>(a, sl, m, wd[h]);
 #pragma unroll
             for (int w = 0; w < kStateWords; ++w)
-                a.st.pop[(base + m) * kStateWords + w] = wd[h][w];
+                a.st.pop[(base + m) * kStateWords + w] =
+                    (uint64_t)wd[h][2 * w] | ((uint64_t)wd[h][2 * w + 1] << 32);
             a.st.popE[base + m] = e[h];
+        } else {
+            e[h] = INT_MAX;
         }
     }
     // bestSeq: the lowest-index member of minimum energy.
@@ -76,31 +82,64 @@ __global__ __launch_bounds__(64) void memetic_init_kernel(MemeticLaunchArgs a) {
     const int src = t0 ? __builtin_ctzll(t0) : __builtin_ctzll(t1);
 #pragma unroll
     for (int w = 0; w < kStateWords; ++w) {
-        const uint64_t sel = h == 0 ? wd[0][w] : wd[1][w];
-        const uint64_t v = ((uint64_t)readlane_u((uint32_t)(sel >> 32), src) << 32) |
-                           readlane_u((uint32_t)sel, src);
-        a.st.best[(int64_t)sl.state * kStateWords + w] = v;  // uniform values, every lane
+        const uint32_t lo = h == 0 ? wd[0][2 * w] : wd[1][2 * w];
+        const uint32_t hi = h == 0 ? wd[0][2 * w + 1] : wd[1][2 * w + 1];
+        a.st.best[(int64_t)sl.state * kStateWords + w] =  // uniform values, every lane
+            ((uint64_t)readlane_u(hi, src) << 32) | readlane_u(lo, src);
     }
     a.st.bestE[sl.state] = mn;
     a.st.gen[sl.state] = 0;
     a.st.hit[sl.state] = -1;
 }
 
-// Mutation mask of a child: bit i flips when word i%4 of draw
-// (pop, g, base + i/4, MUT) is below thr.
+// The draws of one child: (pop, g, 2b, GEN), (pop, g, 2b + 1, GEN), word 0 of
+// (pop, walk generation, 0, LEN) and the mutation mask, bit i of which flips
+// when word i % 4 of (pop, g, 64 b + i / 4, MUT) is below thr.  Lanes 0, 1
+// and 2 take the first three counters and, for N <= 128, lane 32 + q mutation
+// draw q, so one call of the generator serves them all; longer sequences
+// take a second one.
 template <int NW>
-__device__ __forceinline__ typename MaskOf<NW>::type mutation_mask(const MemeticSlot &sl,
-                                                                   uint32_t gg, uint32_t base,
-                                                                   uint32_t thr) {
+struct ChildDraws {
+    Draw4 a, b;
+    uint32_t len;
+    typename MaskOf<NW>::type flips;
+};
+template <int NW>
+__device__ __forceinline__ ChildDraws<NW> child_draws(const MemeticSlot &sl, uint32_t g,
+                                                      uint32_t walk_gen, uint32_t b, int N,
+                                                      uint32_t thr) {
+    static_assert(NW <= 2 || NW == 4, "N <= 128 or N <= 256");
     const int lane = lane_id();
+    const bool mut = lane >= 32;
+    const Draw4 d = philox10(sl.pop_id, lane == 2 ? walk_gen : g,
+                             mut ? 64u * b + (uint32_t)(lane - 32) : lane == 2 ? 0u : 2u * b + lane,
+                             mut ? kTagMut : lane == 2 ? kTagLen : kTagGen, sl.k0, sl.k1);
+    ChildDraws<NW> r;
+    r.a = {readlane_u(d.w0, 0), readlane_u(d.w1, 0), readlane_u(d.w2, 0), readlane_u(d.w3, 0)};
+    r.b = {readlane_u(d.w0, 1), readlane_u(d.w1, 1), readlane_u(d.w2, 1), readlane_u(d.w3, 1)};
+    r.len = readlane_u(d.w0, 2);
+    // bit q of word k: word k of mutation draw q is below thr
+    uint64_t hit[4];
+    if constexpr (NW <= 2) {
+        hit[0] = ballot(d.w0 < thr) >> 32;
+        hit[1] = ballot(d.w1 < thr) >> 32;
+        hit[2] = ballot(d.w2 < thr) >> 32;
+        hit[3] = ballot(d.w3 < thr) >> 32;
+    } else {
+        const Draw4 e = philox10(sl.pop_id, g, 64u * b + (uint32_t)lane, kTagMut, sl.k0, sl.k1);
+        hit[0] = ballot(e.w0 < thr);
+        hit[1] = ballot(e.w1 < thr);
+        hit[2] = ballot(e.w2 < thr);
+        hit[3] = ballot(e.w3 < thr);
+    }
+    // lane i of word h: position i + 64 h, draw (i + 64 h) / 4, word i % 4
+    const uint64_t mine = lane & 1 ? (lane & 2 ? hit[3] : hit[1]) : (lane & 2 ? hit[2] : hit[0]);
     uint64_t f[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
-    for (int h = 0; h < NW; ++h) {
-        const int i = lane + 64 * h;
-        const Draw4 d = philox10(sl.pop_id, gg, base + (uint32_t)(i >> 2), kTagMut, sl.k0, sl.k1);
-        f[h] = ballot(i < sl.n && word_of(d, i & 3) < thr);
-    }
-    return make_mask<NW>(f[0], f[1], f[2], f[3]);
+    for (int h = 0; h < NW; ++h)
+        f[h] = ballot(lane + 64 * h < N && ((mine >> ((lane >> 2) + 16 * h)) & 1ull));
+    r.flips = make_mask<NW>(f[0], f[1], f[2], f[3]);
+    return r;
 }
 
 // A child's walk of N <= 64 NW (NW = 4: N > 128) on one wavefront, with the
@@ -109,8 +148,8 @@ template <int NW>
 __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskOf<NW>::type &child,
                                                      const MemeticLaunchArgs &a,
                                                      const MemeticSlot &sl, uint32_t gen,
-                                                     uint8_t *lds) {
-    const Schedule sch = make_schedule(a.rule, N, sl.k0, sl.k1, sl.pop_id, gen);
+                                                     uint32_t len, uint8_t *lds) {
+    const Schedule sch = make_schedule(a.rule, N, len);
     if (NW == 4 && __builtin_amdgcn_readfirstlane(N) <= 192) {
         const auto r = tabu_walk<NW == 4 ? 3 : NW>(N, child, sch, a.rule.aspiration, sl.k0, sl.k1,
                                                    sl.pop_id, gen, lds, nullptr);
@@ -148,8 +187,8 @@ __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &s
             break;
         }
         const uint32_t gg = (uint32_t)g;
-        const Draw4 da = philox10(sl.pop_id, gg, 0u, kTagGen, sl.k0, sl.k1);
-        const Draw4 db = philox10(sl.pop_id, gg, 1u, kTagGen, sl.k0, sl.k1);
+        const ChildDraws<NW> cd = child_draws<NW>(sl, gg, gg, 0u, N, thr);
+        const Draw4 &da = cd.a, &db = cd.b;
         Mask child;
         if (da.w0 < a.p_comb) {
             // selectParents: two binary tournaments; Combine: one-point crossover
@@ -167,9 +206,8 @@ __device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &s
             const int c = (int)below(da.w1, (uint32_t)K);
             child = load_mask<NW>(pop[c]);
         }
-        // Mutate: bit i flips when word i%4 of draw (pop, g, i/4, MUT) < thr.
-        child = m_xor(child, mutation_mask<NW>(sl, gg, 0u, thr));
-        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, gg, lds);
+        child = m_xor(child, cd.flips);  // Mutate
+        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, gg, cd.len, lds);
         if (r.best_e < bestE) {
             bestE = r.best_e;
             best = r.best;
@@ -268,8 +306,9 @@ __global__ __launch_bounds__(64 * kMaxChildren) void memetic_batched_kernel(
             break;
         }
         const uint32_t gg = (uint32_t)g;
-        const Draw4 da = philox10(sl.pop_id, gg, (uint32_t)(2 * b), kTagGen, sl.k0, sl.k1);
-        const Draw4 db = philox10(sl.pop_id, gg, (uint32_t)(2 * b + 1), kTagGen, sl.k0, sl.k1);
+        const uint32_t wgen = (uint32_t)(g * B + b);
+        const ChildDraws<NW> cd = child_draws<NW>(sl, gg, wgen, (uint32_t)b, N, thr);
+        const Draw4 &da = cd.a, &db = cd.b;
         Mask child;
         if (da.w0 < a.p_comb) {
             int i = (int)below(da.w1, (uint32_t)K), j = (int)below(da.w2, (uint32_t)K);
@@ -286,10 +325,8 @@ __global__ __launch_bounds__(64 * kMaxChildren) void memetic_batched_kernel(
             const int c = (int)below(da.w1, (uint32_t)K);
             child = load_mask<NW>(pop[c]);
         }
-        // child b's mutation words: (pop, g, 64 b + i/4, MUT)
-        child = m_xor(child, mutation_mask<NW>(sl, gg, (uint32_t)(64 * b), thr));
-        const uint32_t wgen = (uint32_t)(g * B + b);
-        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, lds);
+        child = m_xor(child, cd.flips);
+        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, cd.len, lds);
         uint64_t *mine = res + kResWords * b;
         store_mask<NW>(mine, r.best);  // uniform values, every lane of wavefront b
         mine[4] = (uint64_t)(uint32_t)r.best_e;
@@ -366,7 +403,7 @@ __global__ void gather_best_kernel(MemeticStateDev st, const int32_t *__restrict
 
 hipError_t launch_memetic_init(const MemeticLaunchArgs &a, hipStream_t s) {
     if (a.n_slots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(memetic_init_kernel, dim3((unsigned)a.n_slots), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(memetic_init_kernel, dim3((unsigned)a.n_slots), dim3(64 * kInitWaves), 0, s, a);
     return hipGetLastError();
 }
 

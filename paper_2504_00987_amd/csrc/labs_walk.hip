@@ -53,45 +53,6 @@ __device__ __forceinline__ uint32_t row_bits16(const int8_t *row, int c, int N) 
     return bits & (N - x >= 16 ? 0xFFFFu : (1u << (N - x)) - 1u);
 }
 
-// Part of one row's energy in one lane: the lags k0, k0 + STEP, .. below
-// nmax (>= N), with the row's mask in W words:
-//   C_k = (N - k) - 2 popc over k <= i < N of (M ^ (M << k)).
-// M << k moves by STEP bits a lag; of lags in [32 b, 32 b + 32) the words
-// below b hold no pair.  Lags past N add nothing (N - k saturates at 0).
-template <int W, int STEP>
-__device__ __forceinline__ int lane_lags(const uint32_t *mask, int N, int nmax, int k0) {
-    static_assert(STEP < 32, "shifts stay within two words");
-    uint32_t M[W], Y[W], V[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        M[w] = mask[w];
-        const int n = N - 32 * w;  // valid bits of word w
-        V[w] = n >= 32 ? ~0u : n <= 0 ? 0u : (1u << n) - 1u;
-    }
-#pragma unroll
-    for (int w = W - 1; w >= 0; --w)
-        Y[w] = w ? __builtin_amdgcn_alignbit(M[w], M[w - 1], (uint32_t)(32 - k0)) : M[w] << k0;
-    int k = k0, e = 0;
-    uint32_t left = (uint32_t)max(N - k0, 0);  // N - k
-#pragma unroll
-    for (int b = 0; b < W; ++b) {
-        const int end = min(nmax, 32 * (b + 1));
-        for (; k < end; k += STEP) {
-            int pop = __popc((M[b] ^ Y[b]) & (V[b] & (~0u << (k & 31))));
-#pragma unroll
-            for (int w = b + 1; w < W; ++w) pop += __popc((M[w] ^ Y[w]) & V[w]);
-            const int c = mad_i24_const<-2>(pop, (int)left);
-            e = mad_i24(c, c, e);
-            left = __builtin_elementwise_sub_sat(left, (uint32_t)STEP);
-#pragma unroll
-            for (int w = W - 1; w > b; --w)
-                Y[w] = __builtin_amdgcn_alignbit(Y[w], Y[w - 1], 32 - STEP);
-            Y[b] <<= STEP;
-        }
-    }
-    return e;
-}
-
 // Eq. (2) for 64 rows per workgroup: the rows' sign bits are packed into LDS
 // with 16-byte loads, then lane l of every wavefront holds row l as a bit
 // mask and the four wavefronts take every fourth lag.  Bound: VALU, three
@@ -126,17 +87,7 @@ __global__ __launch_bounds__(64 * kEnergyWaves) void energy_kernel(
     }
     __syncthreads();
     const uint32_t *m = mask[lane];
-    int e = 0;
-    switch (words) {  // wave-uniform
-    case 1: e = lane_lags<1, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 2: e = lane_lags<2, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 3: e = lane_lags<3, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 4: e = lane_lags<4, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 5: e = lane_lags<5, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 6: e = lane_lags<6, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    case 7: e = lane_lags<7, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    default: e = lane_lags<8, kEnergyWaves>(m, N, nmax, wave + 1); break;
-    }
+    int e = lane_energy<kEnergyWaves>(words, m, N, nmax, wave + 1);
     part[wave][lane] = e;
     __syncthreads();
     if (wave == 0 && lane < rows) {
@@ -180,12 +131,18 @@ __device__ __forceinline__ typename MaskOf<NW>::type walk_start(const TabuLaunch
     return make_mask<NW>(wd[0], wd[1], wd[2], wd[3]);
 }
 
+// Word 0 of the draw (walk, 0, 0, LEN), where the rule draws the length.
+__device__ __forceinline__ uint32_t length_draw(const RuleParams &r, uint32_t k0, uint32_t k1,
+                                                uint32_t walk) {
+    return r.steps_rule >= 2 ? philox10(walk, 0u, 0u, kTagLen, k0, k1).w0 : 0u;
+}
+
 // One walk on one wavefront, NW neighbours per lane.
 template <int NW, bool TRACE>
 __device__ void run_tabu_item(const TabuLaunchArgs &a, int64_t w, int N, uint8_t *lds) {
     const int lane = lane_id();
     const auto M = walk_start<NW>(a, w, N);
-    const Schedule sch = make_schedule(a.rule, N, a.k0, a.k1, (uint32_t)w, 0u);
+    const Schedule sch = make_schedule(a.rule, N, length_draw(a.rule, a.k0, a.k1, (uint32_t)w));
     const WalkResult<NW> r =
         tabu_walk<NW, TRACE>(N, M, sch, a.rule.aspiration, a.k0, a.k1, (uint32_t)w, 0u, lds,
                              TRACE ? a.trace + w * (int64_t)a.trace_stride : nullptr);
@@ -286,7 +243,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
         const Draw4 d = philox10((uint32_t)w, 0u, 0u, kTagStart, a.k0, a.k1);
         M = N > 0 ? d.w0 & (0xffffffffu >> (32 - N)) : 0u;
     }
-    Schedule sch = make_schedule(a.rule, N, a.k0, a.k1, (uint32_t)w, 0u);
+    Schedule sch = make_schedule(a.rule, N, length_draw(a.rule, a.k0, a.k1, (uint32_t)w));
     if (!live) sch.T = 0;
     const uint32_t Mr = N > 0 ? __builtin_bitreverse32(M) >> (32 - N) : 0u;  // bit i: s_{N-1-i}
 
