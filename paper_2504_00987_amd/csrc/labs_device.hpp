@@ -787,6 +787,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             }
             const int gain = m - off;  // E' - E = 4 (N - 1 + d_p)
             off += 32;
+            asm("" : "+s"(off));
             above += gain;
             asp += gain;
             if (__builtin_expect(above < 0, 0)) {
@@ -855,6 +856,7 @@ __device__ __forceinline__ WalkResult<NW> tabu_walk(const int N_in,
             __builtin_amdgcn_sched_barrier(0);  // every load is out
             if constexpr (NW == 1) moved(integral_constant<int, 0>());
             ++slot;
+            asm("" : "+s"(slot));  // one register: the loop closes with one branch
 
 #pragma unroll
             for (int h = 0; h < NW; ++h)
