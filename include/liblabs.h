@@ -175,14 +175,14 @@ int labs_skew_deviation_batch(labs_handle *h, const int8_t *seqs, const int32_t 
  * Exhaustive minimum of Eq. (2) over all 2^n sequences of length n
  * (3 <= n <= LABS_MAX_BRUTE_N), the reference targets for time-to-solution
  * at small n.  E is invariant under negation (Sec. II.B), so the 2^(n-1)
- * sequences with s_0 = +1 are searched (from n = 25 on by branch and bound).
+ * sequences with s_0 = +1 are searched (from n = 24 on by branch and bound).
  *   min_e   HOST int32: the minimum energy
  *   count   HOST int64 (or NULL): how many of the 2^n sequences attain it
  *   argmin  HOST int8 [n] (or NULL): of the minima with s_0 = +1, the one
  *           whose bit pattern (bit i set <=> s_i = -1) is the smallest
  *           integer
- * Synchronous (on the handle's stream).  n = 33 takes about half a
- * millisecond, n = 36 three, n = 40 seventy.
+ * Synchronous (on the handle's stream).  n = 33 takes about a
+ * third of a millisecond, n = 36 two, n = 40 fifty-five.
  */
 #define LABS_MAX_BRUTE_N 40
 int labs_bruteforce_min(labs_handle *h, int32_t n, int32_t *min_e, int64_t *count,

@@ -405,7 +405,7 @@ static int bruteforce_impl(labs_handle *h, int32_t n, bool skew, int32_t *min_e,
     // unrestricted searches that a bound shortens start from the best of a
     // batch of short walks
     const bool search = !skew && n >= kSearchMinN;
-    constexpr int kWalks = 4096, kWalkStride = 64;
+    constexpr int kWalks = 1024, kWalkStride = 64;
     const int64_t waves = skew ? skew_brute_waves(n) : search ? search_waves() : brute_waves(n);
     // Workspace: [out e | out count | out code | bound (256 B)] [part e]
     // [part count] [part code] [walk heads | walk e, e | walk sequences] [queue]

@@ -151,11 +151,12 @@ __global__ __launch_bounds__(256) void skew_bruteforce_kernel(int N, uint64_t pe
 // takes 64 root nodes of depth m0 at a time from a queue and runs their
 // subtrees in LDS: a stack per depth, always the deepest one that fills the
 // wavefront, so every lane has a node until the queue is empty.  A node's
-// children cost about ten instructions each.  Bound: VALU, with the queue
-// close behind.  Against evaluating every code (a call): n = 26 235 -> 115 us,
-// n = 30 3.3 -> 0.19 ms, n = 33 41 -> 0.47 ms, n = 35 174 -> 1.3 ms; n = 40
-// takes 67 ms.
+// children cost about ten instructions each.  Bound: VALU, most of it the last
+// lags of the leaves.  Against evaluating every code (a call): n = 26 235 ->
+// 68 us, n = 30 3.3 -> 0.14 ms, n = 33 41 -> 0.33 ms; n = 36 takes 2.3 ms,
+// n = 40 54 ms.
 constexpr uint32_t kTwice = 1u << 31;     // in a node's second word: x' is not searched
+constexpr int kFirstLags = 2;              // evaluated before the leaves are gathered again
 constexpr int kStackNodes = 64 + 4 * 64;  // below 64 when a batch's children come on top
 
 // The queue of root batches is kQueues counters 256 bytes apart, each for the
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(64) void search_kernel(int N, int m0, uint32_t batc
                                                     uint32_t *queue, int32_t *bound,
                                                     int32_t *part_e, int64_t *part_count,
                                                     uint64_t *part_code) {
-    extern __shared__ uint2 stack[];  // [N / 2 - m0 + 1][kStackNodes]
+    extern __shared__ uint2 stack[];  // [N / 2 - m0 + 2][kStackNodes]
     const int lane = lane_id();
     const int half = N / 2;
     queue += kQueueStride * (blockIdx.x % kQueues);
@@ -257,50 +258,78 @@ __global__ __launch_bounds__(64) void search_kernel(int N, int m0, uint32_t batc
             wave_sync();
             continue;
         }
-        // all pairs fixed: the remaining lags, longest first, until no lane
-        // can reach the bound (odd N: both values of the middle spin)
-        for (int z = 0; z <= (N & 1); ++z) {
-            const U M = (U)l | ((U)h << (N - half)) | ((U)z << half);
-            int s = e, k = N - 1 - half;
-            for (; k >= 1; --k) {
-                const U low = (U)((U) ~(U)0 >> (8 * sizeof(U) - (N - k)));
+        // all pairs fixed: the remaining lags 1 .. N - 1 - half, the longest
+        // sums first.  C_k^2 added for k in [from, to); false once no lane
+        // can reach the bound (the lengths still to come: half + 1 .. N - k - 1)
+        auto lags = [&](U M, int from, int to, int &sum) {
+            for (int k = from; k < to; ++k) {
                 int p;
-                if constexpr (sizeof(U) == 8)
-                    p = __popcll((M ^ (M >> k)) & low);
-                else
-                    p = __popc((M ^ (M >> k)) & low);
+                if (sizeof(U) == 4 || N - k <= 32) {  // the pairs fit the low word
+                    uint32_t x = (uint32_t)M >> k;
+                    if constexpr (sizeof(U) == 8)
+                        x = __builtin_amdgcn_alignbit((uint32_t)(M >> 32), (uint32_t)M, (uint32_t)k);
+                    p = __popc(((uint32_t)M ^ x) & (~0u >> (32 - (N - k))));
+                } else {
+                    p = __popcll((M ^ (M >> k)) & (~0ull >> (64 - (N - k))));
+                }
                 const int c = (N - k) - 2 * p;
-                s = mad_i24(c, c, s);
-                if (ballot(on && s <= ub - odd_lengths(N - k + 1, N)) == 0ull) break;
+                sum = mad_i24(c, c, sum);
+                if (ballot(on && sum <= ub - ((N - k) / 2 - (half + 1) / 2)) == 0ull) return false;
             }
-            if (k >= 1) continue;
-            if (on && s <= ub) {
-                // the smallest code of the sequence and its images with s_0 = +1
-                const uint64_t low = ~0ull >> (64 - N);
-                const uint64_t X = (uint64_t)M;
-                uint64_t R = __builtin_bitreverse64(X) >> (64 - N);
-                R = R & 1ull ? ~R & low : R;
-                auto least = [&](uint64_t v) {
-                    const uint64_t alt = (v ^ 0xAAAAAAAAAAAAAAAAull) & low;
-                    return alt < v ? alt : v;
-                };
-                const uint64_t cx = least(X), cr = least(R);
-                const uint64_t code = (cr < cx ? cr : cx) >> 1;
-                if (s < best) {
-                    best = s;
-                    cnt = 0;
-                    best_code = ~0ull;
-                }
-                if (s == best) {
-                    cnt += twice ? 4 : 2;
-                    best_code = code < best_code ? code : best_code;
-                }
+            return true;
+        };
+        if (m == half) {
+            // both values of an odd length's middle spin; what the first lags
+            // leave (a fifth) is gathered again on the last stack
+            const int thr = ub - ((N - kFirstLags) / 2 - (half + 1) / 2);
+            int at = readlane(held, level + 1);
+            const int at0 = at;
+            for (uint32_t z = 0; z <= (uint32_t)(N & 1); ++z) {
+                int sum = e;
+                if (!lags((U)l | ((U)h << (N - half)) | ((U)z << half), 1, 1 + kFirstLags, sum))
+                    continue;
+                const bool keep = on && sum <= thr;
+                const uint64_t kept = ballot(keep);
+                if (keep)
+                    stack[(level + 1) * kStackNodes + at +
+                          __builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u))] =
+                        make_uint2(l | ((uint32_t)sum << 20), h | (z << 30) | twice);
+                at += (int)__popcll(kept);
             }
-            const int found = wave_min(on ? s : INT_MAX);
-            if (found < ub) {
-                ub = found;
-                atomicMin(bound, found);  // one value from every lane
+            held += lane == level + 1 ? at - at0 : 0;
+            wave_sync();
+            continue;
+        }
+        const U M = (U)l | ((U)(h & 0xFFFFFu) << (N - half)) | ((U)(h >> 30) << half);
+        int s = e;
+        if (!lags(M, 1 + kFirstLags, N - half, s)) continue;
+        if (on && s <= ub) {
+            // the smallest code of the sequence and its images with s_0 = +1
+            const uint64_t low = ~0ull >> (64 - N);
+            const uint64_t X = (uint64_t)M;
+            uint64_t R = __builtin_bitreverse64(X) >> (64 - N);
+            R = R & 1ull ? ~R & low : R;
+            auto least = [&](uint64_t v) {
+                const uint64_t alt = (v ^ 0xAAAAAAAAAAAAAAAAull) & low;
+                return alt < v ? alt : v;
+            };
+            const uint64_t cx = least(X), cr = least(R);
+            const uint64_t code = (cr < cx ? cr : cx) >> 1;
+            if (s < best) {
+                best = s;
+                cnt = 0;
+                best_code = ~0ull;
             }
+            if (s == best) {
+                cnt += twice ? 4 : 2;
+                best_code = code < best_code ? code : best_code;
+            }
+        }
+        const int found = wave_min(on ? s : INT_MAX);
+        if (found < ub) {
+            ub = found;
+            atomicMin(bound, found);  // one value from every lane
         }
     }
     write_part(best, cnt, best_code, (uint64_t)blockIdx.x, part_e, part_count, part_code);
@@ -308,37 +337,72 @@ __global__ __launch_bounds__(64) void search_kernel(int N, int m0, uint32_t batc
 
 // The search's start: its queue, and as the bound the least energy of W
 // walks and of the mean over all sequences, N (N - 1) / 2.
-__global__ __launch_bounds__(64) void search_start_kernel(const int32_t *best_e, int32_t W, int N,
-                                                          uint32_t *queue, int32_t *bound) {
+constexpr int kStartThreads = 1024;
+__global__ __launch_bounds__(kStartThreads) void search_start_kernel(const int32_t *best_e, int32_t W,
+                                                                     int N, uint32_t *queue,
+                                                                     int32_t *bound) {
+    __shared__ int part[kStartThreads / 64];
     int m = N * (N - 1) / 2;
-    for (int i = lane_id(); i < W; i += 64) m = min(m, best_e[i]);
-    for (uint32_t i = (uint32_t)lane_id(); i < kQueues; i += 64u) queue[kQueueStride * i] = 0u;
-    bound[0] = wave_min(m);  // uniform values, every lane
+    for (int i = (int)threadIdx.x; i < W; i += kStartThreads) m = min(m, best_e[i]);
+    if (threadIdx.x < kQueues) queue[kQueueStride * threadIdx.x] = 0u;
+    part[threadIdx.x >> 6] = wave_min(m);  // uniform values, every lane
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int i = 0; i < kStartThreads / 64; ++i) m = min(m, part[i]);
+    bound[0] = m;
 }
 
-__global__ __launch_bounds__(64) void bruteforce_reduce_kernel(int64_t waves, BruteParts p) {
-    const int lane = lane_id();
+// One workgroup: every thread a share of the wavefronts' parts, then thread 0
+// the threads' (with one wavefront, 25 us for 4096 parts).
+constexpr int kReduceThreads = 512;
+__global__ __launch_bounds__(kReduceThreads) void bruteforce_reduce_kernel(int64_t waves,
+                                                                          BruteParts p) {
+    __shared__ int best_s[kReduceThreads / 64];
+    __shared__ int64_t cnt_s[kReduceThreads / 64];
+    __shared__ uint64_t code_s[kReduceThreads / 64];
+    const int wave = (int)(threadIdx.x >> 6);
     int best = INT_MAX;
-    for (int64_t w = lane; w < waves; w += 64) best = min(best, p.part_e[w]);
-    const int m = wave_min(best);
     int64_t cnt = 0;
     uint64_t code = ~0ull;
-    for (int64_t w = lane; w < waves; w += 64) {
-        if (p.part_e[w] == m) {
-            cnt += p.part_count[w];
-            code = p.part_code[w] < code ? p.part_code[w] : code;
+    for (int64_t w = threadIdx.x; w < waves; w += kReduceThreads) {
+        const int e = p.part_e[w];
+        const int64_t n = p.part_count[w];
+        const uint64_t c = p.part_code[w];
+        if (e < best) {
+            best = e;
+            cnt = 0;
+            code = ~0ull;
+        }
+        if (e == best) {
+            cnt += n;
+            code = c < code ? c : code;
         }
     }
+    const int m = wave_min(best);
     int64_t tot = 0;
     uint64_t cmin = ~0ull;
-    for (int l = 0; l < 64; ++l) {
-        tot += ((int64_t)readlane_u((uint32_t)(cnt >> 32), l) << 32) |
-               readlane_u((uint32_t)cnt, l);
+    for (uint64_t at = ballot(best == m); at != 0ull; at &= at - 1ull) {
+        const int l = __builtin_ctzll(at);
+        tot += ((int64_t)readlane_u((uint32_t)(cnt >> 32), l) << 32) | readlane_u((uint32_t)cnt, l);
         const uint64_t cl = ((uint64_t)readlane_u((uint32_t)(code >> 32), l) << 32) |
                             readlane_u((uint32_t)code, l);
         cmin = cl < cmin ? cl : cmin;
     }
-    p.out_e[0] = m;  // uniform values, stored by every lane
+    best_s[wave] = m;  // uniform values, every lane
+    cnt_s[wave] = tot;
+    code_s[wave] = cmin;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    best = INT_MAX;
+    for (int i = 0; i < kReduceThreads / 64; ++i) best = min(best, best_s[i]);
+    tot = 0;
+    cmin = ~0ull;
+    for (int i = 0; i < kReduceThreads / 64; ++i)
+        if (best_s[i] == best) {
+            tot += cnt_s[i];
+            cmin = code_s[i] < cmin ? code_s[i] : cmin;
+        }
+    p.out_e[0] = best;
     p.out_count[0] = 2 * tot;  // and the negations (s_0 = -1)
     p.out_code[0] = cmin << 1;
 }
@@ -374,7 +438,7 @@ hipError_t launch_skew_bruteforce(int n, const BruteParts &p, hipStream_t s) {
     else
         hipLaunchKernelGGL(skew_bruteforce_kernel<2>, dim3(blocks), dim3(threads), 0, s, n, per,
                            total, p.part_e, p.part_count, p.part_code);
-    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(64), 0, s, (int64_t)(lanes >> 6), p);
+    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, (int64_t)(lanes >> 6), p);
     return hipGetLastError();
 }
 
@@ -391,15 +455,15 @@ hipError_t launch_search(int n, const BruteParts &p, const int32_t *walk_e, int3
     // (at n = 33 one pair more or less costs 10 to 25 %)
     const int m0 = std::min(n / 2 - 4, 13);
     const uint32_t batches = 1u << (2 * m0 - 8);
-    const size_t lds = (size_t)(n / 2 - m0 + 1) * kStackNodes * sizeof(uint2);
-    hipLaunchKernelGGL(search_start_kernel, dim3(1), dim3(64), 0, s, walk_e, walks, n, queue, bound);
+    const size_t lds = (size_t)(n / 2 - m0 + 2) * kStackNodes * sizeof(uint2);
+    hipLaunchKernelGGL(search_start_kernel, dim3(1), dim3(kStartThreads), 0, s, walk_e, walks, n, queue, bound);
     if (n <= 32)
         hipLaunchKernelGGL(search_kernel<uint32_t>, dim3(kSearchWaves), dim3(64), lds, s, n, m0,
                            batches, queue, bound, p.part_e, p.part_count, p.part_code);
     else
         hipLaunchKernelGGL(search_kernel<uint64_t>, dim3(kSearchWaves), dim3(64), lds, s, n, m0,
                            batches, queue, bound, p.part_e, p.part_count, p.part_code);
-    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(64), 0, s, (int64_t)kSearchWaves, p);
+    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, (int64_t)kSearchWaves, p);
     return hipGetLastError();
 }
 
@@ -411,7 +475,7 @@ hipError_t launch_bruteforce(int n, const BruteParts &p, hipStream_t s) {
     const unsigned threads = (unsigned)(lanes < 256 ? lanes : 256);
     hipLaunchKernelGGL(bruteforce_kernel, dim3(blocks), dim3(threads), 0, s, n, per, total,
                        p.part_e, p.part_count, p.part_code);
-    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(64), 0, s, (int64_t)(lanes >> 6), p);
+    hipLaunchKernelGGL(bruteforce_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, (int64_t)(lanes >> 6), p);
     return hipGetLastError();
 }
 

@@ -219,12 +219,11 @@ struct BruteParts {
 };
 int64_t brute_waves(int n);
 hipError_t launch_bruteforce(int n, const BruteParts &p, hipStream_t s);
-// The same by branch and bound, from kSearchMinN on (a call: n = 24 95 us by
-// enumeration, 110 by search; n = 25 138 and 113; n = 26 235 and 115):
-// `walk_e` holds the energies that `walks` walks reached, whose
+// The same by branch and bound, from kSearchMinN on (a call: n = 23 69 us by
+// enumeration; n = 24 82 us, by search 72; n = 25 138 and 72): `walk_e` holds the energies that `walks` walks reached, whose
 // least bounds the search from above; `queue` takes search_queue_bytes(),
 // `bound` one word.
-constexpr int kSearchMinN = 25;
+constexpr int kSearchMinN = 24;
 int64_t search_waves();
 size_t search_queue_bytes();
 hipError_t launch_search(int n, const BruteParts &p, const int32_t *walk_e, int32_t walks,
