@@ -335,22 +335,20 @@ typedef struct labs_memetic_params {
     int32_t stop_all;    /* 1: once any replica reaches target_e, every
                             replica stops at the end of the current chunk
                             (the global termination flag of Sec. IV) */
-    int32_t waves_per_replica; /* 0, 1 or 2: accepted, without effect (every
-                            replica runs on one wavefront per child) */
+    int32_t waves_per_replica; /* 0, 1 or 2: accepted, without effect (a child
+                            walks on one wavefront; how many children of a
+                            replica walk at a time is the library's choice) */
     int32_t children;    /* children per generation, 1..8 (0 means 1).  1 is
                             Alg. 1 (steady state).  B > 1 is the batched-
                             generation variant: B children are made from
                             the population as it stands at the start of the
                             generation, walked concurrently (one wavefront
-                            each), then merged in order b = 0..B-1 as Alg. 1
+                            each) and merged in order b = 0..B-1 as Alg. 1
                             merges its one child; child b draws from
                             (replica, g, 2b | 2b+1, GEN), mutates with
                             (replica, g, 64b + i/4, MUT) and walks as
                             generation g*B + b.  Targets are checked once per
-                            generation; hit_gen counts generations.  For
-                            N > 128, B is further limited to what one
-                            workgroup can hold (LABS_E_INVAL beyond; all 8
-                            on the MI355X). */
+                            generation; hit_gen counts generations. */
     int32_t resume;      /* 1: continue the replicas this handle holds (left
                             by its last labs_memetic_run or put there by
                             labs_memetic_load) instead of drawing new

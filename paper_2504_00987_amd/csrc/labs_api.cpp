@@ -291,10 +291,6 @@ int labs_create(labs_handle **out, int device) {
     for (int i = 0; i < kSideStreams && ok; ++i)
         ok = hipStreamCreateWithFlags(&h->sides.s[i], hipStreamNonBlocking) == hipSuccess &&
              hipEventCreateWithFlags(&h->sides.join[i], hipEventDisableTiming) == hipSuccess;
-    if (ok) {
-        h->max_children_wide = prepare_memetic_kernels();
-        ok = h->max_children_wide >= 0;
-    }
     if (ok) ok = noalloc_scratch_address(device, &h->scratch) == hipSuccess;
     if (ok) ok = hipEventCreateWithFlags(&h->mem_event, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; i < 4 && ok; ++i)

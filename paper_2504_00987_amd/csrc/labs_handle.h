@@ -49,7 +49,6 @@ struct labs_handle {
     liblabs::SideStreams sides{};      // further length classes of a mixed batch
     hipEvent_t ws_event = nullptr;     // completion of the last device-workspace user
     hipEvent_t stage_event = nullptr;  // completion of the last copy out of `pin`
-    int max_children_wide = 0;         // batched children per generation at N > 128
     void *scratch = nullptr;           // this device's allocation-free scratch
     bool ws_event_valid = false;
     bool stage_event_valid = false;
@@ -115,7 +114,6 @@ int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *sta
 int check_memetic(labs_handle *h, const labs_memetic_params *p);
 // Children per generation against what the device fits (classes: bit c set
 // when a replica of memetic_class c is present).
-int check_children(labs_handle *h, int children, int classes);
 // Bytes of device state per memetic replica with population size K.
 inline size_t memetic_state_bytes(int K) {
     return (size_t)K * (kStateWords * sizeof(uint64_t) + sizeof(int32_t)) +

@@ -182,6 +182,7 @@ struct MemeticLaunchArgs {
     int32_t gens;            // generations per launch
     int32_t classes;         // bit c set: some slot is of memetic_class c
     int32_t children;        // children per generation (1: Alg. 1)
+    int32_t cus;             // compute units of the device
     MemeticStateDev st;
     uint32_t *any_hit;       // set to 1 when a replica reaches its target
     const uint32_t *stop;    // nonzero: the launch does nothing (null: never)
@@ -245,11 +246,6 @@ hipError_t launch_memetic_init(const MemeticLaunchArgs &a, hipStream_t s);
 hipError_t launch_memetic_latch(const uint32_t *any_hit, uint32_t *stop,
                                 const volatile uint32_t *cancel, uint32_t epoch, int stop_all,
                                 hipStream_t s);
-// Once per device before the first launch: raises the dynamic LDS limit of
-// the batched-generation kernels to what kMaxChildren children need (N > 128:
-// as far as the device allows).  Returns the most children per generation
-// the N > 128 kernel can take, or -1 on failure.
-int prepare_memetic_kernels();
 // Advances every slot by a.gens generations.  With several length classes
 // present and `sides` given, the widest class runs on s and the others on
 // side streams forked from and joined back into s, concurrently; the

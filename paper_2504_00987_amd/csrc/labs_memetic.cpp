@@ -51,13 +51,6 @@ static MemLayout mem_layout(int pops, int K) {
 
 static_assert(kMaxChildren == LABS_MAX_CHILDREN, "kernel and ABI limits agree");
 
-int check_children(labs_handle *h, int children, int classes) {
-    if (children > 1 && (classes & 4) && children > h->max_children_wide)
-        return fail(h, LABS_E_INVAL, "children=%d: this device fits at most %d per generation "
-                    "for N > 128", children, h->max_children_wide);
-    return LABS_OK;
-}
-
 int check_memetic(labs_handle *h, const labs_memetic_params *p) {
     if (!p) return fail(h, LABS_E_INVAL, "null memetic params");
     if (p->K < 2 || p->K > LABS_MAX_K) return fail(h, LABS_E_INVAL, "K=%d out of [2, %d]", p->K, LABS_MAX_K);
@@ -156,7 +149,6 @@ extern "C" int labs_memetic_run(labs_handle *h, const labs_memetic_params *p,
         classes |= 1 << c;
     }
     const int children = std::max(1, (int)p->children);
-    if ((rc = check_children(h, children, classes))) return rc;
     const bool resume = p->resume == 1;
     if (resume) {
         const auto &hd = h->held;
@@ -241,6 +233,7 @@ extern "C" int labs_memetic_run(labs_handle *h, const labs_memetic_params *p,
     a.stop = d_flag + 1;
     a.classes = classes;
     a.children = children;
+    a.cus = std::max(1, h->num_cus);
     if (resume) {
         // any_hit carries over (the global flag of the run being continued);
         // the stop flag is this run's

@@ -1,10 +1,9 @@
 // Memetic kernels of liblabs for gfx950 and their launchers.
 //
 //   memetic_init_kernel    random populations (Alg. 1, first two lines)
-//   memetic_advance_kernel memetic generations (Alg. 1 / Alg. 3), one replica
-//                          per wavefront, population resident in LDS
-//   memetic_batched_kernel B children per generation, one wavefront each,
-//                          from one snapshot of the population
+//   memetic_advance_kernel memetic generations (Alg. 1 / Alg. 3), several
+//                          children of a replica in flight, population
+//                          resident in LDS
 //   gather_best_kernel     best sequences and energies to caller buffers
 #include <algorithm>
 
@@ -92,32 +91,44 @@ __global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLa
     a.st.hit[sl.state] = -1;
 }
 
-// The draws of one child: (pop, g, 2b, GEN), (pop, g, 2b + 1, GEN), word 0 of
-// (pop, walk generation, 0, LEN) and the mutation mask, bit i of which flips
-// when word i % 4 of (pop, g, 64 b + i / 4, MUT) is below thr.  Lanes 0, 1
-// and 2 take the first three counters and, for N <= 128, lane 32 + q mutation
-// draw q, so one call of the generator serves them all; longer sequences
-// take a second one.
+// The draws of child b of generation g: (pop, g, 2b, GEN), (pop, g, 2b + 1,
+// GEN), word 0 of (pop, walk generation, 0, LEN) and the mutation mask, bit i
+// of which flips when word i % 4 of (pop, g, 64 b + i / 4, MUT) is below thr.
+// Lanes 0, 1 and 2 take the first three counters and, for N <= 128, lane
+// 32 + q mutation draw q, so one call of the generator serves them all;
+// longer sequences take a second one.  Lanes 3 .. 2 + kLookback take the
+// second GEN draw of the children 1 .. kLookback before this one, whose word
+// 2 names the member that child replaces; `back` is how many generations
+// before this child's that one is (0: the same).
+constexpr int kLookback = 15;
 template <int NW>
 struct ChildDraws {
     Draw4 a, b;
     uint32_t len;
     typename MaskOf<NW>::type flips;
+    uint32_t w2;  // per lane: word 2 of the lane's draw
+    int back;     // per lane, lanes 3 .. 2 + kLookback
 };
 template <int NW>
 __device__ __forceinline__ ChildDraws<NW> child_draws(const MemeticSlot &sl, uint32_t g,
-                                                      uint32_t walk_gen, uint32_t b, int N,
-                                                      uint32_t thr) {
+                                                      uint32_t walk_gen, int b, int B,
+                                                      uint32_t magic, int N, uint32_t thr) {
     static_assert(NW <= 2 || NW == 4, "N <= 128 or N <= 256");
     const int lane = lane_id();
     const bool mut = lane >= 32;
-    const Draw4 d = philox10(sl.pop_id, lane == 2 ? walk_gen : g,
-                             mut ? 64u * b + (uint32_t)(lane - 32) : lane == 2 ? 0u : 2u * b + lane,
-                             mut ? kTagMut : lane == 2 ? kTagLen : kTagGen, sl.k0, sl.k1);
+    const int dist = lane - 2;  // of an earlier child
     ChildDraws<NW> r;
+    // ceil((dist - b) / B): t / B by a product, exact for t < 40 and B <= 8
+    r.back = dist > 0 ? (int)(((uint32_t)(dist - b + B - 1) * magic) >> 16) : 0;
+    const uint32_t slot = dist > 0 ? 2u * (uint32_t)(b - dist + r.back * B) + 1u
+                                   : 2u * (uint32_t)b + (uint32_t)lane;
+    const Draw4 d = philox10(sl.pop_id, mut ? g : lane == 2 ? walk_gen : g - (uint32_t)r.back,
+                             mut ? 64u * (uint32_t)b + (uint32_t)(lane - 32) : lane == 2 ? 0u : slot,
+                             mut ? kTagMut : lane == 2 ? kTagLen : kTagGen, sl.k0, sl.k1);
     r.a = {readlane_u(d.w0, 0), readlane_u(d.w1, 0), readlane_u(d.w2, 0), readlane_u(d.w3, 0)};
     r.b = {readlane_u(d.w0, 1), readlane_u(d.w1, 1), readlane_u(d.w2, 1), readlane_u(d.w3, 1)};
     r.len = readlane_u(d.w0, 2);
+    r.w2 = d.w2;
     // bit q of word k: word k of mutation draw q is below thr
     uint64_t hit[4];
     if constexpr (NW <= 2) {
@@ -126,7 +137,8 @@ __device__ __forceinline__ ChildDraws<NW> child_draws(const MemeticSlot &sl, uin
         hit[2] = ballot(d.w2 < thr) >> 32;
         hit[3] = ballot(d.w3 < thr) >> 32;
     } else {
-        const Draw4 e = philox10(sl.pop_id, g, 64u * b + (uint32_t)lane, kTagMut, sl.k0, sl.k1);
+        const Draw4 e = philox10(sl.pop_id, g, 64u * (uint32_t)b + (uint32_t)lane, kTagMut, sl.k0,
+                                 sl.k1);
         hit[0] = ballot(e.w0 < thr);
         hit[1] = ballot(e.w1 < thr);
         hit[2] = ballot(e.w2 < thr);
@@ -159,212 +171,258 @@ __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskO
                          nullptr);
 }
 
-// One replica on one wavefront.
+// One workgroup per replica, its children on the workgroup's wavefronts.
+//
+// The children of a replica (B = a.children per generation, numbered from the
+// launch's first) take effect one after another, but a child needs nothing
+// of an earlier one unless that one replaces a member it draws (of K, at most
+// four drawn, one replaced), and the draws of both are known beforehand.  So
+// wavefronts claim children in order, a child starts once the earlier
+// children that replace its members are finished, takes such a member from
+// the ring where finished children wait, and these are merged in order by
+// whichever wavefront finishes next: with K = 100 eight wavefronts keep six
+// children going.  The results are those of one child after another.
+//
+//   claimed   next child to start; a wavefront claims, walks, posts, claims
+//   merged    children below it are in the population, in order
+//   done[i]   child number + 1 once its result stands in ring slot i: a slot
+//             is read only by the kLookback children after its own, and the
+//             child that takes it next starts after these are merged
+//   built[i]  child number + 1 once it has read the population: a generation
+//             is merged only when all its B children have, since they are
+//             made from the population before it
+//   busy      held by the wavefront that merges; nobody waits for it, a
+//             wavefront that leaves it looks again
+//
+// Every wait ends: a child waits only for earlier generations (their results
+// and, kLookback children back, their merging; B <= 8 keeps its own
+// generation's out of that), children are claimed in order, a claimed child
+// that does not wait walks and is posted, and the last of a generation to be
+// posted finds all of them built and merges them if nobody else does.
+// Children past a reached target are dropped.
+//
+// A generation is one walk, a serial chain that leaves most of a SIMD idle:
+// 64 generations of 256 replicas at N = 120 took 2452 us on one wavefront per
+// replica, 37.5 us a generation, and take 529 us with eight; 16 generations
+// of eight children 899 us with a barrier after each generation, 766 us here.
+constexpr int kRing = 32;
+static_assert(kRing >= 2 * (kLookback + 1) && 2 + kLookback < 32 && kMaxChildren <= kLookback,
+              "a slot outlives its readers, its draws have a lane, no wait inside a generation");
+constexpr int kMaxMemeticWaves = 8;
+
 template <int NW>
-__device__ void memetic_replica(const MemeticLaunchArgs &a, const MemeticSlot &sl,
-                                uint64_t (*pop)[NW], int *popE, uint8_t *lds) {
-    using Mask = typename MaskOf<NW>::type;
-    const int lane = lane_id();
-    const int N = sl.n, K = a.K, st = sl.state;
-    const int64_t base = (int64_t)st * K;
-    for (int i = lane; i < K; i += 64) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) pop[i][w] = a.st.pop[(base + i) * kStateWords + w];
-        popE[i] = a.st.popE[base + i];
-    }
-    wave_sync();
-    Mask best = load_mask<NW>(a.st.best + (int64_t)st * kStateWords);
-    int bestE = a.st.bestE[st];
-    int64_t g = a.st.gen[st];
-    int64_t hit = a.st.hit[st];
-    const uint32_t thr = a.mut_rule == 0 ? (uint32_t)(0x100000000ull / (uint64_t)N) : a.p_mut;
-    const bool targeted = sl.target >= 0;
+struct __attribute__((aligned(16))) ReplicaLds {
+    uint64_t pop[kMaxK][NW];
+    uint64_t res[kRing][NW];
+    uint64_t best[NW];
+    int popE[kMaxK];
+    int resE[kRing], resSlot[kRing];
+    uint32_t done[kRing], built[kRing];
+    uint32_t claimed, merged, busy, stopped;
+    int bestE;
+    uint32_t total;  // children of this launch
+    int64_t g0;      // generations done before it
+};
 
-    for (int it = 0; it < a.gens; ++it) {
-        if (g >= sl.gen_limit) break;
-        if (targeted && bestE <= sl.target) {
-            if (hit < 0) hit = g;
-            break;
-        }
-        const uint32_t gg = (uint32_t)g;
-        const ChildDraws<NW> cd = child_draws<NW>(sl, gg, gg, 0u, N, thr);
-        const Draw4 &da = cd.a, &db = cd.b;
-        Mask child;
-        if (da.w0 < a.p_comb) {
-            // selectParents: two binary tournaments; Combine: one-point crossover
-            int i = (int)below(da.w1, (uint32_t)K), j = (int)below(da.w2, (uint32_t)K);
-            const int pa = popE[i] <= popE[j] ? i : j;
-            i = (int)below(da.w3, (uint32_t)K);
-            j = (int)below(db.w0, (uint32_t)K);
-            const int pb = popE[i] <= popE[j] ? i : j;
-            const int cut = 1 + (int)below(db.w1, (uint32_t)(N - 1));
-            const Mask A = load_mask<NW>(pop[pa]);
-            const Mask B = load_mask<NW>(pop[pb]);
-            const Mask lowm = m_low(A, cut);
-            child = m_or(m_and(A, lowm), m_and(B, m_not(lowm)));
-        } else {
-            const int c = (int)below(da.w1, (uint32_t)K);
-            child = load_mask<NW>(pop[c]);
-        }
-        child = m_xor(child, cd.flips);  // Mutate
-        const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, gg, cd.len, lds);
-        if (r.best_e < bestE) {
-            bestE = r.best_e;
-            best = r.best;
-        }
-        const int rep = (int)below(db.w2, (uint32_t)K);
-        wave_sync();
-        store_mask<NW>(pop[rep], r.best);  // uniform values, every lane
-        popE[rep] = r.best_e;
-        wave_sync();
-        ++g;
-        if (targeted && bestE <= sl.target) {
-            if (hit < 0) hit = g;
-            break;
-        }
-    }
-
-    for (int i = lane; i < K; i += 64) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) a.st.pop[(base + i) * kStateWords + w] = pop[i][w];
-        a.st.popE[base + i] = popE[i];
-    }
-    store_mask<NW>(a.st.best + (int64_t)st * kStateWords, best);  // uniform values, every lane
-    a.st.bestE[st] = bestE;
-    a.st.gen[st] = g;
-    a.st.hit[st] = hit;
-    if (hit >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
+// The launch's arguments and a slot, read again where they are used (scalar
+// loads, cached) so that they take no registers during the walks: kept there,
+// they spilled into the step loop.
+typedef const __attribute__((address_space(4))) MemeticLaunchArgs ConstArgs;
+typedef const __attribute__((address_space(4))) MemeticSlot ConstSlot;
+__device__ __forceinline__ const MemeticLaunchArgs &fresh_args() {
+    ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const MemeticLaunchArgs *)p;
+}
+__device__ __forceinline__ const MemeticSlot &fresh_slot(const MemeticLaunchArgs &a) {
+    ConstSlot *p = (ConstSlot *)(uintptr_t)(a.slots + blockIdx.x);
+    return *(const MemeticSlot *)p;
 }
 
-// Replicas of one length class: N <= 64 (NW = 1), 64 < N <= 128 (NW = 2) or
-// 128 < N <= 256 (NW = 4), one wavefront per replica; slots of the other
-// classes and idle slots return at once.
-template <int NW>
-__global__ __launch_bounds__(64) void memetic_advance_kernel(MemeticLaunchArgs a) {
-    __shared__ uint64_t pop[kMaxK][NW];
-    __shared__ int popE[kMaxK];
-    __shared__ __attribute__((aligned(16))) uint8_t lds[WalkLds<NW>::BYTES];
-    const int s = blockIdx.x;
-    if (s >= a.n_slots) return;
-    if (a.stop != nullptr && *a.stop != 0u) return;  // one value for the whole grid
-    const MemeticSlot sl = a.slots[s];
-    if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
-    memetic_replica<NW>(a, sl, pop, popE, lds);
+template <typename T>
+__device__ __forceinline__ T lds_get(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t lds_get_u(const uint32_t *p) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_get(p));
 }
 
-// Batched-generation variant: one workgroup of B = a.children wavefronts per
-// replica.  Wavefront b makes child b of generation g from the population as
-// it stands at the start of g (LDS, read-only while the children walk) and
-// walks it in its own LDS scratch; after a barrier every wavefront merges the
-// B results in order b = 0..B-1 into its copy of best, and wavefront 0
-// alone writes the replacements (so they land in order); a second barrier
-// publishes them.  All control flow depends only on values every wavefront
-// holds identically, so every wavefront reaches every barrier.
-// Dynamic LDS: population [kMaxK][NW] words, energies [kMaxK], per child
-// kResWords words (mask, energy, replaced slot), then the B walk scratches.
-constexpr int kResWords = 8;
+// Child c is posted and, at the first of a generation, all B are built.
 template <int NW>
-constexpr int batched_header() {
-    return kMaxK * 8 * NW + kMaxK * 4 + kMaxChildren * kResWords * 8;
+__device__ __forceinline__ bool mergeable(const ReplicaLds<NW> &L, uint32_t c, uint32_t B) {
+    if (lds_get_u(&L.done[c % kRing]) != c + 1u) return false;
+    if (B == 1u || c % B != 0u) return true;
+    const uint32_t i = c + min((uint32_t)lane_id(), B - 1u);
+    return ballot(lds_get(&L.built[i % kRing]) == i + 1u) == ~0ull;
+}
+
+// Merges what is posted, in order, unless another wavefront is at it.
+template <int NW>
+__device__ __forceinline__ void merge_children(ReplicaLds<NW> &L, uint32_t B, bool targeted,
+                                               int target) {
+    for (;;) {
+        uint32_t held = 1u;
+        if (lane_id() == 0)
+            held = __hip_atomic_exchange(&L.busy, 1u, __ATOMIC_SEQ_CST,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (__builtin_amdgcn_readfirstlane((int)held) != 0) return;
+        uint32_t c = lds_get_u(&L.merged);
+        bool stop = lds_get_u(&L.stopped) != 0u;
+        while (!stop && mergeable<NW>(L, c, B)) {
+            const int r = (int)(c % kRing);
+            const int slot = __builtin_amdgcn_readfirstlane(L.resSlot[r]);
+            const int e = __builtin_amdgcn_readfirstlane(L.resE[r]);
+            const auto m = load_mask<NW>(L.res[r]);
+            store_mask<NW>(L.pop[slot], m);  // uniform values, every lane
+            L.popE[slot] = e;
+            int be = __builtin_amdgcn_readfirstlane(L.bestE);
+            if (e < be) {
+                be = e;
+                store_mask<NW>(L.best, m);
+                L.bestE = e;
+            }
+            ++c;
+            if (targeted && be <= target && c % B == 0u) {
+                stop = true;
+                lds_put(&L.stopped, 1u);
+            }
+        }
+        lds_put(&L.merged, c);
+        lds_put(&L.busy, 0u);
+        if (stop || !mergeable<NW>(L, c, B)) return;
+    }
 }
 
 template <int NW>
-__global__ __launch_bounds__(64 * kMaxChildren) void memetic_batched_kernel(
-    MemeticLaunchArgs a) {
+__global__ __launch_bounds__(64 * kMaxMemeticWaves)
+__attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kernel(
+    MemeticLaunchArgs args) {
     using Mask = typename MaskOf<NW>::type;
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[];
-    uint64_t(*pop)[NW] = (uint64_t(*)[NW])dyn_lds;
-    int *popE = (int *)(dyn_lds + kMaxK * 8 * NW);
-    uint64_t *res = (uint64_t *)(dyn_lds + kMaxK * (8 * NW + 4));  // [B][kResWords]
-    const int s = blockIdx.x;
-    if (s >= a.n_slots) return;
-    if (a.stop != nullptr && *a.stop != 0u) return;  // one value for the whole grid
-    const MemeticSlot sl = a.slots[s];
-    if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
-    const int B = a.children;
-    const int b = (int)(threadIdx.x >> 6);
-    uint8_t *lds = dyn_lds + batched_header<NW>() + b * WalkLds<NW>::BYTES;
-    const int N = sl.n, K = a.K, st = sl.state;
-    const int64_t base = (int64_t)st * K;
-    for (int i = (int)threadIdx.x; i < K; i += 64 * B) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) pop[i][w] = a.st.pop[(base + i) * kStateWords + w];
-        popE[i] = a.st.popE[base + i];
-    }
-    __syncthreads();
-    Mask best = load_mask<NW>(a.st.best + (int64_t)st * kStateWords);
-    int bestE = a.st.bestE[st];
-    int64_t g = a.st.gen[st];
-    int64_t hit = a.st.hit[st];
-    const uint32_t thr = a.mut_rule == 0 ? (uint32_t)(0x100000000ull / (uint64_t)N) : a.p_mut;
-    const bool targeted = sl.target >= 0;
-
-    for (int it = 0; it < a.gens; ++it) {
-        if (g >= sl.gen_limit) break;
-        if (targeted && bestE <= sl.target) {
-            if (hit < 0) hit = g;
-            break;
+    ReplicaLds<NW> &L = *(ReplicaLds<NW> *)dyn_lds;
+    if ((int)blockIdx.x >= args.n_slots) return;
+    if (args.stop != nullptr && *args.stop != 0u) return;  // one value for the whole grid
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint8_t *lds = dyn_lds + sizeof(ReplicaLds<NW>) + wave * WalkLds<NW>::BYTES;
+    {
+        const MemeticLaunchArgs &a = fresh_args();
+        const MemeticSlot &sl = fresh_slot(a);
+        if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
+        const int K = a.K, st = sl.state;
+        const int64_t base = (int64_t)st * K;
+        const int64_t g0 = a.st.gen[st];
+        const int64_t left = min(sl.gen_limit - g0, (int64_t)a.gens);
+        if (left <= 0) {
+            if (threadIdx.x == 0 && a.st.hit[st] >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
+            return;
         }
-        const uint32_t gg = (uint32_t)g;
+        for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) L.pop[i][w] = a.st.pop[(base + i) * kStateWords + w];
+            L.popE[i] = a.st.popE[base + i];
+        }
+        for (int i = (int)threadIdx.x; i < kRing; i += (int)blockDim.x) L.done[i] = L.built[i] = 0u;
+        const int bestE0 = a.st.bestE[st];
+        if (threadIdx.x < NW) L.best[threadIdx.x] = a.st.best[(int64_t)st * kStateWords + threadIdx.x];
+        if (threadIdx.x == 0) {
+            L.claimed = L.merged = L.busy = 0u;
+            L.stopped = sl.target >= 0 && bestE0 <= sl.target ? 1u : 0u;
+            L.bestE = bestE0;
+            L.total = (uint32_t)left * (uint32_t)a.children;
+            L.g0 = g0;
+        }
+        __syncthreads();
+    }
+
+    for (;;) {
+        const MemeticLaunchArgs &a = fresh_args();
+        const MemeticSlot &sl = fresh_slot(a);
+        const int N = sl.n, K = a.K, B = a.children;
+        const uint32_t thr = a.mut_rule == 0 ? (uint32_t)(0x100000000ull / (uint64_t)N) : a.p_mut;
+        const uint32_t magic = 65536u / (uint32_t)B + 1u;
+        uint32_t idx = 0u;
+        if (lane == 0)
+            idx = __hip_atomic_fetch_add(&L.claimed, 1u, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+        idx = (uint32_t)__builtin_amdgcn_readfirstlane((int)idx);
+        if (idx >= lds_get_u(&L.total) || lds_get_u(&L.stopped) != 0u) break;
+        const uint32_t gi = idx / (uint32_t)B;
+        const int b = (int)(idx - gi * (uint32_t)B);
+        const int64_t g = (int64_t)uniform64((uint64_t)L.g0) + (int64_t)gi;
         const uint32_t wgen = (uint32_t)(g * B + b);
-        const ChildDraws<NW> cd = child_draws<NW>(sl, gg, wgen, (uint32_t)b, N, thr);
+        const ChildDraws<NW> cd = child_draws<NW>(sl, (uint32_t)g, wgen, b, B, magic, N, thr);
         const Draw4 &da = cd.a, &db = cd.b;
+        const bool comb = da.w0 < a.p_comb;
+        const int m0 = (int)below(da.w1, (uint32_t)K), m1 = (int)below(da.w2, (uint32_t)K);
+        const int m2 = (int)below(da.w3, (uint32_t)K), m3 = (int)below(db.w0, (uint32_t)K);
+        // wait for the earlier children that replace a member drawn here, and
+        // for the merging of those out of reach
+        const int rep = (int)below(cd.w2, (uint32_t)K);
+        const int dist = lane - 2;
+        const bool near = dist > 0 && dist <= kLookback && dist <= (int)idx && cd.back > 0;
+        const bool clash = near && (rep == m0 || (comb && (rep == m1 || rep == m2 || rep == m3)));
+        const uint32_t from = idx - (uint32_t)dist;  // the lane's earlier child
+        while (((int)lds_get_u(&L.merged) < (int)idx - kLookback ||
+                ballot(clash && lds_get(&L.done[from % kRing]) != from + 1u) != 0ull) &&
+               lds_get_u(&L.stopped) == 0u)
+            __builtin_amdgcn_s_sleep(4);
+        if (lds_get_u(&L.stopped) != 0u) break;
+        // member m: the ring slot of its nearest replacement, or -1
+        const auto replaced = [&](int m) {
+            const uint64_t at = ballot(near && rep == m);
+            return at ? (int)((idx + 2u - (uint32_t)__builtin_ctzll(at)) % kRing) : -1;
+        };
+        const auto energy = [&](int m, int r) { return r < 0 ? L.popE[m] : L.resE[r]; };
+        const auto member = [&](int m, int r) { return load_mask<NW>(r < 0 ? L.pop[m] : L.res[r]); };
+        const int r0 = replaced(m0);
         Mask child;
-        if (da.w0 < a.p_comb) {
-            int i = (int)below(da.w1, (uint32_t)K), j = (int)below(da.w2, (uint32_t)K);
-            const int pa = popE[i] <= popE[j] ? i : j;
-            i = (int)below(da.w3, (uint32_t)K);
-            j = (int)below(db.w0, (uint32_t)K);
-            const int pb = popE[i] <= popE[j] ? i : j;
+        if (comb) {
+            // selectParents: two binary tournaments; Combine: one-point crossover
+            const int r1 = replaced(m1), r2 = replaced(m2), r3 = replaced(m3);
+            const bool first = energy(m0, r0) <= energy(m1, r1);
+            const bool third = energy(m2, r2) <= energy(m3, r3);
             const int cut = 1 + (int)below(db.w1, (uint32_t)(N - 1));
-            const Mask A = load_mask<NW>(pop[pa]);
-            const Mask Bm = load_mask<NW>(pop[pb]);
+            const Mask A = first ? member(m0, r0) : member(m1, r1);
+            const Mask Bm = third ? member(m2, r2) : member(m3, r3);
             const Mask lowm = m_low(A, cut);
             child = m_or(m_and(A, lowm), m_and(Bm, m_not(lowm)));
         } else {
-            const int c = (int)below(da.w1, (uint32_t)K);
-            child = load_mask<NW>(pop[c]);
+            child = member(m0, r0);
         }
-        child = m_xor(child, cd.flips);
+        child = m_xor(child, cd.flips);  // Mutate
+        const int replaces = (int)below(db.w2, (uint32_t)K);
+        if (B > 1) lds_put(&L.built[idx % kRing], idx + 1u);
         const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, cd.len, lds);
-        uint64_t *mine = res + kResWords * b;
-        store_mask<NW>(mine, r.best);  // uniform values, every lane of wavefront b
-        mine[4] = (uint64_t)(uint32_t)r.best_e;
-        mine[5] = (uint64_t)below(db.w2, (uint32_t)K);
-        __syncthreads();
-        for (int c = 0; c < B; ++c) {
-            const uint64_t *rc = res + kResWords * c;
-            uint64_t wd[4] = {0ull, 0ull, 0ull, 0ull};
-#pragma unroll
-            for (int w = 0; w < NW; ++w) wd[w] = uniform64(rc[w]);
-            const int e = __builtin_amdgcn_readfirstlane((int)(uint32_t)rc[4]);
-            const int slot = __builtin_amdgcn_readfirstlane((int)(uint32_t)rc[5]);
-            const Mask m = make_mask<NW>(wd[0], wd[1], wd[2], wd[3]);
-            if (e < bestE) {
-                bestE = e;
-                best = m;
-            }
-            if (b == 0) {
-                store_mask<NW>(pop[slot], m);  // uniform values, every lane of wavefront 0
-                popE[slot] = e;
-            }
-        }
-        __syncthreads();
-        ++g;
-        if (targeted && bestE <= sl.target) {
-            if (hit < 0) hit = g;
-            break;
-        }
+        const MemeticLaunchArgs &a2 = fresh_args();
+        const int target = fresh_slot(a2).target;
+        const int slot = (int)(idx % kRing);
+        store_mask<NW>(L.res[slot], r.best);  // uniform values, every lane
+        L.resE[slot] = r.best_e;
+        L.resSlot[slot] = replaces;
+        lds_put(&L.done[slot], idx + 1u);
+        merge_children<NW>(L, (uint32_t)a2.children, target >= 0, target);
     }
+    __syncthreads();
 
-    for (int i = (int)threadIdx.x; i < K; i += 64 * B) {
+    const MemeticLaunchArgs &a = fresh_args();
+    const int K = a.K, st = fresh_slot(a).state;
+    const int64_t base = (int64_t)st * K;
+    for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) a.st.pop[(base + i) * kStateWords + w] = pop[i][w];
-        a.st.popE[base + i] = popE[i];
+        for (int w = 0; w < NW; ++w) a.st.pop[(base + i) * kStateWords + w] = L.pop[i][w];
+        a.st.popE[base + i] = L.popE[i];
     }
-    if (b != 0) return;
-    store_mask<NW>(a.st.best + (int64_t)st * kStateWords, best);  // uniform values, every lane
-    a.st.bestE[st] = bestE;
+    if (threadIdx.x < NW) a.st.best[(int64_t)st * kStateWords + threadIdx.x] = L.best[threadIdx.x];
+    if (threadIdx.x != 0) return;
+    const int64_t g = L.g0 + (int64_t)(L.merged / (uint32_t)a.children);
+    int64_t hit = a.st.hit[st];
+    if (L.stopped != 0u && hit < 0) hit = g;
+    a.st.bestE[st] = L.bestE;
     a.st.gen[st] = g;
     a.st.hit[st] = hit;
     if (hit >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
@@ -417,59 +475,33 @@ hipError_t launch_memetic_latch(const uint32_t *any_hit, uint32_t *stop,
 
 namespace {
 
-// Batched generations: B wavefronts per replica and dynamic LDS for the
-// population plus B walk scratches.
+// Wavefronts per replica: eight while the device has them to spare, that is
+// up to eight replicas per compute unit (N <= 128) or two (N > 128, where a
+// wavefront holds more of the LDS and registers), four beyond, and no more
+// than the launch has children.  32 generations of K = 100 (MI355X, us) on
+// 1, 4 and 8 wavefronts per replica: N = 120 1352, 456 and 326 at 256
+// replicas, 1615, 946 and 909 at 2048, 3975, 2853 and 3002 at 8192; N = 200
+// 3075, 1017 and 718 at 256, 3209, 1246 and 956 at 512, 3261, 1492 and 1602
+// at 1024; N = 33 352, 131 and 101 at 256, 887, 769 and 788 at 8192.
 template <int NW>
-constexpr size_t batched_lds_bytes(int children) {
-    return batched_header<NW>() + (size_t)children * WalkLds<NW>::BYTES;
+int memetic_waves(const MemeticLaunchArgs &a) {
+    const int64_t spare = (int64_t)(NW == 4 ? 2 : 8) * a.cus;
+    const int64_t want = a.n_slots <= spare ? kMaxMemeticWaves : 4;
+    return (int)std::min(want, (int64_t)a.gens * a.children);
 }
 
 template <int NW>
-hipError_t launch_batched(const MemeticLaunchArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL((memetic_batched_kernel<NW>), dim3((unsigned)a.n_slots), dim3(64 * a.children),
-                       batched_lds_bytes<NW>(a.children), s, a);
+hipError_t launch_memetic_nw(const MemeticLaunchArgs &a, hipStream_t s) {
+    const int w = memetic_waves<NW>(a);
+    hipLaunchKernelGGL(memetic_advance_kernel<NW>, dim3((unsigned)a.n_slots), dim3(64 * w),
+                       sizeof(ReplicaLds<NW>) + (size_t)w * WalkLds<NW>::BYTES, s, a);
     return hipGetLastError();
 }
-
-}  // namespace
-
-int prepare_memetic_kernels() {
-    // raised in case the default limit of dynamic LDS is below eight children's
-    hipError_t e = hipFuncSetAttribute((const void *)memetic_batched_kernel<1>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)batched_lds_bytes<1>(kMaxChildren));
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)memetic_batched_kernel<2>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)batched_lds_bytes<2>(kMaxChildren));
-    if (e != hipSuccess) return -1;
-    for (int b = kMaxChildren; b >= 1; --b) {
-        if (hipFuncSetAttribute((const void *)memetic_batched_kernel<4>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)batched_lds_bytes<4>(b)) == hipSuccess)
-            return b;
-        (void)hipGetLastError();  // clear the refusal
-    }
-    return 0;
-}
-
-namespace {
 
 // Kernels of one memetic length class c (mask words 1 << c) on stream s.
 hipError_t launch_memetic_class(const MemeticLaunchArgs &a, int c, hipStream_t s) {
-    const dim3 grid((unsigned)a.n_slots);
-    if (a.children > 1) {
-        if (c == 0) return launch_batched<1>(a, s);
-        if (c == 1) return launch_batched<2>(a, s);
-        return launch_batched<4>(a, s);
-    }
-    if (c == 0)
-        hipLaunchKernelGGL(memetic_advance_kernel<1>, grid, dim3(64), 0, s, a);
-    else if (c == 1)
-        hipLaunchKernelGGL(memetic_advance_kernel<2>, grid, dim3(64), 0, s, a);
-    else
-        hipLaunchKernelGGL(memetic_advance_kernel<4>, grid, dim3(64), 0, s, a);
-    return hipGetLastError();
+    return c == 0 ? launch_memetic_nw<1>(a, s)
+                  : c == 1 ? launch_memetic_nw<2>(a, s) : launch_memetic_nw<4>(a, s);
 }
 
 }  // namespace

@@ -170,6 +170,7 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     a.gens = params.chunk;
     a.classes = classes;
     a.children = std::max(1, (int)params.children);
+    a.cus = std::max(1, h->num_cus);
     if (e == hipSuccess) e = launch_memetic_advance(a, stream, &sides);
     if (e == hipSuccess) e = hipMemcpyAsync(h_bestE, st.bestE, n_used * 4, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(h_gen, st.gen, n_used * 8, hipMemcpyDeviceToHost, stream);
@@ -286,10 +287,7 @@ extern "C" int labs_server_submit(labs_server *s, int32_t n, uint64_t seed, int3
     {
         // the tabu rule must be valid at this length
         labs_handle tmp;
-        tmp.max_children_wide = s->h->max_children_wide;
-        if (check_rule(&tmp, to_rule(s->params.tabu), n) ||
-            check_children(&tmp, std::max(1, (int)s->params.children), 1 << memetic_class(n)))
-            return LABS_E_INVAL;
+        if (check_rule(&tmp, to_rule(s->params.tabu), n)) return LABS_E_INVAL;
     }
     std::lock_guard<std::mutex> lk(s->mu);
     if (s->stop) return LABS_E_CANCELLED;

@@ -5,6 +5,7 @@ import pytest
 
 from oracle import oracle as O
 from paper_2504_00987_amd import inputs as I
+from tests.test_gpu_parity import _oracle_memetic, _oracle_walks
 
 pytestmark = pytest.mark.gpu
 
@@ -100,3 +101,77 @@ def test_exhaustive_minimum_search(lb, n, e, count, code):
     got_e, got_count, seq = lb.bruteforce_min(n)
     assert (got_e, got_count) == (e, count)
     assert sum(1 << i for i, s in enumerate(seq) if s < 0) == code
+
+
+# neighbours per lane and their masks change at 64, 128 and 192, several walks share a wavefront at
+# N <= 32 (16 lanes with one or two neighbours each), the last group of such a batch is partly idle
+@pytest.mark.parametrize("n", [15, 16, 17, 32, 33, 64, 65, 128, 129, 191, 192, 193, 256])
+@pytest.mark.parametrize("launch,walks", [((64, 1), 3), ((128, 2), 5), ((256, 4), 7),
+                                          ((64, 2), 5), ((64, 4), 1), ((64, 4), 9)])
+def test_walk_class_edges(lb, n, launch, walks):
+    rules = I.Rules(I.STEPS_MULT_N, 1, I.TENURE_LINEAR, 1, 10, 0, 1, 5, 0, 1)
+    lb.set_launch(*launch)
+    try:
+        res = lb.tabu_batch(rules, walks, 99 + n, n_uniform=n, out_stride=256, trace_stride=n)
+    finally:
+        lb.set_launch(None)
+    best, be, fe, trs = _oracle_walks(walks, n, rules, 99 + n)
+    assert np.array_equal(res.best_e.cpu().numpy(), be)
+    assert np.array_equal(res.final_e.cpu().numpy(), fe)
+    assert np.array_equal(res.best_seq.cpu().numpy()[:, :best.shape[1]], best)
+    assert np.array_equal(res.trace.cpu().numpy()[:, :n], np.stack(trs))
+
+
+# the default layout changes between 2048 and 2049 walks (N <= 16) and 4096 and 4097 (N <= 32)
+@pytest.mark.parametrize("lo,hi,walks", [(9, 16, 2048), (9, 16, 2049), (12, 32, 4096),
+                                         (12, 32, 4097), (12, 40, 4097)])
+def test_default_layout_lines(lb, lo, hi, walks):
+    rules = I.rules_tabu(2)
+    ns = I.uneven_lengths(walks, lo, hi, seed=walks)
+    res = lb.tabu_batch(rules, walks, 5, ns=ns)
+    lb.set_launch(64, 1)
+    try:
+        one = lb.tabu_batch(rules, walks, 5, ns=ns)
+    finally:
+        lb.set_launch(None)
+    for a, b in ((res.best_e, one.best_e), (res.final_e, one.final_e), (res.best_seq, one.best_seq)):
+        assert torch.equal(a, b)
+    head = _oracle_walks(20, ns, rules, 5, with_trace=False)[1]
+    assert np.array_equal(res.best_e.cpu().numpy()[:20], head)
+
+
+# children in flight: with K = 2 and 3 nearly every child waits for the one before it, with 128
+# few do; more and fewer generations than wavefronts; generations of one, three, seven and eight
+@pytest.mark.parametrize("K,gens,chunk", [(2, 21, 21), (3, 40, 7), (17, 5, 3), (128, 33, 33)])
+@pytest.mark.parametrize("children", [1, 3, 7, 8])
+def test_memetic_children_in_flight(lb, K, gens, chunk, children):
+    ns = np.array([24, 33, 64, 65, 96, 129, 193], dtype=np.int32)
+    rules = I.RULES_MEMETIC
+    batch = 0 if children == 1 else children
+    ref = _oracle_memetic(ns, K, rules, gens, 31 + K, children=batch)
+    res = lb.memetic_run(K, rules, gens, len(ns), 31 + K, ns=ns, chunk=chunk, children=children,
+                         out_stride=256)
+    for p, st in enumerate(ref):
+        assert (int(res.best_e[p]), int(res.gens_done[p])) == (st.bestE, gens)
+        assert np.array_equal(res.best_seq[p, :int(ns[p])].cpu().numpy(), st.best)
+    # a target that some replicas reach on the way, with later children in flight
+    target = sorted(st.bestE for st in ref)[len(ns) // 2]
+    ref = _oracle_memetic(ns, K, rules, gens, 31 + K, target=target, children=batch)
+    res = lb.memetic_run(K, rules, gens, len(ns), 31 + K, ns=ns, chunk=chunk, children=children,
+                         out_stride=256, target=target)
+    for p, st in enumerate(ref):
+        assert (int(res.best_e[p]), int(res.hit_gen[p])) == (st.bestE, st.hit)
+        assert int(res.gens_done[p]) == st.gen
+
+
+# both sides of the lines where a replica gets fewer wavefronts
+@pytest.mark.parametrize("n,pops", [(24, 2048), (24, 2049), (70, 2049), (130, 512), (130, 513)])
+def test_memetic_wavefront_lines(lb, n, pops):
+    rules = I.RULES_MEMETIC
+    kw = dict(n_uniform=n, out_stride=256)
+    many = lb.memetic_run(20, rules, 11, pops, 6, **kw)
+    few = lb.memetic_run(20, rules, 11, 24, 6, **kw)
+    assert torch.equal(many.best_e[:24], few.best_e)
+    assert torch.equal(many.best_seq[:24], few.best_seq)
+    ref = _oracle_memetic([n] * 4, 20, rules, 11, 6)
+    assert [int(e) for e in many.best_e[:4]] == [st.bestE for st in ref]
