@@ -366,14 +366,25 @@ __device__ __forceinline__ int mul_i24_s(int a, int b) {  // b wave-uniform
     return d;
 }
 
+// popc(x) + acc in one instruction.
+__device__ __forceinline__ int popc_add(uint32_t x, int acc) {
+    int d;
+    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(d) : "v"(x), "v"(acc));
+    return d;
+}
+
 // Part of one row's energy in one lane: the lags k0, k0 + STEP, .. below
-// nmax (>= N), with the row's mask in W words:
+// nmax (>= N) except 0, with the row's mask in W words, 0 <= k0 < STEP:
 //   C_k = (N - k) - 2 popc over k <= i < N of (M ^ (M << k)).
 // M << k moves by STEP bits a lag; of lags in [32 b, 32 b + 32) the words
-// below b hold no pair.  Lags past N add nothing (N - k saturates at 0).
+// below b hold no pair.  Lags past N add nothing (N - k saturates at 0, no
+// bit of a word is at or above the lag), so a trip of the loop takes four
+// lags: the shifted words' copies and the loop's own instructions were a
+// third of a trip with one.
 template <int W, int STEP>
 __device__ __forceinline__ int lane_lags(const uint32_t *mask, int N, int nmax, int k0) {
-    static_assert(STEP < 32, "shifts stay within two words");
+    constexpr int kLags = 4;
+    static_assert(32 % (STEP * kLags) == 0, "trips end with the words");
     uint32_t M[W], Y[W], V[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
@@ -383,23 +394,27 @@ __device__ __forceinline__ int lane_lags(const uint32_t *mask, int N, int nmax, 
     }
 #pragma unroll
     for (int w = W - 1; w >= 0; --w)
-        Y[w] = w ? __builtin_amdgcn_alignbit(M[w], M[w - 1], (uint32_t)(32 - k0)) : M[w] << k0;
-    int k = k0, e = 0;
+        Y[w] = w && k0 ? __builtin_amdgcn_alignbit(M[w], M[w - 1], (uint32_t)(32 - k0))
+                       : M[w] << k0;
+    int k = k0, e = k0 ? 0 : -N * N;  // the square of lag 0
     uint32_t left = (uint32_t)max(N - k0, 0);  // N - k
 #pragma unroll
     for (int b = 0; b < W; ++b) {
         const int end = min(nmax, 32 * (b + 1));
-        for (; k < end; k += STEP) {
-            int pop = __popc((M[b] ^ Y[b]) & (V[b] & (~0u << (k & 31))));
+        while (k < end) {
 #pragma unroll
-            for (int w = b + 1; w < W; ++w) pop += __popc((M[w] ^ Y[w]) & V[w]);
-            const int c = mad_i24_const<-2>(pop, (int)left);
-            e = mad_i24(c, c, e);
-            left = __builtin_elementwise_sub_sat(left, (uint32_t)STEP);
+            for (int i = 0; i < kLags; ++i, k += STEP) {
+                int pop = popc_add((M[b] ^ Y[b]) & (V[b] & (~0u << (k & 31))), 0);
 #pragma unroll
-            for (int w = W - 1; w > b; --w)
-                Y[w] = __builtin_amdgcn_alignbit(Y[w], Y[w - 1], 32 - STEP);
-            Y[b] <<= STEP;
+                for (int w = b + 1; w < W; ++w) pop = popc_add((M[w] ^ Y[w]) & V[w], pop);
+                const int c = mad_i24_const<-2>(pop, (int)left);
+                e = mad_i24(c, c, e);
+                left = __builtin_elementwise_sub_sat(left, (uint32_t)STEP);
+#pragma unroll
+                for (int w = W - 1; w > b; --w)
+                    Y[w] = __builtin_amdgcn_alignbit(Y[w], Y[w - 1], 32 - STEP);
+                Y[b] <<= STEP;
+            }
         }
     }
     return e;

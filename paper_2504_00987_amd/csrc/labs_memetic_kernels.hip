@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLa
             }
         }
         part[wave][lane + 64 * h] =
-            64 * h < K ? lane_energy<kInitWaves>(words, wd[h], N, N, wave + 1) : 0;
+            64 * h < K ? lane_energy<kInitWaves>(words, wd[h], N, N, wave) : 0;
     }
     __syncthreads();
     if (wave != 0) return;

@@ -33,41 +33,73 @@ __device__ __forceinline__ uint32_t sign_bits16(const uint4 &v) {
     return lo | (hi << 8);
 }
 
-// Bits [16 c, 16 c + 16) of a row's mask (bit i set <=> s_i = -1; bits past N
-// clear).  Rows may have any alignment and stride: the 16 bytes are read at
-// any address (global loads need no alignment on this target), and the last
-// chunk of a row from its last 16 bytes, so nothing past N is read.
-__device__ __forceinline__ uint32_t row_bits16(const int8_t *row, int c, int N) {
-    const int x = 16 * c;
-    if (x >= N) return 0u;
-    uint32_t bits;
-    if (N >= 16) {
-        const int at = min(x, N - 16);
-        uint4 v;
-        __builtin_memcpy(&v, row + at, 16);
-        bits = sign_bits16(v) >> (x - at);
-    } else {
-        bits = 0u;
-        for (int i = 0; i < N; ++i) bits |= (uint32_t)(row[i] < 0) << i;
+// Sign bits of a workgroup's rows into LDS (bit i set <=> s_i = -1; bits past
+// N clear): thread r * chunks + c takes bits [16 c, 16 c + 16) of row r, whose
+// length is len(r).  Rows may have any alignment and stride: the 16 bytes are
+// read at any address (global loads need no alignment on this target), and
+// the last chunk of a row from its last 16 bytes, so nothing past N is read.
+// A thread has kDeep reads in flight: a workgroup lives for little more than
+// these reads' latency, which one after another is what bounds it.
+constexpr int kEnergyWaves = 4, kEnergyThreads = 64 * kEnergyWaves;
+constexpr int kRowWords = LABS_MAX_N / 32;
+template <int ROWS, typename Len>
+__device__ __forceinline__ void load_row_masks(uint32_t (*mask)[kRowWords + 1],
+                                               const int8_t *__restrict__ seqs, int stride,
+                                               int words, Len len) {
+    constexpr int kDeep = 4;
+    const uint32_t chunks = 2u * (uint32_t)words, total = ROWS * chunks;
+    const uint32_t magic = 65536u / chunks + 1u;  // i / chunks, exact for i < 4096
+    for (uint32_t base = 0; base < total; base += kDeep * kEnergyThreads) {
+        uint4 v[kDeep];
+        int n[kDeep];
+        const auto at = [&](int j, uint32_t &r, uint32_t &c) {
+            const uint32_t i = base + (uint32_t)j * kEnergyThreads + threadIdx.x;
+            r = (i * magic) >> 16;
+            c = i - r * chunks;
+            return i < total;
+        };
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) {
+            uint32_t r, c;
+            const bool in = at(j, r, c);
+            n[j] = len((int)min(r, (uint32_t)ROWS - 1u));
+            const int x = 16 * (int)c;
+            if (in && x < n[j] && n[j] >= 16)
+                __builtin_memcpy(&v[j], seqs + (int)r * (int64_t)stride + min(x, n[j] - 16), 16);
+        }
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) {
+            uint32_t r, c, bits = 0u;
+            const bool in = at(j, r, c);
+            const int x = 16 * (int)c, left = n[j] - x;
+            if (in && left > 0) {
+                if (n[j] >= 16) {
+                    bits = sign_bits16(v[j]) >> max(16 - left, 0);
+                } else {
+                    const int8_t *row = seqs + (int)r * (int64_t)stride;
+                    for (int i = 0; i < n[j]; ++i) bits |= (uint32_t)(row[i] < 0) << i;
+                }
+            }
+            if (in) ((uint16_t *)mask[r])[c] = (uint16_t)bits;
+        }
     }
-    return bits & (N - x >= 16 ? 0xFFFFu : (1u << (N - x)) - 1u);
 }
 
-// Eq. (2) for 64 rows per workgroup: the rows' sign bits are packed into LDS
-// with 16-byte loads, then lane l of every wavefront holds row l as a bit
-// mask and the four wavefronts take every fourth lag.  Bound: VALU, three
-// instructions per 32 pairs and lag and four per lag (row l in one lane needs
-// no cross-lane sum, and a shift by a fixed number of bits is one instruction
-// a word; a row per wavefront takes twice as many).  262144 rows of N in
-// 20..128 (34 MB): 124 -> 15.9 us a call against a row per wavefront on
-// 256-bit masks.
-constexpr int kEnergyRows = 64, kEnergyWaves = 4;
-__global__ __launch_bounds__(64 * kEnergyWaves) void energy_kernel(
+// Eq. (2) for 64 rows per workgroup: lane l of every wavefront holds row l as
+// a bit mask and the four wavefronts take every fourth lag.  Bound: VALU,
+// three instructions per 32 pairs and lag and four per lag (row l in one lane
+// needs no cross-lane sum, and a shift by a fixed number of bits is one
+// instruction a word; a row per wavefront takes twice as many).  A group takes
+// as long as its longest row; 256 rows ordered by length first are 8 % faster
+// for a million rows and no faster for 262144.  262144 rows of N in 20..128
+// (34 MB): 14.8 us a call (124 with a row per wavefront on 256-bit masks,
+// 15.6 with one read in flight and a lag a trip); of N in 3..256 41.6 (48.9).
+constexpr int kEnergyRows = 64;
+__global__ __launch_bounds__(kEnergyThreads) void energy_kernel(
     const int8_t *__restrict__ seqs, const int32_t *__restrict__ ns, int32_t n_uniform,
     int32_t stride, int64_t count, int32_t *__restrict__ out) {
-    constexpr int kWords = 8;
     // rows of 9 words: lanes read their rows' words without bank conflicts
-    __shared__ uint32_t mask[kEnergyRows][kWords + 1];
+    __shared__ uint32_t mask[kEnergyRows][kRowWords + 1];
     __shared__ int part[kEnergyWaves][kEnergyRows];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t r0 = (int64_t)blockIdx.x * kEnergyRows;
@@ -75,19 +107,10 @@ __global__ __launch_bounds__(64 * kEnergyWaves) void energy_kernel(
     const int N = lane < rows ? (ns ? ns[r0 + lane] : n_uniform) : 0;
     const int nmax = -wave_min(-N);
     const int words = (nmax + 31) >> 5;
-    // 2 * words chunks of 16 bytes a row
-    const int chunks = 2 * words;
-    for (int i = (int)threadIdx.x; i < kEnergyRows * chunks; i += 64 * kEnergyWaves) {
-        const int r = i / chunks, c = i - r * chunks;
-        uint32_t bits = 0u;
-        if (r < rows)
-            bits = row_bits16(seqs + (r0 + r) * (int64_t)stride, c,
-                              ns ? ns[r0 + r] : n_uniform);
-        ((uint16_t *)mask[r])[c] = (uint16_t)bits;
-    }
+    load_row_masks<kEnergyRows>(mask, seqs + r0 * (int64_t)stride, stride, words,
+                                [&](int r) { return __shfl(N, r); });
     __syncthreads();
-    const uint32_t *m = mask[lane];
-    int e = lane_energy<kEnergyWaves>(words, m, N, nmax, wave + 1);
+    int e = lane_energy<kEnergyWaves>(words, mask[lane], N, nmax, wave);
     part[wave][lane] = e;
     __syncthreads();
     if (wave == 0 && lane < rows) {
@@ -567,9 +590,9 @@ hipError_t launch_in_ranges(int64_t begin, int64_t end, int per_group, int lanes
 hipError_t launch_energy(const int8_t *seqs, const int32_t *ns, int32_t n_uniform,
                          int32_t stride, int64_t count, int32_t *out, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    return launch_in_ranges(0, count, kEnergyRows, 64 * kEnergyWaves,
+    return launch_in_ranges(0, count, kEnergyRows, kEnergyThreads,
                             [&](int64_t b, int64_t e, unsigned grid) {
-        hipLaunchKernelGGL(energy_kernel, dim3(grid), dim3(64 * kEnergyWaves), 0, s,
+        hipLaunchKernelGGL(energy_kernel, dim3(grid), dim3(kEnergyThreads), 0, s,
                            seqs + b * (int64_t)stride, ns ? ns + b : nullptr, n_uniform, stride,
                            e - b, out + b);
     });
