@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLa
 // second GEN draw of the children 1 .. kLookback before this one, whose word
 // 2 names the member that child replaces; `back` is how many generations
 // before this child's that one is (0: the same).
-constexpr int kLookback = 15;
+constexpr int kLookback = 28;
 template <int NW>
 struct ChildDraws {
     Draw4 a, b;
@@ -181,7 +181,8 @@ __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskO
 // children that replace its members are finished, takes such a member from
 // the ring where finished children wait, and these are merged in order by
 // whichever wavefront finishes next: with K = 100 eight wavefronts keep six
-// children going.  The results are those of one child after another.
+// children going, twelve eight.  The results are those of one child after
+// another.
 //
 //   claimed   next child to start; a wavefront claims, walks, posts, claims
 //   merged    children below it are in the population, in order
@@ -203,12 +204,12 @@ __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskO
 //
 // A generation is one walk, a serial chain that leaves most of a SIMD idle:
 // 64 generations of 256 replicas at N = 120 took 2452 us on one wavefront per
-// replica, 37.5 us a generation, and take 529 us with eight; 16 generations
-// of eight children 899 us with a barrier after each generation, 766 us here.
-constexpr int kRing = 32;
+// replica, 37.5 us a generation, and take 451 us with twelve; 16 generations
+// of eight children 899 us with a barrier after each generation, 633 us here.
+constexpr int kRing = 64;
 static_assert(kRing >= 2 * (kLookback + 1) && 2 + kLookback < 32 && kMaxChildren <= kLookback,
               "a slot outlives its readers, its draws have a lane, no wait inside a generation");
-constexpr int kMaxMemeticWaves = 8;
+constexpr int kMaxMemeticWaves = 12;
 
 template <int NW>
 struct __attribute__((aligned(16))) ReplicaLds {
@@ -475,18 +476,20 @@ hipError_t launch_memetic_latch(const uint32_t *any_hit, uint32_t *stop,
 
 namespace {
 
-// Wavefronts per replica: eight while the device has them to spare, that is
-// up to eight replicas per compute unit (N <= 128) or two (N > 128, where a
-// wavefront holds more of the LDS and registers), four beyond, and no more
-// than the launch has children.  32 generations of K = 100 (MI355X, us) on
-// 1, 4 and 8 wavefronts per replica: N = 120 1352, 456 and 326 at 256
-// replicas, 1615, 946 and 909 at 2048, 3975, 2853 and 3002 at 8192; N = 200
-// 3075, 1017 and 718 at 256, 3209, 1246 and 956 at 512, 3261, 1492 and 1602
-// at 1024; N = 33 352, 131 and 101 at 256, 887, 769 and 788 at 8192.
+// Wavefronts per replica: twelve up to one replica per compute unit, eight
+// while the device has them to spare, that is up to eight replicas per
+// compute unit (N <= 128) or two (N > 128, where a wavefront holds more of the
+// LDS and registers), four beyond, and no more than the launch has children.
+// 32 generations of K = 100 (MI355X, us) on 1, 4, 8 and 12 wavefronts per
+// replica: N = 120 1352, 456, 318 and 294 at 256 replicas, 1390, 544, 426 and
+// 424 at 512, 1615, 946 and 909 (8) at 2048, 3975, 2853 and 3002 (8) at 8192;
+// N = 200 3075, 1017, 716 and 663 at 256, 3209, 1246, 956 and 1237 at 512,
+// 3261, 1492 and 1602 (8) at 1024; N = 33 352, 131, 107 and 91 at 256, 887,
+// 769 and 788 (8) at 8192.
 template <int NW>
 int memetic_waves(const MemeticLaunchArgs &a) {
     const int64_t spare = (int64_t)(NW == 4 ? 2 : 8) * a.cus;
-    const int64_t want = a.n_slots <= spare ? kMaxMemeticWaves : 4;
+    const int64_t want = a.n_slots <= a.cus ? kMaxMemeticWaves : a.n_slots <= spare ? 8 : 4;
     return (int)std::min(want, (int64_t)a.gens * a.children);
 }
 

@@ -165,7 +165,8 @@ def test_memetic_children_in_flight(lb, K, gens, chunk, children):
 
 
 # both sides of the lines where a replica gets fewer wavefronts
-@pytest.mark.parametrize("n,pops", [(24, 2048), (24, 2049), (70, 2049), (130, 512), (130, 513)])
+@pytest.mark.parametrize("n,pops", [(70, 256), (70, 257), (24, 2048), (24, 2049), (70, 2049),
+                                    (130, 512), (130, 513)])
 def test_memetic_wavefront_lines(lb, n, pops):
     rules = I.RULES_MEMETIC
     kw = dict(n_uniform=n, out_stride=256)
