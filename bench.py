@@ -33,17 +33,23 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# MI355X (gfx950) figures at its 2.4 GHz peak clock, 256 CUs: v_dot4_i32_i8
-# sums four int8 products into an int32 per lane, 64 lanes per CU-cycle (a
-# wave64 dot instruction every 4 cycles per SIMD) -- the contraction of the
-# neighbour scoring; one int32 operation per lane at that issue rate; the
-# CDNA4 LDS serves 256 bytes per CU-cycle (twice CDNA3's 128).  Under the
-# dot-product load of labs_device_peaks the clock measures about 2.06 GHz,
-# which is reported beside these.
+# MI355X (gfx950) figures at its 2.4 GHz peak clock, 256 CUs: one int32
+# operation per lane, 64 lanes per CU-cycle (a wave64 instruction every 4
+# cycles per SIMD; plain additions issue faster, which the measured peak
+# shows); v_dot4_i32_i8 sums four int8 products at that issue rate; the CDNA4
+# LDS serves 256 bytes per CU-cycle (twice CDNA3's 128).  Under the load of
+# labs_device_peaks the clock measures about 2.06 GHz, which is reported
+# beside these.
 CLOCK_HZ, CUS = 2.4e9, 256
 PEAK_DOT4_OPS = CUS * 64 * 4 * CLOCK_HZ    # 157.3e12 int8 products/s
 PEAK_INT32_OPS = CUS * 64 * CLOCK_HZ       # 39.3e12 int32 lane-ops/s
 PEAK_LDS_BYTES = CUS * 256 * CLOCK_HZ      # 157.3e12 B/s
+# A step's arithmetic per neighbour, a multiply-add as one operation: the sign
+# product of the two spins (1), the score's change from C_k, Q_m and two
+# further spins (5), the new C_k and Q_m (2), the test whether the move is
+# admissible (1) and the minimum (1); of the LDS it reads C_k, Q_m and two int8
+# spins and writes C_k and Q_m.
+OPS_PER_EVAL, LDS_BYTES_PER_EVAL = 10, 18
 METRIC = "flip-neighbour evals/sec (N=64..120) + time-to-target energy; batched vs plain"
 # What decides which walk kernels a call runs and how they are compiled: the
 # kernels, the length classes, the launch selection and the build flags.
@@ -62,84 +68,70 @@ KERNEL_SOURCES = ("paper_2504_00987_amd/csrc/labs_device.hpp",
 # XCDs; the LDS busy fraction is SQ_LDS_IDX_ACTIVE over one XCD's busy cycles
 # times the CUs.  SQ_WAVE_CYCLES and the SQ_*_ANY counters are wave-time in
 # units of four cycles.  The summaries live in profiles/.
-COPY_SCALE = {"FETCH_SIZE": 262144 / 131087, "WRITE_SIZE": 262144 / 262144}
+COPY_SCALE = {"FETCH_SIZE": 262144 / 131086, "WRITE_SIZE": 262144 / 262144}
 XCDS = 8
 COUNTERS_SOURCE = "profiles/tabu_kernel_counters.md"
-COUNTERS_DIGEST = "65597ff269d66762"
+COUNTERS_DIGEST = "90289fc2985257a5"
 COUNTERS = {
     ("tabu_n64", (64, 1, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 45513148, "SQ_INSTS_SALU": 33101021,
-        "SQ_INSTS_LDS": 13721600, "SQ_LDS_BANK_CONFLICT": 2847176,
-        "SQ_LDS_IDX_ACTIVE": 47100360, "GRBM_GUI_ACTIVE": 2602963, "SQ_WAVE_CYCLES": 249625723,
-        "SQ_ACTIVE_INST_ANY": 100487299, "SQ_WAIT_ANY": 90887124, "SQ_WAIT_INST_ANY": 58246496,
-        "FETCH_SIZE": 86.3, "WRITE_SIZE": 768.0},
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31554016, "SQ_INSTS_SALU": 20843490,
+        "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
+        "GRBM_GUI_ACTIVE": 1664244, "SQ_WAVE_CYCLES": 153963744, "SQ_ACTIVE_INST_ANY": 68958587,
+        "SQ_WAIT_ANY": 53984223, "SQ_WAIT_INST_ANY": 31291025, "FETCH_SIZE": 48.5,
+        "WRITE_SIZE": 768.0},
     ("tabu_n64", (128, 2, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 45537724, "SQ_INSTS_SALU": 33121501,
-        "SQ_INSTS_LDS": 13721600, "SQ_LDS_BANK_CONFLICT": 2847176,
-        "SQ_LDS_IDX_ACTIVE": 47100360, "GRBM_GUI_ACTIVE": 2641890, "SQ_WAVE_CYCLES": 244954014,
-        "SQ_ACTIVE_INST_ANY": 100529590, "SQ_WAIT_ANY": 84688251, "SQ_WAIT_INST_ANY": 59949379,
-        "FETCH_SIZE": 82.9, "WRITE_SIZE": 640.0},
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31578592, "SQ_INSTS_SALU": 20863970,
+        "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
+        "GRBM_GUI_ACTIVE": 1649351, "SQ_WAVE_CYCLES": 150494178, "SQ_ACTIVE_INST_ANY": 69003973,
+        "SQ_WAIT_ANY": 48486750, "SQ_WAIT_INST_ANY": 32833436, "FETCH_SIZE": 48.0,
+        "WRITE_SIZE": 640.0},
     ("tabu_n64", (256, 4, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 45537724, "SQ_INSTS_SALU": 33121501,
-        "SQ_INSTS_LDS": 13721600, "SQ_LDS_BANK_CONFLICT": 2847176,
-        "SQ_LDS_IDX_ACTIVE": 47100360, "GRBM_GUI_ACTIVE": 2565526, "SQ_WAVE_CYCLES": 245254690,
-        "SQ_ACTIVE_INST_ANY": 100531017, "SQ_WAIT_ANY": 85030196, "SQ_WAIT_INST_ANY": 59846120,
-        "FETCH_SIZE": 84.3, "WRITE_SIZE": 576.0},
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31578592, "SQ_INSTS_SALU": 20863970,
+        "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
+        "GRBM_GUI_ACTIVE": 1648837, "SQ_WAVE_CYCLES": 151491919, "SQ_ACTIVE_INST_ANY": 69003655,
+        "SQ_WAIT_ANY": 49673542, "SQ_WAIT_INST_ANY": 32820658, "FETCH_SIZE": 50.5,
+        "WRITE_SIZE": 576.0},
     ("tabu_uneven", (64, 1, 0, 0, 0)): {
-        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 238153444, "SQ_INSTS_SALU": 107004426,
-        "SQ_INSTS_LDS": 65717792, "SQ_LDS_BANK_CONFLICT": 35697887,
-        "SQ_LDS_IDX_ACTIVE": 263385095, "GRBM_GUI_ACTIVE": 10981097,
-        "SQ_WAVE_CYCLES": 1235198368, "SQ_ACTIVE_INST_ANY": 427094313, "SQ_WAIT_ANY": 286088155,
-        "SQ_WAIT_INST_ANY": 522007640, "FETCH_SIZE": 649.8, "WRITE_SIZE": 1361.1},
-    ("tabu_uneven", (128, 2, 0, 0, 0)): {
-        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 238981029, "SQ_INSTS_SALU": 107045386,
-        "SQ_INSTS_LDS": 65717792, "SQ_LDS_BANK_CONFLICT": 35697887,
-        "SQ_LDS_IDX_ACTIVE": 263385095, "GRBM_GUI_ACTIVE": 12292234,
-        "SQ_WAVE_CYCLES": 1042541253, "SQ_ACTIVE_INST_ANY": 427827244, "SQ_WAIT_ANY": 249638089,
-        "SQ_WAIT_INST_ANY": 365200678, "FETCH_SIZE": 652.3, "WRITE_SIZE": 1357.5},
-    ("tabu_n120", (64, 1, 0, 0, 1)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 215952677, "SQ_INSTS_SALU": 116891741,
-        "SQ_INSTS_LDS": 67190784, "SQ_LDS_BANK_CONFLICT": 12524579,
-        "SQ_LDS_IDX_ACTIVE": 241409059, "GRBM_GUI_ACTIVE": 14282818,
-        "SQ_WAVE_CYCLES": 800668253, "SQ_ACTIVE_INST_ANY": 421353424, "SQ_WAIT_ANY": 213610749,
-        "SQ_WAIT_INST_ANY": 165679612, "FETCH_SIZE": 221.8, "WRITE_SIZE": 768.0},
+        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 93247140, "SQ_INSTS_SALU": 51172673,
+        "SQ_INSTS_LDS": 23525700, "SQ_LDS_BANK_CONFLICT": 21636, "SQ_LDS_IDX_ACTIVE": 51014776,
+        "GRBM_GUI_ACTIVE": 3575165, "SQ_WAVE_CYCLES": 521136133, "SQ_ACTIVE_INST_ANY": 195564866,
+        "SQ_WAIT_ANY": 128550870, "SQ_WAIT_INST_ANY": 196881081, "FETCH_SIZE": 351.1,
+        "WRITE_SIZE": 1361.1},
+    ("tabu_uneven", (256, 4, 0, 0, 0)): {
+        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 93322433, "SQ_INSTS_SALU": 51231634,
+        "SQ_INSTS_LDS": 23525700, "SQ_LDS_BANK_CONFLICT": 21636, "SQ_LDS_IDX_ACTIVE": 51014776,
+        "GRBM_GUI_ACTIVE": 3648897, "SQ_WAVE_CYCLES": 522707209, "SQ_ACTIVE_INST_ANY": 195699734,
+        "SQ_WAIT_ANY": 129530818, "SQ_WAIT_INST_ANY": 197563049, "FETCH_SIZE": 355.9,
+        "WRITE_SIZE": 1354.7},
     ("tabu_n120", (64, 1, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 283060663, "SQ_INSTS_SALU": 107530772,
-        "SQ_INSTS_LDS": 80859136, "SQ_LDS_BANK_CONFLICT": 17711104,
-        "SQ_LDS_IDX_ACTIVE": 305389568, "GRBM_GUI_ACTIVE": 13829119,
-        "SQ_WAVE_CYCLES": 1335726845, "SQ_ACTIVE_INST_ANY": 486242331, "SQ_WAIT_ANY": 371388113,
-        "SQ_WAIT_INST_ANY": 478146242, "FETCH_SIZE": 72.8, "WRITE_SIZE": 768.0},
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 90939913, "SQ_INSTS_SALU": 49841274,
+        "SQ_INSTS_LDS": 23842816, "SQ_LDS_BANK_CONFLICT": 16384, "SQ_LDS_IDX_ACTIVE": 51970048,
+        "GRBM_GUI_ACTIVE": 4242659, "SQ_WAVE_CYCLES": 413505933, "SQ_ACTIVE_INST_ANY": 191675260,
+        "SQ_WAIT_ANY": 125628008, "SQ_WAIT_INST_ANY": 96049336, "FETCH_SIZE": 70.5,
+        "WRITE_SIZE": 768.0},
+    ("tabu_n120", (256, 4, 0, 0, 0)): {
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 90984969, "SQ_INSTS_SALU": 49869946,
+        "SQ_INSTS_LDS": 23842816, "SQ_LDS_BANK_CONFLICT": 16384, "SQ_LDS_IDX_ACTIVE": 51970048,
+        "GRBM_GUI_ACTIVE": 4208174, "SQ_WAVE_CYCLES": 414646081, "SQ_ACTIVE_INST_ANY": 191748116,
+        "SQ_WAIT_ANY": 125999927, "SQ_WAIT_INST_ANY": 96591758, "FETCH_SIZE": 77.0,
+        "WRITE_SIZE": 576.0},
     ("tabu_n32", (64, 2, 0, 0, 0)): {
-        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 65617920, "SQ_INSTS_SALU": 11116544,
-        "SQ_INSTS_LDS": 11632640, "SQ_LDS_BANK_CONFLICT": 3187117,
-        "SQ_LDS_IDX_ACTIVE": 39068077, "GRBM_GUI_ACTIVE": 2257454, "SQ_WAVE_CYCLES": 347045904,
-        "SQ_ACTIVE_INST_ANY": 99851470, "SQ_WAIT_ANY": 79889195, "SQ_WAIT_INST_ANY": 167204589,
-        "FETCH_SIZE": 66.1, "WRITE_SIZE": 2560.0},
-    ("tabu_n32", (128, 4, 0, 0, 0)): {
-        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 65658880, "SQ_INSTS_SALU": 11124736,
-        "SQ_INSTS_LDS": 11632640, "SQ_LDS_BANK_CONFLICT": 3187117,
-        "SQ_LDS_IDX_ACTIVE": 39068077, "GRBM_GUI_ACTIVE": 2248578, "SQ_WAVE_CYCLES": 351115208,
-        "SQ_ACTIVE_INST_ANY": 99899866, "SQ_WAIT_ANY": 84375146, "SQ_WAIT_INST_ANY": 166874530,
-        "FETCH_SIZE": 66.4, "WRITE_SIZE": 2304.0},
-    ("tabu_n32", (64, 4, 0, 0, 0)): {
-        "SQ_WAVES": 8192, "SQ_INSTS_VALU": 65617920, "SQ_INSTS_SALU": 11116544,
-        "SQ_INSTS_LDS": 11632640, "SQ_LDS_BANK_CONFLICT": 3187117,
-        "SQ_LDS_IDX_ACTIVE": 39068077, "GRBM_GUI_ACTIVE": 2251066, "SQ_WAVE_CYCLES": 347053631,
-        "SQ_ACTIVE_INST_ANY": 99853791, "SQ_WAIT_ANY": 80004182, "SQ_WAIT_INST_ANY": 167201910,
-        "FETCH_SIZE": 66.4, "WRITE_SIZE": 2560.0},
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 40871910, "SQ_INSTS_SALU": 8323956,
+        "SQ_INSTS_LDS": 8155136, "SQ_LDS_BANK_CONFLICT": 10160502, "SQ_LDS_IDX_ACTIVE": 29722998,
+        "GRBM_GUI_ACTIVE": 1645531, "SQ_WAVE_CYCLES": 144418777, "SQ_ACTIVE_INST_ANY": 63861970,
+        "SQ_WAIT_ANY": 39751106, "SQ_WAIT_INST_ANY": 40811073, "FETCH_SIZE": 76.0,
+        "WRITE_SIZE": 2304.0},
     ("tabu_n256", (256, 4, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 2027584427, "SQ_INSTS_SALU": 381779144,
-        "SQ_INSTS_LDS": 541691904, "SQ_LDS_BANK_CONFLICT": 4194304,
-        "SQ_LDS_IDX_ACTIVE": 2027626496, "GRBM_GUI_ACTIVE": 105383441,
-        "SQ_WAVE_CYCLES": 5970235536, "SQ_ACTIVE_INST_ANY": 3033241847,
-        "SQ_WAIT_ANY": 1285363394, "SQ_WAIT_INST_ANY": 1651510685, "FETCH_SIZE": 178.8,
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 305432921, "SQ_INSTS_SALU": 148342219,
+        "SQ_INSTS_LDS": 93036544, "SQ_LDS_BANK_CONFLICT": 32768, "SQ_LDS_IDX_ACTIVE": 212467712,
+        "GRBM_GUI_ACTIVE": 13888063, "SQ_WAVE_CYCLES": 1375209870, "SQ_ACTIVE_INST_ANY": 627152556,
+        "SQ_WAIT_ANY": 369234765, "SQ_WAIT_INST_ANY": 379065075, "FETCH_SIZE": 106.5,
         "WRITE_SIZE": 1088.0},
     ("tabu_long_uneven", (256, 4, 0, 0, 0)): {
-        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 1391622528, "SQ_INSTS_SALU": 281735379,
-        "SQ_INSTS_LDS": 368409501, "SQ_LDS_BANK_CONFLICT": 114441374,
-        "SQ_LDS_IDX_ACTIVE": 1480472504, "GRBM_GUI_ACTIVE": 73559732,
-        "SQ_WAVE_CYCLES": 4305539543, "SQ_ACTIVE_INST_ANY": 2100988348,
-        "SQ_WAIT_ANY": 989369525, "SQ_WAIT_INST_ANY": 1215187811, "FETCH_SIZE": 451.0,
+        "SQ_WAVES": 4096, "SQ_INSTS_VALU": 213752207, "SQ_INSTS_SALU": 104315526,
+        "SQ_INSTS_LDS": 63122415, "SQ_LDS_BANK_CONFLICT": 24502, "SQ_LDS_IDX_ACTIVE": 143331822,
+        "GRBM_GUI_ACTIVE": 8947884, "SQ_WAVE_CYCLES": 989140507, "SQ_ACTIVE_INST_ANY": 436731828,
+        "SQ_WAIT_ANY": 254018779, "SQ_WAIT_INST_ANY": 298325148, "FETCH_SIZE": 298.2,
         "WRITE_SIZE": 1184.9},
 }
 
@@ -174,11 +166,6 @@ def host_cpu() -> dict:
     return {"nproc": os.cpu_count(), "affinity": len(os.sched_getaffinity(0)), "model": model}
 
 
-def lag_terms_per_step(n: int) -> int:
-    """Sum over neighbours j of L_j = max(N-j, j-1) (1-based): floor((3N^2-2N)/4)."""
-    return sum(max(n - j, j - 1) for j in range(1, n + 1))
-
-
 # ---------------------------------------------------------------------------
 # Batched walks (the headline number)
 # ---------------------------------------------------------------------------
@@ -188,7 +175,8 @@ def tabu_section(args, lb, wl, peaks=None):
     W = wl.walks
     steps_per_walk = ns.astype(np.int64) * wl.rules.steps_a
     evals_per_step = int(np.sum(steps_per_walk * ns))
-    ops_per_launch = 3 * int(sum(int(s) * lag_terms_per_step(int(n)) for s, n in zip(steps_per_walk, ns)))
+    ops_per_launch = OPS_PER_EVAL * evals_per_step
+    lds_per_launch = LDS_BYTES_PER_EVAL * evals_per_step
 
     dev = torch.device("cuda", 0)
     out = (torch.empty((W, max(128, int(ns.max()))), dtype=torch.int8, device=dev),
@@ -250,40 +238,32 @@ def tabu_section(args, lb, wl, peaks=None):
     achieved = ops_per_launch / (kernel_ms * 1e-3)
     launch = lb.get_launch(int(ns.min()), int(ns.max()))
 
-    lag_terms = ops_per_launch // 3
     roof = {
         "bound": "alu",
         "achieved": achieved / 1e12,
-        "peak": PEAK_DOT4_OPS / 1e12,
-        "unit": "Top/s (3 integer ops per lag term; peak: v_dot4_i32_i8, 4 int8 products "
-                "per lane per clock)",
-        "frac": achieved / PEAK_DOT4_OPS,
+        "peak": PEAK_INT32_OPS / 1e12,
+        "unit": "Top/s (10 int32 operations per flip-neighbour evaluation; peak: one per lane "
+                "per clock)",
+        "frac": achieved / PEAK_INT32_OPS,
         "traffic": None,
         "kernel": "tabu_kernel",
         "kernel_ms": kernel_ms,
         "algorithmic_ops_per_launch": ops_per_launch,
-        # the same work against one int32 operation per lane per clock: above
-        # 1 it shows the reduction of work by the packed int8 products, it is
-        # not a fraction of any peak
-        "work_vs_int32_issue": achieved / PEAK_INT32_OPS,
         "lds": {
-            # algorithmic LDS bytes: two spins and C_k as int8 per lag term;
-            # the lag form reads one byte of its row per lag term and C_k as
-            # a broadcast, so the hardware figure (hardware.lds_busy_frac, from
-            # counters) is the measured one
-            "algorithmic_bytes_per_launch": 3 * lag_terms,
-            "achieved": 3 * lag_terms / (kernel_ms * 1e-3) / 1e12,
+            "algorithmic_bytes_per_launch": lds_per_launch,
+            "achieved": lds_per_launch / (kernel_ms * 1e-3) / 1e12,
             "peak": PEAK_LDS_BYTES / 1e12,
             "unit": "TB/s",
-            "frac": 3 * lag_terms / (kernel_ms * 1e-3) / PEAK_LDS_BYTES,
+            "frac": lds_per_launch / (kernel_ms * 1e-3) / PEAK_LDS_BYTES,
         },
     }
     if peaks is not None:
-        roof["measured_peak"] = peaks["dot4_ops_per_s"] / 1e12
-        roof["frac_of_measured_peak"] = achieved / peaks["dot4_ops_per_s"]
+        roof["measured_peak"] = peaks["int32_ops_per_s"] / 1e12
+        roof["frac_of_measured_peak"] = achieved / peaks["int32_ops_per_s"]
         roof["clock_hz_under_load"] = peaks["clock_hz"]
         roof["lds"]["measured_peak"] = peaks["lds_bytes_per_s"] / 1e12
-        roof["lds"]["frac_of_measured_peak"] = 3 * lag_terms / (kernel_ms * 1e-3) / peaks["lds_bytes_per_s"]
+        roof["lds"]["frac_of_measured_peak"] = (lds_per_launch / (kernel_ms * 1e-3)
+                                                / peaks["lds_bytes_per_s"])
     digest = kernel_digest()
     c = COUNTERS.get((wl.name, tuple(launch)))
     if c is not None and COUNTERS_DIGEST == digest:

@@ -221,9 +221,9 @@ struct BruteParts {
 int64_t brute_waves(int n);
 hipError_t launch_bruteforce(int n, const BruteParts &p, hipStream_t s);
 // The same by branch and bound, from kSearchMinN on (a call: n = 23 69 us by
-// enumeration; n = 24 82 us, by search 72; n = 25 138 and 72): `walk_e` holds the energies that `walks` walks reached, whose
-// least bounds the search from above; `queue` takes search_queue_bytes(),
-// `bound` one word.
+// enumeration; n = 24 82 us, by search 72; n = 25 138 and 72): `walk_e` holds
+// the energies that `walks` walks reached, whose least bounds the search from
+// above; `queue` takes search_queue_bytes(), `bound` one word.
 constexpr int kSearchMinN = 24;
 int64_t search_waves();
 size_t search_queue_bytes();

@@ -495,6 +495,8 @@ int memetic_waves(const MemeticLaunchArgs &a) {
 
 template <int NW>
 hipError_t launch_memetic_nw(const MemeticLaunchArgs &a, hipStream_t s) {
+    static_assert(sizeof(ReplicaLds<NW>) + kMaxMemeticWaves * WalkLds<NW>::BYTES <= 65536,
+                  "dynamic LDS within the default limit");
     const int w = memetic_waves<NW>(a);
     hipLaunchKernelGGL(memetic_advance_kernel<NW>, dim3((unsigned)a.n_slots), dim3(64 * w),
                        sizeof(ReplicaLds<NW>) + (size_t)w * WalkLds<NW>::BYTES, s, a);

@@ -234,7 +234,8 @@ __device__ __forceinline__ void set_moved_v(uint64_t at, uint32_t za, int d_new,
 }
 
 // Walks at processing-order positions pos0 .. pos0 + 3 (those below `end`),
-// all of N <= 16 NL, on one wavefront; `lds` holds four walks' tables.  Results as the one-walk-per-wavefront form writes them.
+// all of N <= 16 NL, on one wavefront; `lds` holds four walks' tables.
+// Results as the one-walk-per-wavefront form writes them.
 template <int NL, bool TRACE>
 __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t end,
                                 uint8_t *lds_wave) {
