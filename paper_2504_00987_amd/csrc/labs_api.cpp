@@ -241,6 +241,7 @@ WalkLaunch walk_launch(const labs_handle *h, const labs_launch &l) {
     w.groups = l.persistent
                    ? cus * (l.groups_per_cu > 0 ? l.groups_per_cu : std::max(1, 8 / w.waves_per_group))
                    : 0;
+    w.ahead_from = 8 * (int64_t)cus;
     return w;
 }
 

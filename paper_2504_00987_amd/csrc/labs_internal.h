@@ -134,6 +134,7 @@ struct WalkLaunch {
     int waves_per_group;  // wavefronts per workgroup
     int lanes;            // walks of N <= 32: 64 (one per wavefront), 32 or 16 (walk_launch_groups)
     int groups;           // persistent grid (0: none)
+    int64_t ahead_from;   // walks of two wavefronts per SIMD
 };
 
 // Words of a sequence mask in the memetic state (N <= 256).

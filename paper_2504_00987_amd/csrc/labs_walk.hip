@@ -161,13 +161,13 @@ __device__ __forceinline__ uint32_t length_draw(const RuleParams &r, uint32_t k0
 }
 
 // One walk on one wavefront, NW neighbours per lane.
-template <int NW, bool TRACE>
+template <int NW, bool TRACE, bool AHEAD>
 __device__ void run_tabu_item(const TabuLaunchArgs &a, int64_t w, int N, uint8_t *lds) {
     const int lane = lane_id();
     const auto M = walk_start<NW>(a, w, N);
     const Schedule sch = make_schedule(a.rule, N, length_draw(a.rule, a.k0, a.k1, (uint32_t)w));
     const WalkResult<NW> r =
-        tabu_walk<NW, TRACE>(N, M, sch, a.rule.aspiration, a.k0, a.k1, (uint32_t)w, 0u, lds,
+        tabu_walk<NW, TRACE, AHEAD>(N, M, sch, a.rule.aspiration, a.k0, a.k1, (uint32_t)w, 0u, lds,
                              TRACE ? a.trace + w * (int64_t)a.trace_stride : nullptr);
     int8_t *out = a.best_seq + w * (int64_t)a.out_stride;
     for (int i = lane; i < a.out_stride; i += 64)
@@ -467,26 +467,27 @@ __global__ __launch_bounds__(64 * WAVES) void tabu_kernel_group(TabuLaunchArgs a
 
 // The walk at one position of the processing order, of N <= 64 NWMAX, on the
 // fewest neighbours per lane that hold it.
-template <int NWMAX, bool TRACE>
+template <int NWMAX, bool TRACE, bool AHEAD>
 __device__ __forceinline__ void run_position(const TabuLaunchArgs &a, int64_t pos, uint8_t *lds) {
     const int64_t w = a.order ? (int64_t)a.order[pos] : pos;
     const int N = __builtin_amdgcn_readfirstlane(a.ns ? a.ns[w] : a.n_uniform);
     if (NWMAX >= 4 && N > 192)
-        run_tabu_item<NWMAX >= 4 ? 4 : 1, TRACE>(a, w, N, lds);
+        run_tabu_item<NWMAX >= 4 ? 4 : 1, TRACE, AHEAD>(a, w, N, lds);
     else if (NWMAX >= 4 && N > 128)
-        run_tabu_item<NWMAX >= 4 ? 3 : 1, TRACE>(a, w, N, lds);
+        run_tabu_item<NWMAX >= 4 ? 3 : 1, TRACE, AHEAD>(a, w, N, lds);
     else if (NWMAX >= 2 && N > 64)
-        run_tabu_item<NWMAX >= 2 ? 2 : 1, TRACE>(a, w, N, lds);
+        run_tabu_item<NWMAX >= 2 ? 2 : 1, TRACE, AHEAD>(a, w, N, lds);
     else
-        run_tabu_item<1, TRACE>(a, w, N, lds);
+        run_tabu_item<1, TRACE, AHEAD>(a, w, N, lds);
 }
 
 // Walks of N <= 64 NWMAX at positions [begin, end) of the processing order,
 // one per wavefront.  PERSIST: a grid sized to the device drains the range
 // through the queue head `counter`; otherwise one wavefront per position.
 // TRACE: record every walk's moves (a separate instantiation, so that the
-// untraced kernel does not carry the registers of the traced one).
-template <int NWMAX, int WPG, bool PERSIST, bool TRACE>
+// untraced kernel does not carry the registers of the traced one).  AHEAD: as
+// in tabu_walk (untraced grids).
+template <int NWMAX, int WPG, bool PERSIST, bool TRACE, bool AHEAD>
 __global__ __launch_bounds__(64 * WPG) void tabu_kernel(TabuLaunchArgs a, int64_t begin,
                                                         int64_t end, uint32_t *counter) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[WPG][WalkLds<NWMAX>::BYTES];
@@ -495,10 +496,10 @@ __global__ __launch_bounds__(64 * WPG) void tabu_kernel(TabuLaunchArgs a, int64_
     if constexpr (PERSIST) {
         for (int64_t pos = begin + next_work(counter); pos < end;
              pos = begin + next_work(counter))
-            run_position<NWMAX, TRACE>(a, pos, lds);
+            run_position<NWMAX, TRACE, AHEAD>(a, pos, lds);
     } else {
         const int64_t pos = begin + (int64_t)blockIdx.x * WPG + wave;
-        if (pos < end) run_position<NWMAX, TRACE>(a, pos, lds);
+        if (pos < end) run_position<NWMAX, TRACE, AHEAD>(a, pos, lds);
     }
 }
 
@@ -601,19 +602,19 @@ hipError_t launch_energy(const int8_t *seqs, const int32_t *ns, int32_t n_unifor
 
 namespace {
 
-template <int NWMAX, int WPG, bool TRACE>
+template <int NWMAX, int WPG, bool TRACE, bool AHEAD>
 hipError_t launch_wave_t(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
                          uint32_t *counter, hipStream_t s) {
     if (groups > 0) {
         hipError_t e = launch_fill_u32(counter, 0u, 1, s);
         if (e != hipSuccess) return e;
         const int64_t need = (end - begin + WPG - 1) / WPG;
-        hipLaunchKernelGGL((tabu_kernel<NWMAX, WPG, true, TRACE>),
+        hipLaunchKernelGGL((tabu_kernel<NWMAX, WPG, true, TRACE, false>),
                            dim3((unsigned)std::min<int64_t>(groups, need)), dim3(64 * WPG), 0, s, a,
                            begin, end, counter);
     } else {
         return launch_in_ranges(begin, end, WPG, 64 * WPG, [&](int64_t b, int64_t e, unsigned grid) {
-            hipLaunchKernelGGL((tabu_kernel<NWMAX, WPG, false, TRACE>), dim3(grid), dim3(64 * WPG),
+            hipLaunchKernelGGL((tabu_kernel<NWMAX, WPG, false, TRACE, AHEAD>), dim3(grid), dim3(64 * WPG),
                                0, s, a, b, e, counter);
         });
     }
@@ -622,10 +623,19 @@ hipError_t launch_wave_t(const TabuLaunchArgs &a, int64_t begin, int64_t end, in
 
 template <int NWMAX, int WPG>
 hipError_t launch_wave(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
-                       uint32_t *counter, hipStream_t s) {
+                       int64_t ahead_from, uint32_t *counter, hipStream_t s) {
     if (end <= begin) return hipSuccess;
-    return a.trace != nullptr ? launch_wave_t<NWMAX, WPG, true>(a, begin, end, groups, counter, s)
-                              : launch_wave_t<NWMAX, WPG, false>(a, begin, end, groups, counter, s);
+    if (a.trace != nullptr)
+        return launch_wave_t<NWMAX, WPG, true, false>(a, begin, end, groups, counter, s);
+    // Walks of one length from two wavefronts per SIMD on issue ahead of each
+    // other (a call, without -> with): 4096 walks of N = 64 81.6 -> 77.2 us,
+    // of N = 120 214 -> 200.  64 walks 30.7 -> 30.95; of mixed lengths, where
+    // the shorter walks' steps crowd out those of the longer ones that
+    // finish last, 8192 of N in 48..120 199 -> 216 and 4096 of N in 129..256
+    // 492 -> 519.
+    if (groups == 0 && a.ns == nullptr && end - begin >= ahead_from)
+        return launch_wave_t<NWMAX, WPG, false, true>(a, begin, end, 0, counter, s);
+    return launch_wave_t<NWMAX, WPG, false, false>(a, begin, end, groups, counter, s);
 }
 
 template <int NL, int WAVES, bool TRACE>
@@ -678,11 +688,11 @@ hipError_t launch_tabu_wpg(const TabuLaunchArgs &a, const WalkLaunch &l, const h
         else if (kind == kKindGroup4)
             e = launch_group<1, WPG>(a, begin, end, l.groups, q, st[g]);
         else if (kClassMaxN[f] <= 64)
-            e = launch_wave<1, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_wave<1, WPG>(a, begin, end, l.groups, l.ahead_from, q, st[g]);
         else if (kClassMaxN[f] <= 128)
-            e = launch_wave<2, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_wave<2, WPG>(a, begin, end, l.groups, l.ahead_from, q, st[g]);
         else
-            e = launch_wave<4, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_wave<4, WPG>(a, begin, end, l.groups, l.ahead_from, q, st[g]);
     }
     return e;
 }
