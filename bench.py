@@ -71,67 +71,67 @@ KERNEL_SOURCES = ("paper_2504_00987_amd/csrc/labs_device.hpp",
 COPY_SCALE = {"FETCH_SIZE": 262144 / 131086, "WRITE_SIZE": 262144 / 262144}
 XCDS = 8
 COUNTERS_SOURCE = "profiles/tabu_kernel_counters.md"
-COUNTERS_DIGEST = "90289fc2985257a5"
+COUNTERS_DIGEST = "739c8bc2fa683bbe"
 COUNTERS = {
     ("tabu_n64", (64, 1, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31554016, "SQ_INSTS_SALU": 20843490,
         "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
-        "GRBM_GUI_ACTIVE": 1664244, "SQ_WAVE_CYCLES": 153963744, "SQ_ACTIVE_INST_ANY": 68958587,
-        "SQ_WAIT_ANY": 53984223, "SQ_WAIT_INST_ANY": 31291025, "FETCH_SIZE": 48.5,
+        "GRBM_GUI_ACTIVE": 1553358, "SQ_WAVE_CYCLES": 157577464, "SQ_ACTIVE_INST_ANY": 68958303,
+        "SQ_WAIT_ANY": 55282645, "SQ_WAIT_INST_ANY": 33328039, "FETCH_SIZE": 51.5,
         "WRITE_SIZE": 768.0},
     ("tabu_n64", (128, 2, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31578592, "SQ_INSTS_SALU": 20863970,
         "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
-        "GRBM_GUI_ACTIVE": 1649351, "SQ_WAVE_CYCLES": 150494178, "SQ_ACTIVE_INST_ANY": 69003973,
-        "SQ_WAIT_ANY": 48486750, "SQ_WAIT_INST_ANY": 32833436, "FETCH_SIZE": 48.0,
+        "GRBM_GUI_ACTIVE": 1540304, "SQ_WAVE_CYCLES": 154384211, "SQ_ACTIVE_INST_ANY": 69002582,
+        "SQ_WAIT_ANY": 50026491, "SQ_WAIT_INST_ANY": 35452727, "FETCH_SIZE": 48.0,
         "WRITE_SIZE": 640.0},
     ("tabu_n64", (256, 4, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 31578592, "SQ_INSTS_SALU": 20863970,
         "SQ_INSTS_LDS": 7434240, "SQ_LDS_BANK_CONFLICT": 8192, "SQ_LDS_IDX_ACTIVE": 14974976,
-        "GRBM_GUI_ACTIVE": 1648837, "SQ_WAVE_CYCLES": 151491919, "SQ_ACTIVE_INST_ANY": 69003655,
-        "SQ_WAIT_ANY": 49673542, "SQ_WAIT_INST_ANY": 32820658, "FETCH_SIZE": 50.5,
+        "GRBM_GUI_ACTIVE": 1550930, "SQ_WAVE_CYCLES": 155499830, "SQ_ACTIVE_INST_ANY": 69002323,
+        "SQ_WAIT_ANY": 50893697, "SQ_WAIT_INST_ANY": 35583799, "FETCH_SIZE": 48.0,
         "WRITE_SIZE": 576.0},
     ("tabu_uneven", (64, 1, 0, 0, 0)): {
         "SQ_WAVES": 8192, "SQ_INSTS_VALU": 93247140, "SQ_INSTS_SALU": 51172673,
         "SQ_INSTS_LDS": 23525700, "SQ_LDS_BANK_CONFLICT": 21636, "SQ_LDS_IDX_ACTIVE": 51014776,
-        "GRBM_GUI_ACTIVE": 3575165, "SQ_WAVE_CYCLES": 521136133, "SQ_ACTIVE_INST_ANY": 195564866,
-        "SQ_WAIT_ANY": 128550870, "SQ_WAIT_INST_ANY": 196881081, "FETCH_SIZE": 351.1,
+        "GRBM_GUI_ACTIVE": 3586570, "SQ_WAVE_CYCLES": 521386736, "SQ_ACTIVE_INST_ANY": 195568533,
+        "SQ_WAIT_ANY": 128830785, "SQ_WAIT_INST_ANY": 196950627, "FETCH_SIZE": 356.6,
         "WRITE_SIZE": 1361.1},
     ("tabu_uneven", (256, 4, 0, 0, 0)): {
         "SQ_WAVES": 8192, "SQ_INSTS_VALU": 93322433, "SQ_INSTS_SALU": 51231634,
         "SQ_INSTS_LDS": 23525700, "SQ_LDS_BANK_CONFLICT": 21636, "SQ_LDS_IDX_ACTIVE": 51014776,
-        "GRBM_GUI_ACTIVE": 3648897, "SQ_WAVE_CYCLES": 522707209, "SQ_ACTIVE_INST_ANY": 195699734,
-        "SQ_WAIT_ANY": 129530818, "SQ_WAIT_INST_ANY": 197563049, "FETCH_SIZE": 355.9,
+        "GRBM_GUI_ACTIVE": 3647483, "SQ_WAVE_CYCLES": 522272826, "SQ_ACTIVE_INST_ANY": 195700008,
+        "SQ_WAIT_ANY": 128842590, "SQ_WAIT_INST_ANY": 197614734, "FETCH_SIZE": 355.9,
         "WRITE_SIZE": 1354.7},
     ("tabu_n120", (64, 1, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 90939913, "SQ_INSTS_SALU": 49841274,
         "SQ_INSTS_LDS": 23842816, "SQ_LDS_BANK_CONFLICT": 16384, "SQ_LDS_IDX_ACTIVE": 51970048,
-        "GRBM_GUI_ACTIVE": 4242659, "SQ_WAVE_CYCLES": 413505933, "SQ_ACTIVE_INST_ANY": 191675260,
-        "SQ_WAIT_ANY": 125628008, "SQ_WAIT_INST_ANY": 96049336, "FETCH_SIZE": 70.5,
+        "GRBM_GUI_ACTIVE": 3898569, "SQ_WAVE_CYCLES": 421806358, "SQ_ACTIVE_INST_ANY": 191674809,
+        "SQ_WAIT_ANY": 126940014, "SQ_WAIT_INST_ANY": 103058605, "FETCH_SIZE": 69.0,
         "WRITE_SIZE": 768.0},
     ("tabu_n120", (256, 4, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 90984969, "SQ_INSTS_SALU": 49869946,
         "SQ_INSTS_LDS": 23842816, "SQ_LDS_BANK_CONFLICT": 16384, "SQ_LDS_IDX_ACTIVE": 51970048,
-        "GRBM_GUI_ACTIVE": 4208174, "SQ_WAVE_CYCLES": 414646081, "SQ_ACTIVE_INST_ANY": 191748116,
-        "SQ_WAIT_ANY": 125999927, "SQ_WAIT_INST_ANY": 96591758, "FETCH_SIZE": 77.0,
+        "GRBM_GUI_ACTIVE": 3956272, "SQ_WAVE_CYCLES": 423948082, "SQ_ACTIVE_INST_ANY": 191747962,
+        "SQ_WAIT_ANY": 128794488, "SQ_WAIT_INST_ANY": 103415676, "FETCH_SIZE": 77.0,
         "WRITE_SIZE": 576.0},
     ("tabu_n32", (64, 2, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 40871910, "SQ_INSTS_SALU": 8323956,
         "SQ_INSTS_LDS": 8155136, "SQ_LDS_BANK_CONFLICT": 10160502, "SQ_LDS_IDX_ACTIVE": 29722998,
-        "GRBM_GUI_ACTIVE": 1645531, "SQ_WAVE_CYCLES": 144418777, "SQ_ACTIVE_INST_ANY": 63861970,
-        "SQ_WAIT_ANY": 39751106, "SQ_WAIT_INST_ANY": 40811073, "FETCH_SIZE": 76.0,
+        "GRBM_GUI_ACTIVE": 1625881, "SQ_WAVE_CYCLES": 144345812, "SQ_ACTIVE_INST_ANY": 63862966,
+        "SQ_WAIT_ANY": 39596013, "SQ_WAIT_INST_ANY": 40903401, "FETCH_SIZE": 77.0,
         "WRITE_SIZE": 2304.0},
     ("tabu_n256", (256, 4, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 305432921, "SQ_INSTS_SALU": 148342219,
         "SQ_INSTS_LDS": 93036544, "SQ_LDS_BANK_CONFLICT": 32768, "SQ_LDS_IDX_ACTIVE": 212467712,
-        "GRBM_GUI_ACTIVE": 13888063, "SQ_WAVE_CYCLES": 1375209870, "SQ_ACTIVE_INST_ANY": 627152556,
-        "SQ_WAIT_ANY": 369234765, "SQ_WAIT_INST_ANY": 379065075, "FETCH_SIZE": 106.5,
+        "GRBM_GUI_ACTIVE": 13056368, "SQ_WAVE_CYCLES": 1399397793, "SQ_ACTIVE_INST_ANY": 627126903,
+        "SQ_WAIT_ANY": 364493813, "SQ_WAIT_INST_ANY": 407794171, "FETCH_SIZE": 106.5,
         "WRITE_SIZE": 1088.0},
     ("tabu_long_uneven", (256, 4, 0, 0, 0)): {
         "SQ_WAVES": 4096, "SQ_INSTS_VALU": 213752207, "SQ_INSTS_SALU": 104315526,
         "SQ_INSTS_LDS": 63122415, "SQ_LDS_BANK_CONFLICT": 24502, "SQ_LDS_IDX_ACTIVE": 143331822,
-        "GRBM_GUI_ACTIVE": 8947884, "SQ_WAVE_CYCLES": 989140507, "SQ_ACTIVE_INST_ANY": 436731828,
-        "SQ_WAIT_ANY": 254018779, "SQ_WAIT_INST_ANY": 298325148, "FETCH_SIZE": 298.2,
+        "GRBM_GUI_ACTIVE": 8976799, "SQ_WAVE_CYCLES": 989055665, "SQ_ACTIVE_INST_ANY": 436735837,
+        "SQ_WAIT_ANY": 253990936, "SQ_WAIT_INST_ANY": 298399579, "FETCH_SIZE": 291.8,
         "WRITE_SIZE": 1184.9},
 }
 

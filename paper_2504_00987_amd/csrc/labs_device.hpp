@@ -558,8 +558,8 @@ __device__ __forceinline__ void set_moved(uint64_t bit, uint32_t za, int d_new, 
 // entries' new values are stored in the wait states of the minimum.  One
 // wavefront per walk with NW neighbours per lane keeps the chain free of
 // barriers.  Measured (MI355X, a call; recomputing v_j from packed int8
-// products -> this): 4096 walks of N = 64 and 256 steps 131 -> 81 us, of
-// N = 120 and 480 steps 717 -> 214 us, of N in 129..256 3.90 -> 0.49 ms.
+// products -> this): 4096 walks of N = 64 and 256 steps 131 -> 77 us, of
+// N = 120 and 480 steps 717 -> 200 us, of N in 129..256 3.90 -> 0.49 ms.
 //   lds    WalkLds<NW>::BYTES bytes of per-walk scratch, 16-aligned
 //   trace  with TRACE: trace[t-1] = flipped index
 //   AHEAD  the wavefront issues ahead of the others of its SIMD from the

@@ -176,3 +176,20 @@ def test_memetic_wavefront_lines(lb, n, pops):
     assert torch.equal(many.best_seq[:24], few.best_seq)
     ref = _oracle_memetic([n] * 4, 20, rules, 11, 6)
     assert [int(e) for e in many.best_e[:4]] == [st.bestE for st in ref]
+
+
+# batches of one length run with raised issue priority from 2048 walks (two wavefronts per SIMD) on;
+# a batch of two lengths runs without
+@pytest.mark.parametrize("n", [40, 64, 65, 130, 200])
+@pytest.mark.parametrize("walks", [2047, 2048])
+def test_one_length_priority_line(lb, n, walks):
+    rules = I.Rules(I.STEPS_FIXED, 70, I.TENURE_LINEAR, 1, 10, 0, 1, 5, 0, 1)
+    kw = dict(out_stride=256)
+    one = lb.tabu_batch(rules, walks, 17, n_uniform=n, **kw)
+    ns = np.full(walks + 1, n, dtype=np.int32)
+    ns[walks] = n - 1
+    two = lb.tabu_batch(rules, walks + 1, 17, ns=ns, **kw)
+    for a, b in ((one.best_e, two.best_e), (one.final_e, two.final_e), (one.best_seq, two.best_seq)):
+        assert torch.equal(a, b[:walks])
+    assert np.array_equal(one.best_e.cpu().numpy()[:8],
+                          _oracle_walks(8, n, rules, 17, with_trace=False)[1])
