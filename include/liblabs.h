@@ -100,9 +100,9 @@ typedef struct labs_tabu_params {
 /* Launch configuration of the batched walk kernels.  group_lanes /
  * walks_per_group: 64 (one walk per wavefront: {64, 1}, {128, 2}, {256, 4});
  * 32 ({64, 2}, {128, 4}): the walks of N <= 32 run several per wavefront
- * (four, 16 lanes and two neighbours per lane each); 16 ({64, 4}): the same,
- * those of N <= 16 with one neighbour per lane.  A batch's longer walks run
- * one per wavefront.  {128, 1} is accepted and runs as {128, 2}: a walk's
+ * (two of 32 lanes each, or four of 16 in larger batches); 16 ({64, 4}): the
+ * same, those of N <= 16 in a launch of their own, always on 16 lanes.  A
+ * batch's longer walks run one per wavefront.  {128, 1} is accepted and runs as {128, 2}: a walk's
  * step is short enough that no length gains from a second wavefront.
  * {256, 1} and {256, 2} are rejected (LABS_E_INVAL). */
 typedef struct labs_launch {

@@ -242,6 +242,7 @@ WalkLaunch walk_launch(const labs_handle *h, const labs_launch &l) {
                    ? cus * (l.groups_per_cu > 0 ? l.groups_per_cu : std::max(1, 8 / w.waves_per_group))
                    : 0;
     w.ahead_from = 8 * (int64_t)cus;
+    w.pairs_to = (l.persistent ? 8 : 16) * (int64_t)cus;
     return w;
 }
 

@@ -57,7 +57,7 @@ constexpr int kSideStreams = kWalkClasses - 1;
 enum WalkKind : int {
     kKindWave = 0,    // one walk per wavefront
     kKindSplit = 1,   // walks of 64 < N <= 128 apart from the shorter ones
-    kKindGroup2 = 2,  // walks of N <= 32, four per wavefront (16 lanes, two neighbours each)
+    kKindGroup2 = 2,  // walks of N <= 32, two or four per wavefront (group2_form)
     kKindGroup4 = 4,  // walks of N <= 16, four per wavefront (16 lanes, one neighbour each)
 };
 
@@ -129,12 +129,31 @@ inline WalkGroups tabu_launch_groups(const int64_t *class_end, int lanes) {
     return g;
 }
 
+// Lanes per walk and neighbours per lane of the walks of a kKindGroup2 group
+// that begins with length class `first` (one walk of N <= 32 on 16 or 32
+// lanes).  N <= 16 alone fills 16 lanes.  Longer walks take 32 lanes up to
+// `pairs_to` walks, where a step costs its chain of dependent instructions
+// (which the second neighbour lengthens), and 16 lanes beyond, where it costs
+// the instructions issued.  A call of W walks of N = 32 and 128 steps, 16
+// lanes against 32 (MI355X, us): W = 64 64 and 53, 1024 66 and 56, 4096 67 and
+// 61, 6144 74 and 70, 8192 75 and 80, 16384 100 and 118; as a persistent grid
+// 1024 72 and 67, 2048 79 and 73, 3072 83 and 84, 8192 103 and 128.
+struct GroupForm {
+    int lanes, neighbours;
+};
+inline GroupForm group2_form(int first, int64_t walks, int64_t pairs_to) {
+    if (kClassMaxN[first] <= 16) return {16, 1};
+    if (walks <= pairs_to) return {32, 1};
+    return {16, 2};
+}
+
 // How labs_tabu_batch launches its walks.
 struct WalkLaunch {
     int waves_per_group;  // wavefronts per workgroup
     int lanes;            // walks of N <= 32: 64 (one per wavefront), 32 or 16 (walk_launch_groups)
     int groups;           // persistent grid (0: none)
     int64_t ahead_from;   // walks of two wavefronts per SIMD
+    int64_t pairs_to;     // group2_form
 };
 
 // Words of a sequence mask in the memetic state (N <= 256).

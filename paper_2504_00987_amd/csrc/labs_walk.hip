@@ -4,7 +4,7 @@
 //   tabu_kernel     independent tabu walks (Alg. 2 / Alg. 4), one walk per
 //                   wave, either one wave per walk or a persistent grid
 //                   draining a longest-first work queue
-//   tabu_kernel_group  four walks of N <= 32 per wave
+//   tabu_kernel_group  two or four walks of N <= 32 per wave
 //   fill_u32_kernel device-side fill (queue heads, flags), capturable
 //   order_by_length_kernel  longest-first processing order built on the
 //                   device (the allocation-free entry point's lengths)
@@ -179,32 +179,55 @@ __device__ void run_tabu_item(const TabuLaunchArgs &a, int64_t w, int N, uint8_t
 // ---------------------------------------------------------------------------
 // Several walks per wavefront (N <= 32).
 // ---------------------------------------------------------------------------
-// A wavefront runs four walks of N <= 16 NL (NL = 1 or 2) at once, lane l of
-// a group of 16 owning neighbours j = l + 16h, h < NL.  The step is
+// A wavefront runs 64 / GL walks of N <= GL NL (GL = 16 or 32 lanes) at once,
+// lane l of a group of GL owning neighbours j = l + GL h, h < NL.  The step is
 // tabu_walk's, with every per-walk quantity (the sequence mask, the energy,
 // the best, the chosen move, the schedule) held per lane for the lane's own
 // walk instead of in scalar registers, and the minimum taken within each
 // group of lanes.  Walks of different lengths share the step loop; a walk past
 // its last step takes no move.  Bound: VALU on a full device (72 instructions
-// a step of four walks); 16 lanes with two neighbours each share the per-walk
-// work over half the lanes of 32 with one: 16384 walks of N = 32 and 128 steps
-// 104 -> 80 us a call.
-constexpr int kGroupLanes = 16;
+// a step of four walks), where 16 lanes with two neighbours each share the
+// per-walk work over half the lanes of 32 with one; one step's chain of
+// dependent instructions on a part-filled one, where the second neighbour
+// lengthens it (group2_form).  16384 walks of N = 32 and 128 steps on 32 lanes
+// 118 us a call, on 16 100; 64 walks 53 and 64.
 
-// Minimum and sum over each row of 16 lanes by DPP, every lane receiving its
-// row's value.
+// The values of the two 16-lane rows of each half wavefront, in every lane of
+// the half.
+__device__ __forceinline__ void row_pair(int v, int &a, int &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+}
+
+// Minimum and sum over each group of GL lanes, every lane receiving its
+// group's value: rows of 16 by DPP, then two rows.
+template <int GL>
 __device__ __forceinline__ int group_min(int v) {
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_1032, 0xf, 0xf, true));
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_2301, 0xf, 0xf, true));
     v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_HALF_MIRROR, 0xf, 0xf, true));
-    return min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true));
+    v = min(v, __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true));
+    if constexpr (GL == 32) {
+        int a, b;
+        row_pair(v, a, b);
+        v = min(a, b);
+    }
+    return v;
 }
 
+template <int GL>
 __device__ __forceinline__ int group_sum(int v) {
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_1032, 0xf, 0xf, true);
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_QUAD_2301, 0xf, 0xf, true);
     v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_HALF_MIRROR, 0xf, 0xf, true);
-    return v + __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true);
+    v += __builtin_amdgcn_mov_dpp(v, LABS_DPP_ROW_MIRROR, 0xf, 0xf, true);
+    if constexpr (GL == 32) {
+        int a, b;
+        row_pair(v, a, b);
+        v = a + b;
+    }
+    return v;
 }
 
 // |a - b| + c in one instruction, every operand per lane.
@@ -233,14 +256,15 @@ __device__ __forceinline__ void set_moved_v(uint64_t at, uint32_t za, int d_new,
         : "memory", "scc");
 }
 
-// Walks at processing-order positions pos0 .. pos0 + 3 (those below `end`),
-// all of N <= 16 NL, on one wavefront; `lds` holds four walks' tables.
+// Walks at processing-order positions pos0 .. pos0 + 64 / GL - 1 (those below
+// `end`), all of N <= GL NL, on one wavefront; `lds` holds their tables.
 // Results as the one-walk-per-wavefront form writes them.
-template <int NL, bool TRACE>
+template <int GL, int NL, bool TRACE>
 __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t end,
                                 uint8_t *lds_wave) {
-    constexpr int GL = kGroupLanes, SPAN = GL * NL;
-    static_assert(SPAN <= 32, "one-word masks");
+    constexpr int SPAN = GL * NL;
+    static_assert((GL == 16 || GL == 32) && SPAN <= 32, "rows of lanes, one-word masks");
+    constexpr uint32_t kGroupMask = GL == 32 ? ~0u : 0xffffu;
     using L = WalkTables<SPAN>;
     const int lane = lane_id();
     const int g = lane / GL, l = lane % GL;
@@ -261,7 +285,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
 #pragma unroll
         for (int h = 0; h < NL; ++h) {
             const int j = l + GL * h;
-            M |= ((uint32_t)(ballot(j < N && row[j] < 0) >> (GL * g)) & 0xffffu) << (GL * h);
+            M |= ((uint32_t)(ballot(j < N && row[j] < 0) >> (GL * g)) & kGroupMask) << (GL * h);
         }
     } else {
         const Draw4 d = philox10((uint32_t)w, 0u, 0u, kTagStart, a.k0, a.k1);
@@ -295,7 +319,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
         const int x = l + GL * i - SPAN;
         SP[x] = x >= 0 && x < N ? (((M >> x) & 1u) ? (int8_t)-4 : (int8_t)4) : (int8_t)0;
     }
-    const int E0 = group_sum(sq_e);
+    const int E0 = group_sum<GL>(sq_e);
     wave_sync();
 
     // D_j = Q_2j - 1 - s_j v_j, v_j = sum_i s_i C_|i-j|
@@ -356,7 +380,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
             int kmin = key[0];
 #pragma unroll
             for (int h = 1; h < NL; ++h) kmin = min(kmin, key[h]);
-            const int m = group_min(kmin);
+            const int m = group_min<GL>(kmin);
             // ties: the r-th lowest tied neighbour of the group, r from the
             // step's first draw
             uint32_t tied = (uint32_t)(ballot(key[0] == m) >> group_at);
@@ -364,7 +388,7 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
                 tied = __builtin_amdgcn_perm((uint32_t)(ballot(key[1] == m) >> group_at), tied,
                                              0x05040100u);
             else
-                tied &= 0xffffu;
+                tied &= kGroupMask;
             int r = (int)below(dr, (uint32_t)__popc(tied));
             while (r > 0) {  // drop the r lowest
                 tied &= tied - 1u;
@@ -445,23 +469,23 @@ __device__ void run_group_walks(const TabuLaunchArgs &a, int64_t pos0, int64_t e
     }
 }
 
-// Walks of N <= 16 NL at positions [begin, end), four per wavefront and WAVES
-// wavefronts per workgroup.  PERSIST: a grid sized to the device takes four
+// Walks of N <= GL NL at positions [begin, end), G = 64 / GL per wavefront and
+// WAVES wavefronts per workgroup.  PERSIST: a grid sized to the device takes G
 // positions at a time from the queue head `counter`; otherwise one wavefront
-// per four positions.
-template <int NL, int WAVES, bool PERSIST, bool TRACE>
+// per G positions.
+template <int GL, int NL, int WAVES, bool PERSIST, bool TRACE>
 __global__ __launch_bounds__(64 * WAVES) void tabu_kernel_group(TabuLaunchArgs a, int64_t begin,
                                                                 int64_t end, uint32_t *counter) {
-    constexpr int G = 64 / kGroupLanes;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES][G * WalkTables<kGroupLanes * NL>::BYTES];
+    constexpr int G = 64 / GL;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES][G * WalkTables<GL * NL>::BYTES];
     uint8_t *lds = lds_all[threadIdx.x >> 6];
     if constexpr (PERSIST) {
         for (int64_t pos = begin + next_work(counter, G); pos < end;
              pos = begin + next_work(counter, G))
-            run_group_walks<NL, TRACE>(a, pos, end, lds);
+            run_group_walks<GL, NL, TRACE>(a, pos, end, lds);
     } else {
         const int64_t pos = begin + ((int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6)) * G;
-        if (pos < end) run_group_walks<NL, TRACE>(a, pos, end, lds);
+        if (pos < end) run_group_walks<GL, NL, TRACE>(a, pos, end, lds);
     }
 }
 
@@ -638,28 +662,28 @@ hipError_t launch_wave(const TabuLaunchArgs &a, int64_t begin, int64_t end, int 
     return launch_wave_t<NWMAX, WPG, false, false>(a, begin, end, groups, counter, s);
 }
 
-template <int NL, int WAVES, bool TRACE>
+template <int GL, int NL, int WAVES, bool TRACE>
 hipError_t launch_group_t(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
                           uint32_t *counter, hipStream_t s) {
-    constexpr int G = 64 / kGroupLanes;
+    constexpr int G = 64 / GL;
     const int64_t need = (end - begin + G * WAVES - 1) / (G * WAVES);
     if (groups > 0) {
         hipError_t e = launch_fill_u32(counter, 0u, 1, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((tabu_kernel_group<NL, WAVES, true, TRACE>),
+        hipLaunchKernelGGL((tabu_kernel_group<GL, NL, WAVES, true, TRACE>),
                            dim3((unsigned)std::min<int64_t>(groups, need)), dim3(64 * WAVES), 0, s,
                            a, begin, end, counter);
     } else {
         return launch_in_ranges(begin, end, G * WAVES, 64 * WAVES,
                                 [&](int64_t b, int64_t e, unsigned grid) {
-            hipLaunchKernelGGL((tabu_kernel_group<NL, WAVES, false, TRACE>), dim3(grid),
+            hipLaunchKernelGGL((tabu_kernel_group<GL, NL, WAVES, false, TRACE>), dim3(grid),
                                dim3(64 * WAVES), 0, s, a, b, e, counter);
         });
     }
     return hipGetLastError();
 }
 
-template <int NL, int WAVES>
+template <int GL, int NL, int WAVES>
 hipError_t launch_group(const TabuLaunchArgs &a, int64_t begin, int64_t end, int groups,
                         uint32_t *counter, hipStream_t s) {
     if (end <= begin) return hipSuccess;
@@ -667,9 +691,18 @@ hipError_t launch_group(const TabuLaunchArgs &a, int64_t begin, int64_t end, int
         return hipErrorInvalidValue;  // several walks per wavefront: 64- or 128-lane workgroups
     } else {
         return a.trace != nullptr
-                   ? launch_group_t<NL, WAVES, true>(a, begin, end, groups, counter, s)
-                   : launch_group_t<NL, WAVES, false>(a, begin, end, groups, counter, s);
+                   ? launch_group_t<GL, NL, WAVES, true>(a, begin, end, groups, counter, s)
+                   : launch_group_t<GL, NL, WAVES, false>(a, begin, end, groups, counter, s);
     }
+}
+
+template <int WAVES>
+hipError_t launch_group2(const TabuLaunchArgs &a, int first, int64_t begin, int64_t end, int groups,
+                         int64_t pairs_to, uint32_t *counter, hipStream_t s) {
+    const GroupForm f = group2_form(first, end - begin, pairs_to);
+    if (f.lanes == 32) return launch_group<32, 1, WAVES>(a, begin, end, groups, counter, s);
+    if (f.neighbours == 1) return launch_group<16, 1, WAVES>(a, begin, end, groups, counter, s);
+    return launch_group<16, 2, WAVES>(a, begin, end, groups, counter, s);
 }
 
 // One launch per launch group, group g on streams[g] with the queue head of
@@ -684,9 +717,9 @@ hipError_t launch_tabu_wpg(const TabuLaunchArgs &a, const WalkLaunch &l, const h
         const int64_t begin = f ? ce[f - 1] : 0, end = ce[wg.last[g]];
         uint32_t *q = a.counter + 32 * f;
         if (kind == kKindGroup2)
-            e = launch_group<2, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_group2<WPG>(a, f, begin, end, l.groups, l.pairs_to, q, st[g]);
         else if (kind == kKindGroup4)
-            e = launch_group<1, WPG>(a, begin, end, l.groups, q, st[g]);
+            e = launch_group<16, 1, WPG>(a, begin, end, l.groups, q, st[g]);
         else if (kClassMaxN[f] <= 64)
             e = launch_wave<1, WPG>(a, begin, end, l.groups, l.ahead_from, q, st[g]);
         else if (kClassMaxN[f] <= 128)

@@ -1,0 +1,54 @@
+"""GPU kernels on both sides of the lines where the library picks another form
+of a launch, against the CPU oracle.  Every result is a whole number:
+equality."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2504_00987_amd import inputs as I
+from tests.test_gpu_parity import _oracle_memetic, _oracle_walks
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lb():
+    from paper_2504_00987_amd.labs import Labs
+    h = Labs(0)
+    yield h
+    h.close()
+
+
+def _cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+# walks of N <= 32: two per wavefront up to 16 (as a persistent grid 8) walks per compute unit, four
+# beyond, the last wavefront partly idle; lengths at the edges of the lanes and mixed ones
+@pytest.mark.parametrize("lengths", [(17, 17), (31, 31), (32, 32), (3, 32)])
+@pytest.mark.parametrize("launch,line", [((64, 2), 16), ((128, 4), 16), ((64, 2, 1), 8),
+                                         ((64, 4), 16)])
+@pytest.mark.parametrize("aspiration", [0, 1])
+def test_short_walk_forms(lb, launch, line, lengths, aspiration):
+    rules = I.Rules(I.STEPS_MULT_N, 2, I.TENURE_LINEAR, 1, 10, 0, 1, 5, 0, aspiration)
+    lo, hi = lengths
+    for walks in (1, 3, line * _cus(), line * _cus() + 1, line * _cus() + 3):
+        ns = None if lo == hi else I.uneven_lengths(walks, lo, hi, seed=walks)
+        kw = dict(ns=ns, n_uniform=hi if lo == hi else 0, out_stride=128, trace_stride=2 * hi)
+        res = {}
+        for form in (launch, (64, 1)):
+            lb.set_launch(*form)
+            try:
+                res[form] = lb.tabu_batch(rules, walks, 23, **kw)
+            finally:
+                lb.set_launch(None)
+        a, b = res.values()
+        for x, y in ((a.best_e, b.best_e), (a.final_e, b.final_e), (a.best_seq, b.best_seq),
+                     (a.trace, b.trace)):
+            assert torch.equal(x, y), walks
+        head = min(walks, 12)
+        best, be, fe, _ = _oracle_walks(head, hi if ns is None else ns, rules, 23, with_trace=False)
+        assert np.array_equal(a.best_e[:head].cpu().numpy(), be[:head])
+        assert np.array_equal(a.best_seq[:head, :best.shape[1]].cpu().numpy(), best[:head])
