@@ -191,6 +191,38 @@ struct SideStreams {
     hipEvent_t fork;
 };
 
+// Wavefronts per replica of a launch, for `words` mask words (1 << memetic_class).
+//
+// What the device has to spare: twelve up to one replica per compute unit,
+// eight up to eight replicas per compute unit (N <= 128) or two (N > 128,
+// where a wavefront holds more of the LDS and registers), four beyond.  32
+// generations of K = 100 (MI355X, us) on 1, 4, 8 and 12 wavefronts: N = 120
+// 1352, 456, 318 and 294 at 256 replicas, 1390, 544, 426 and 424 at 512, 1615,
+// 946 and 909 (8) at 2048, 3975, 2853 and 3002 (8) at 8192; N = 200 3075, 1017,
+// 716 and 663 at 256, 3209, 1246, 956 and 1237 at 512, 3261, 1492 and 1602 (8)
+// at 1024; N = 33 352, 131, 107 and 91 at 256, 887, 769 and 788 (8) at 8192.
+//
+// What the replica has children for: those of one generation, and the more
+// members the more of the next that wait for none of these.  Wavefronts beyond
+// that hold slots other replicas could run in.  16 generations (us) on 1, 2, 3,
+// 4 and 8 wavefronts, N = 64: K = 2 420, 395, 430, 560 and 817 at 2048
+// replicas, 536, 622, 703, 831 and 1459 at 4096; K = 8 427, 339, 342, 403 and
+// 559 at 2048, 557, 516, 542, 588 and 939 at 4096; K = 32 422, 303, 291, 309
+// and 358 at 2048, 552, 468, 450, 445 and 575 at 4096.  4 generations of 4
+// children, K = 2: 422, 297, 289, 272 and 338 at 2048.
+// And no more than the launch has children.
+constexpr int kMaxMemeticWaves = 12;
+inline int memetic_waves(int words, int64_t replicas, int K, int children, int gens, int cus) {
+    const int64_t some = (int64_t)(words == 4 ? 2 : 8) * cus;
+    const bool spare = replicas <= some;
+    const int device = replicas <= cus ? kMaxMemeticWaves : spare ? 8 : 4;
+    int useful = spare ? 2 + K / 8 : 1 + K / 6;
+    if (children > 1) useful = children + (spare ? K / 8 : K / 6);
+    const int64_t all = (int64_t)gens * children;
+    const int w = device < useful ? device : useful;
+    return (int)(w < all ? w : all);
+}
+
 struct MemeticLaunchArgs {
     const MemeticSlot *slots;
     int32_t n_slots;

@@ -209,7 +209,6 @@ __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskO
 constexpr int kRing = 64;
 static_assert(kRing >= 2 * (kLookback + 1) && 2 + kLookback < 32 && kMaxChildren <= kLookback,
               "a slot outlives its readers, its draws have a lane, no wait inside a generation");
-constexpr int kMaxMemeticWaves = 12;
 
 template <int NW>
 struct __attribute__((aligned(16))) ReplicaLds {
@@ -476,28 +475,11 @@ hipError_t launch_memetic_latch(const uint32_t *any_hit, uint32_t *stop,
 
 namespace {
 
-// Wavefronts per replica: twelve up to one replica per compute unit, eight
-// while the device has them to spare, that is up to eight replicas per
-// compute unit (N <= 128) or two (N > 128, where a wavefront holds more of the
-// LDS and registers), four beyond, and no more than the launch has children.
-// 32 generations of K = 100 (MI355X, us) on 1, 4, 8 and 12 wavefronts per
-// replica: N = 120 1352, 456, 318 and 294 at 256 replicas, 1390, 544, 426 and
-// 424 at 512, 1615, 946 and 909 (8) at 2048, 3975, 2853 and 3002 (8) at 8192;
-// N = 200 3075, 1017, 716 and 663 at 256, 3209, 1246, 956 and 1237 at 512,
-// 3261, 1492 and 1602 (8) at 1024; N = 33 352, 131, 107 and 91 at 256, 887,
-// 769 and 788 (8) at 8192.
-template <int NW>
-int memetic_waves(const MemeticLaunchArgs &a) {
-    const int64_t spare = (int64_t)(NW == 4 ? 2 : 8) * a.cus;
-    const int64_t want = a.n_slots <= a.cus ? kMaxMemeticWaves : a.n_slots <= spare ? 8 : 4;
-    return (int)std::min(want, (int64_t)a.gens * a.children);
-}
-
 template <int NW>
 hipError_t launch_memetic_nw(const MemeticLaunchArgs &a, hipStream_t s) {
     static_assert(sizeof(ReplicaLds<NW>) + kMaxMemeticWaves * WalkLds<NW>::BYTES <= 65536,
                   "dynamic LDS within the default limit");
-    const int w = memetic_waves<NW>(a);
+    const int w = memetic_waves(NW, a.n_slots, a.K, a.children, a.gens, a.cus);
     hipLaunchKernelGGL(memetic_advance_kernel<NW>, dim3((unsigned)a.n_slots), dim3(64 * w),
                        sizeof(ReplicaLds<NW>) + (size_t)w * WalkLds<NW>::BYTES, s, a);
     return hipGetLastError();

@@ -14,5 +14,13 @@ int main() {
             std::printf("group2 %d %lld %d %d\n", kClassMaxN[first], (long long)walks, f.lanes,
                         f.neighbours);
         }
+    for (int words : {1, 2, 4})
+        for (int64_t replicas : {1, 256, 257, 512, 513, 2048, 2049, 1 << 22})
+            for (int K = 2; K <= LABS_MAX_K; ++K)
+                for (int children = 1; children <= LABS_MAX_CHILDREN; ++children)
+                    for (int gens : {1, 3, 1 << 20})
+                        std::printf("memetic %d %lld %d %d %d %d\n", words, (long long)replicas, K,
+                                    children, gens,
+                                    memetic_waves(words, replicas, K, children, gens, 256));
     return 0;
 }

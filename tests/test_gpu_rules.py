@@ -52,3 +52,21 @@ def test_short_walk_forms(lb, launch, line, lengths, aspiration):
         best, be, fe, _ = _oracle_walks(head, hi if ns is None else ns, rules, 23, with_trace=False)
         assert np.array_equal(a.best_e[:head].cpu().numpy(), be[:head])
         assert np.array_equal(a.best_seq[:head, :best.shape[1]].cpu().numpy(), best[:head])
+
+
+# both sides of the lines where a replica gets fewer wavefronts: replicas per compute unit, and
+# populations too small to keep more of them busy
+@pytest.mark.parametrize("n,per_cu", [(24, 1), (24, 8), (70, 1), (70, 8), (130, 1), (130, 2)])
+@pytest.mark.parametrize("K,children", [(2, 1), (5, 1), (6, 1), (24, 1), (2, 3), (40, 2)])
+def test_memetic_wavefronts(lb, n, per_cu, K, children):
+    rules = I.RULES_MEMETIC
+    gens = 13 if children == 1 else 5
+    kw = dict(n_uniform=n, out_stride=256, children=children)
+    line = per_cu * _cus()
+    runs = [lb.memetic_run(K, rules, gens, pops, 6, **kw) for pops in (line, line + 1, 3)]
+    for r in runs[:2]:
+        assert torch.equal(r.best_e[:3], runs[2].best_e)
+        assert torch.equal(r.best_seq[:3], runs[2].best_seq)
+    assert torch.equal(runs[0].best_seq, runs[1].best_seq[:line])
+    ref = _oracle_memetic([n] * 3, K, rules, gens, 6, children=0 if children == 1 else children)
+    assert [int(e) for e in runs[2].best_e] == [st.bestE for st in ref]

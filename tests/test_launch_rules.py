@@ -32,3 +32,18 @@ def test_few_short_walks_take_one_neighbour_per_lane(lines):
     for max_n, walks, lanes, neighbours in lines["group2"]:
         assert lanes * neighbours >= max_n
         assert neighbours == (2 if max_n == 32 and walks > 4096 else 1)
+
+
+def test_memetic_wavefronts_have_children_to_walk(lines):
+    for words, replicas, K, children, gens, waves in lines["memetic"]:
+        assert 1 <= waves <= min(12, gens * children)
+        crowded = replicas > (512 if words == 4 else 2048)
+        assert waves <= (12 if replicas <= 256 else 4 if crowded else 8)
+        if children == 1:
+            # small populations: nearly every child waits for the one before it
+            assert waves <= (1 + K // 6 if crowded else 2 + K // 8)
+        else:
+            # a generation's children walk side by side
+            assert waves >= min(children, gens * children, 4)
+        if K == 100 and gens >= 12:
+            assert waves == (12 if replicas <= 256 else 4 if crowded else 8)
