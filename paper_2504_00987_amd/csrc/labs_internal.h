@@ -223,6 +223,18 @@ inline int memetic_waves(int words, int64_t replicas, int K, int children, int g
     return (int)(w < all ? w : all);
 }
 
+// Wavefronts per replica of the random populations: four share the lags of
+// the members' energies, but each makes all the draws, so one does once the
+// replicas fill the device, for N > 128 (where the lags weigh more) later.
+// K = 100 (MI355X, a run of no generations, us), one and four: N = 12 38.9 and
+// 38.5 at 256 replicas, 45.6 and 45.8 at 1024, 49.1 and 50.7 at 2048, 98.9 and
+// 113.9 at 16384; N = 128 45.1 and 40.1, 52.4 and 50.5, 59.2 and 57.8, 158.8
+// and 163.8; N = 256 58.2 and 43.9, 66.3 and 61.0, 80.8 and 78.3, 303.9 and
+// 314.4, and 113.5 and 111.6 at 4096.
+inline int init_waves(int64_t replicas, int classes, int cus) {
+    return replicas <= (int64_t)((classes & 4) ? 16 : 4) * cus ? 4 : 1;
+}
+
 struct MemeticLaunchArgs {
     const MemeticSlot *slots;
     int32_t n_slots;

@@ -22,12 +22,11 @@ constexpr int kMaxK = 128;
 // ---------------------------------------------------------------------------
 // Random populations, one workgroup per replica: member m = lane + 64 h
 // (K <= 128) is the bits 128 q .. 128 q + 127 of the draws (pop, m, q, INIT);
-// each of the four wavefronts takes every fourth lag of every member's
-// energy, a member per lane.  (One wavefront with all lags: 33 us at K = 100,
-// N = 120.)
-constexpr int kInitWaves = 4;
-__global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLaunchArgs a) {
-    __shared__ int part[kInitWaves][kMaxK];
+// each of WAVES wavefronts makes the draws and takes every WAVES-th lag of
+// every member's energy, a member per lane (init_waves).
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void memetic_init_kernel(MemeticLaunchArgs a) {
+    __shared__ int part[WAVES][kMaxK];
     const int s = blockIdx.x;
     if (s >= a.n_slots) return;
     const MemeticSlot sl = a.slots[s];
@@ -53,7 +52,7 @@ __global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLa
             }
         }
         part[wave][lane + 64 * h] =
-            64 * h < K ? lane_energy<kInitWaves>(words, wd[h], N, N, wave) : 0;
+            64 * h < K ? lane_energy<WAVES>(words, wd[h], N, N, wave) : 0;
     }
     __syncthreads();
     if (wave != 0) return;
@@ -63,7 +62,7 @@ __global__ __launch_bounds__(64 * kInitWaves) void memetic_init_kernel(MemeticLa
         const int m = lane + 64 * h;
         e[h] = 0;
 #pragma unroll
-        for (int w = 0; w < kInitWaves; ++w) e[h] += part[w][m];
+        for (int w = 0; w < WAVES; ++w) e[h] += part[w][m];
         if (m < K) {
 #pragma unroll
             for (int w = 0; w < kStateWords; ++w)
@@ -461,7 +460,11 @@ __global__ void gather_best_kernel(MemeticStateDev st, const int32_t *__restrict
 
 hipError_t launch_memetic_init(const MemeticLaunchArgs &a, hipStream_t s) {
     if (a.n_slots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(memetic_init_kernel, dim3((unsigned)a.n_slots), dim3(64 * kInitWaves), 0, s, a);
+    const dim3 grid((unsigned)a.n_slots);
+    if (init_waves(a.n_slots, a.classes, a.cus) == 4)
+        hipLaunchKernelGGL(memetic_init_kernel<4>, grid, dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL(memetic_init_kernel<1>, grid, dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

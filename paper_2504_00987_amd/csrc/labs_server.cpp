@@ -158,6 +158,8 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     a.rule = to_rule(params.tabu);
     a.st = st;
     a.any_hit = nullptr;
+    a.classes = classes;
+    a.cus = std::max(1, h->num_cus);
     hipError_t e = hipSuccess;
     if (n_init > 0) {
         e = hipMemcpyAsync(d_init, h_init, n_init * sizeof(MemeticSlot), hipMemcpyHostToDevice, stream);
@@ -170,9 +172,7 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     a.slots = d_slots;
     a.n_slots = n_used;
     a.gens = params.chunk;
-    a.classes = classes;
     a.children = std::max(1, (int)params.children);
-    a.cus = std::max(1, h->num_cus);
     if (e == hipSuccess) e = launch_memetic_advance(a, stream, &sides);
     if (e == hipSuccess) e = hipMemcpyAsync(h_bestE, st.bestE, n_used * 4, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(h_gen, st.gen, n_used * 8, hipMemcpyDeviceToHost, stream);

@@ -22,5 +22,9 @@ int main() {
                         std::printf("memetic %d %lld %d %d %d %d\n", words, (long long)replicas, K,
                                     children, gens,
                                     memetic_waves(words, replicas, K, children, gens, 256));
+    for (int classes = 1; classes < 8; ++classes)
+        for (int64_t replicas : {1, 1024, 1025, 4096, 4097, 1 << 22})
+            std::printf("init %d %lld %d\n", classes, (long long)replicas,
+                        init_waves(replicas, classes, 256));
     return 0;
 }

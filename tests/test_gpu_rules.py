@@ -70,3 +70,23 @@ def test_memetic_wavefronts(lb, n, per_cu, K, children):
     assert torch.equal(runs[0].best_seq, runs[1].best_seq[:line])
     ref = _oracle_memetic([n] * 3, K, rules, gens, 6, children=0 if children == 1 else children)
     assert [int(e) for e in runs[2].best_e] == [st.bestE for st in ref]
+
+
+# both sides of the lines where one wavefront draws a population, and populations at the edges of a
+# wavefront's lanes
+@pytest.mark.parametrize("n,per_cu", [(3, 4), (33, 4), (128, 4), (129, 16), (256, 16)])
+@pytest.mark.parametrize("K", [2, 63, 64, 65, 128])
+def test_memetic_populations(lb, n, per_cu, K):
+    line = per_cu * _cus()
+    runs = []
+    for pops in (line, line + 1):
+        r = lb.memetic_run(K, I.RULES_MEMETIC, 0, pops, 11, n_uniform=n, out_stride=256)
+        runs.append((r, np.frombuffer(lb.memetic_save(), dtype=np.uint8)))
+    (a, blob_a), (b, blob_b) = runs
+    assert torch.equal(a.best_e, b.best_e[:line]) and torch.equal(a.best_seq, b.best_seq[:line])
+    # every member of the common replicas: 32 bytes each, after the header and the lengths
+    at = [256 + (4 * p + 255) // 256 * 256 for p in (line, line + 1)]
+    size = line * K * 32
+    assert np.array_equal(blob_a[at[0]:at[0] + size], blob_b[at[1]:at[1] + size])
+    ref = _oracle_memetic([n] * 2, K, I.RULES_MEMETIC, 0, 11)
+    assert [int(e) for e in a.best_e[:2]] == [st.bestE for st in ref]

@@ -47,3 +47,8 @@ def test_memetic_wavefronts_have_children_to_walk(lines):
             assert waves >= min(children, gens * children, 4)
         if K == 100 and gens >= 12:
             assert waves == (12 if replicas <= 256 else 4 if crowded else 8)
+
+
+def test_populations_of_a_full_device_are_drawn_once(lines):
+    for classes, replicas, waves in lines["init"]:
+        assert waves == (4 if replicas <= (4096 if classes & 4 else 1024) else 1)
