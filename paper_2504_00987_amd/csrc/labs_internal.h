@@ -202,9 +202,11 @@ struct SideStreams {
 // 716 and 663 at 256, 3209, 1246, 956 and 1237 at 512, 3261, 1492 and 1602 (8)
 // at 1024; N = 33 352, 131, 107 and 91 at 256, 887, 769 and 788 (8) at 8192.
 //
-// What the replica has children for: those of one generation, and the more
-// members the more of the next that wait for none of these.  Wavefronts beyond
-// that hold slots other replicas could run in.  16 generations (us) on 1, 2, 3,
+// What the replica has children for, once two replicas per compute unit leave
+// no slots over: those of one generation, and the more members the more of the
+// next that wait for none of these.  Wavefronts beyond that hold slots other
+// replicas could run in (and up to there draw ahead while they wait: K = 8 at 16
+// replicas takes 390 us on 3 wavefronts and 361 on 12).  16 generations (us) on 1, 2, 3,
 // 4 and 8 wavefronts, N = 64: K = 2 420, 395, 430, 560 and 817 at 2048
 // replicas, 536, 622, 703, 831 and 1459 at 4096; K = 8 427, 339, 342, 403 and
 // 559 at 2048, 557, 516, 542, 588 and 939 at 4096; K = 32 422, 303, 291, 309
@@ -219,7 +221,7 @@ inline int memetic_waves(int words, int64_t replicas, int K, int children, int g
     int useful = spare ? 2 + K / 8 : 1 + K / 6;
     if (children > 1) useful = children + (spare ? K / 8 : K / 6);
     const int64_t all = (int64_t)gens * children;
-    const int w = device < useful ? device : useful;
+    const int w = device < useful || replicas <= 2 * (int64_t)cus ? device : useful;
     return (int)(w < all ? w : all);
 }
 

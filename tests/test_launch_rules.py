@@ -39,7 +39,9 @@ def test_memetic_wavefronts_have_children_to_walk(lines):
         assert 1 <= waves <= min(12, gens * children)
         crowded = replicas > (512 if words == 4 else 2048)
         assert waves <= (12 if replicas <= 256 else 4 if crowded else 8)
-        if children == 1:
+        if replicas <= 512:
+            assert waves == min(12 if replicas <= 256 else 8, gens * children)
+        elif children == 1:
             # small populations: nearly every child waits for the one before it
             assert waves <= (1 + K // 6 if crowded else 2 + K // 8)
         else:
