@@ -153,6 +153,40 @@ __device__ __forceinline__ ChildDraws<NW> child_draws(const MemeticSlot &sl, uin
     return r;
 }
 
+// The members a child draws, and the child before its walk: ref(m) looks a
+// member up, energy(m, ref(m)) and member(m, ref(m)) read it.
+struct Parents {
+    bool comb;
+    int m0, m1, m2, m3;
+};
+__device__ __forceinline__ Parents parents(const Draw4 &da, const Draw4 &db, uint32_t p_comb,
+                                           int K) {
+    return {da.w0 < p_comb, (int)below(da.w1, (uint32_t)K), (int)below(da.w2, (uint32_t)K),
+            (int)below(da.w3, (uint32_t)K), (int)below(db.w0, (uint32_t)K)};
+}
+template <int NW, typename Ref, typename Energy, typename Member>
+__device__ __forceinline__ typename MaskOf<NW>::type breed(const Parents &p,
+                                                           const ChildDraws<NW> &cd, int N,
+                                                           Ref ref, Energy energy, Member member) {
+    using Mask = typename MaskOf<NW>::type;
+    const int r0 = ref(p.m0);
+    Mask child;
+    if (p.comb) {
+        // selectParents: two binary tournaments; Combine: one-point crossover
+        const int r1 = ref(p.m1), r2 = ref(p.m2), r3 = ref(p.m3);
+        const bool first = energy(p.m0, r0) <= energy(p.m1, r1);
+        const bool third = energy(p.m2, r2) <= energy(p.m3, r3);
+        const int cut = 1 + (int)below(cd.b.w1, (uint32_t)(N - 1));
+        const Mask A = first ? member(p.m0, r0) : member(p.m1, r1);
+        const Mask B = third ? member(p.m2, r2) : member(p.m3, r3);
+        const Mask lowm = m_low(A, cut);
+        child = m_or(m_and(A, lowm), m_and(B, m_not(lowm)));
+    } else {
+        child = member(p.m0, r0);
+    }
+    return m_xor(child, cd.flips);  // Mutate
+}
+
 // A child's walk of N <= 64 NW (NW = 4: N > 128) on one wavefront, with the
 // fewest neighbours per lane that hold it.
 template <int NW>
@@ -221,6 +255,7 @@ struct __attribute__((aligned(16))) ReplicaLds {
     int bestE;
     uint32_t total;  // children of this launch
     int64_t g0;      // generations done before it
+    int64_t hit0;    // the hit generation before it
 };
 
 // The launch's arguments and a slot, read again where they are used (scalar
@@ -236,6 +271,42 @@ __device__ __forceinline__ const MemeticLaunchArgs &fresh_args() {
 __device__ __forceinline__ const MemeticSlot &fresh_slot(const MemeticLaunchArgs &a) {
     ConstSlot *p = (ConstSlot *)(uintptr_t)(a.slots + blockIdx.x);
     return *(const MemeticSlot *)p;
+}
+
+// A replica's population and best between its state (index st) and LDS, and its
+// progress.
+template <int NW>
+__device__ __forceinline__ void load_population(uint64_t (*pop)[NW], int *popE, uint64_t *best,
+                                                const MemeticStateDev s, int st, int K) {
+    const int64_t base = (int64_t)st * K;
+    for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) pop[i][w] = s.pop[(base + i) * kStateWords + w];
+        popE[i] = s.popE[base + i];
+    }
+    if (threadIdx.x < NW) best[threadIdx.x] = s.best[(int64_t)st * kStateWords + threadIdx.x];
+}
+template <int NW>
+__device__ __forceinline__ void store_population(const uint64_t (*pop)[NW], const int *popE,
+                                                 const uint64_t *best, const MemeticStateDev s,
+                                                 int st, int K) {
+    const int64_t base = (int64_t)st * K;
+    for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s.pop[(base + i) * kStateWords + w] = pop[i][w];
+        s.popE[base + i] = popE[i];
+    }
+    if (threadIdx.x < NW) s.best[(int64_t)st * kStateWords + threadIdx.x] = best[threadIdx.x];
+}
+// One lane: `hit` as it was before the launch, `reached` if the replica's best
+// has reached its target.
+__device__ __forceinline__ void store_progress(const MemeticLaunchArgs &a, int st, int best_e,
+                                               int64_t gen, int64_t hit, bool reached) {
+    if (reached && hit < 0) hit = gen;
+    a.st.bestE[st] = best_e;
+    a.st.gen[st] = gen;
+    a.st.hit[st] = hit;
+    if (hit >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
 }
 
 template <typename T>
@@ -312,28 +383,24 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
         const MemeticLaunchArgs &a = fresh_args();
         const MemeticSlot &sl = fresh_slot(a);
         if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
-        const int K = a.K, st = sl.state;
-        const int64_t base = (int64_t)st * K;
-        const int64_t g0 = a.st.gen[st];
+        const int st = sl.state;
+        // every read is out before the first is waited for
+        const int64_t g0 = a.st.gen[st], hit0 = a.st.hit[st];
+        const int bestE0 = a.st.bestE[st];
+        load_population<NW>(L.pop, L.popE, L.best, a.st, st, a.K);
         const int64_t left = min(sl.gen_limit - g0, (int64_t)a.gens);
         if (left <= 0) {
-            if (threadIdx.x == 0 && a.st.hit[st] >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
+            if (threadIdx.x == 0 && hit0 >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
             return;
         }
-        for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) L.pop[i][w] = a.st.pop[(base + i) * kStateWords + w];
-            L.popE[i] = a.st.popE[base + i];
-        }
         for (int i = (int)threadIdx.x; i < kRing; i += (int)blockDim.x) L.done[i] = L.built[i] = 0u;
-        const int bestE0 = a.st.bestE[st];
-        if (threadIdx.x < NW) L.best[threadIdx.x] = a.st.best[(int64_t)st * kStateWords + threadIdx.x];
         if (threadIdx.x == 0) {
             L.claimed = L.merged = L.busy = 0u;
             L.stopped = sl.target >= 0 && bestE0 <= sl.target ? 1u : 0u;
             L.bestE = bestE0;
             L.total = (uint32_t)left * (uint32_t)a.children;
             L.g0 = g0;
+            L.hit0 = hit0;
         }
         __syncthreads();
     }
@@ -355,16 +422,14 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
         const int64_t g = (int64_t)uniform64((uint64_t)L.g0) + (int64_t)gi;
         const uint32_t wgen = (uint32_t)(g * B + b);
         const ChildDraws<NW> cd = child_draws<NW>(sl, (uint32_t)g, wgen, b, B, magic, N, thr);
-        const Draw4 &da = cd.a, &db = cd.b;
-        const bool comb = da.w0 < a.p_comb;
-        const int m0 = (int)below(da.w1, (uint32_t)K), m1 = (int)below(da.w2, (uint32_t)K);
-        const int m2 = (int)below(da.w3, (uint32_t)K), m3 = (int)below(db.w0, (uint32_t)K);
+        const Parents pr = parents(cd.a, cd.b, a.p_comb, K);
         // wait for the earlier children that replace a member drawn here, and
         // for the merging of those out of reach
         const int rep = (int)below(cd.w2, (uint32_t)K);
         const int dist = lane - 2;
         const bool near = dist > 0 && dist <= kLookback && dist <= (int)idx && cd.back > 0;
-        const bool clash = near && (rep == m0 || (comb && (rep == m1 || rep == m2 || rep == m3)));
+        const bool clash =
+            near && (rep == pr.m0 || (pr.comb && (rep == pr.m1 || rep == pr.m2 || rep == pr.m3)));
         const uint32_t from = idx - (uint32_t)dist;  // the lane's earlier child
         while (((int)lds_get_u(&L.merged) < (int)idx - kLookback ||
                 ballot(clash && lds_get(&L.done[from % kRing]) != from + 1u) != 0ull) &&
@@ -376,25 +441,10 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
             const uint64_t at = ballot(near && rep == m);
             return at ? (int)((idx + 2u - (uint32_t)__builtin_ctzll(at)) % kRing) : -1;
         };
-        const auto energy = [&](int m, int r) { return r < 0 ? L.popE[m] : L.resE[r]; };
-        const auto member = [&](int m, int r) { return load_mask<NW>(r < 0 ? L.pop[m] : L.res[r]); };
-        const int r0 = replaced(m0);
-        Mask child;
-        if (comb) {
-            // selectParents: two binary tournaments; Combine: one-point crossover
-            const int r1 = replaced(m1), r2 = replaced(m2), r3 = replaced(m3);
-            const bool first = energy(m0, r0) <= energy(m1, r1);
-            const bool third = energy(m2, r2) <= energy(m3, r3);
-            const int cut = 1 + (int)below(db.w1, (uint32_t)(N - 1));
-            const Mask A = first ? member(m0, r0) : member(m1, r1);
-            const Mask Bm = third ? member(m2, r2) : member(m3, r3);
-            const Mask lowm = m_low(A, cut);
-            child = m_or(m_and(A, lowm), m_and(Bm, m_not(lowm)));
-        } else {
-            child = member(m0, r0);
-        }
-        child = m_xor(child, cd.flips);  // Mutate
-        const int replaces = (int)below(db.w2, (uint32_t)K);
+        const Mask child = breed<NW>(
+            pr, cd, N, replaced, [&](int m, int r) { return r < 0 ? L.popE[m] : L.resE[r]; },
+            [&](int m, int r) { return load_mask<NW>(r < 0 ? L.pop[m] : L.res[r]); });
+        const int replaces = (int)below(cd.b.w2, (uint32_t)K);
         if (B > 1) lds_put(&L.built[idx % kRing], idx + 1u);
         const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, cd.len, lds);
         const MemeticLaunchArgs &a2 = fresh_args();
@@ -409,22 +459,106 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
     __syncthreads();
 
     const MemeticLaunchArgs &a = fresh_args();
-    const int K = a.K, st = fresh_slot(a).state;
-    const int64_t base = (int64_t)st * K;
-    for (int i = (int)threadIdx.x; i < K; i += (int)blockDim.x) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) a.st.pop[(base + i) * kStateWords + w] = L.pop[i][w];
-        a.st.popE[base + i] = L.popE[i];
+    const int st = fresh_slot(a).state;
+    store_population<NW>(L.pop, L.popE, L.best, a.st, st, a.K);
+    if (threadIdx.x == 0)
+        store_progress(a, st, L.bestE, L.g0 + (int64_t)(L.merged / (uint32_t)a.children), L.hit0,
+                       L.stopped != 0u);
+}
+
+// A replica's generations one after another: its children (B = a.children) on
+// the workgroup's wavefronts, each waited for before the next generation.  For
+// launches of one generation (PLAIN, GRAPH, chunk = 1) and populations too
+// small for children in flight, whose claims, ring and flags in LDS cost up to
+// a microsecond a launch: 48 launches of one generation of 3-step walks at
+// N = 12 on 16 replicas took 433 us with them and take 370 without; of four
+// such children, 447 and 400.
+constexpr int kMaxStepWaves = kMaxChildren;
+template <int NW>
+struct __attribute__((aligned(16))) StepLds {
+    uint64_t pop[kMaxK][NW];
+    uint64_t res[kMaxChildren][NW];
+    uint64_t best[NW];
+    int popE[kMaxK];
+    int resE[kMaxChildren], resSlot[kMaxChildren];
+};
+template <int NW>
+__global__ __launch_bounds__(64 * kMaxStepWaves)
+__attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_step_kernel(
+    MemeticLaunchArgs args) {
+    using Mask = typename MaskOf<NW>::type;
+    extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[];
+    StepLds<NW> &L = *(StepLds<NW> *)dyn_lds;
+    if (args.stop != nullptr && *args.stop != 0u) return;  // one value for the whole grid
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint8_t *lds = dyn_lds + sizeof(StepLds<NW>) + wave * WalkLds<NW>::BYTES;
+    // wave-uniform, and the same on every wavefront
+    int64_t g, hit;
+    uint32_t left;
+    int be;
+    {
+        const MemeticLaunchArgs &a = fresh_args();
+        const MemeticSlot &sl = fresh_slot(a);
+        if (sl.state < 0 || (1 << memetic_class(sl.n)) != NW) return;
+        // every read is out before the first is waited for
+        const int64_t g0 = a.st.gen[sl.state], hit0 = a.st.hit[sl.state];
+        const int bestE0 = a.st.bestE[sl.state];
+        load_population<NW>(L.pop, L.popE, L.best, a.st, sl.state, a.K);
+        g = (int64_t)uniform64((uint64_t)g0);
+        hit = (int64_t)uniform64((uint64_t)hit0);
+        be = __builtin_amdgcn_readfirstlane(bestE0);
+        const int64_t n = min(sl.gen_limit - g, (int64_t)a.gens);
+        if (n <= 0) {
+            if (threadIdx.x == 0 && hit >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
+            return;
+        }
+        left = (uint32_t)n;
+        __syncthreads();
     }
-    if (threadIdx.x < NW) a.st.best[(int64_t)st * kStateWords + threadIdx.x] = L.best[threadIdx.x];
-    if (threadIdx.x != 0) return;
-    const int64_t g = L.g0 + (int64_t)(L.merged / (uint32_t)a.children);
-    int64_t hit = a.st.hit[st];
-    if (L.stopped != 0u && hit < 0) hit = g;
-    a.st.bestE[st] = L.bestE;
-    a.st.gen[st] = g;
-    a.st.hit[st] = hit;
-    if (hit >= 0 && a.any_hit != nullptr) atomicOr(a.any_hit, 1u);
+    bool reached;
+    for (;; ++g, --left) {
+        const int target = fresh_slot(fresh_args()).target;
+        reached = target >= 0 && be <= target;
+        if (reached || left == 0u) break;
+        const int B = fresh_args().children;
+        for (int b = wave; b < B; b += (int)(blockDim.x >> 6)) {
+            const MemeticLaunchArgs &a = fresh_args();
+            const MemeticSlot &sl = fresh_slot(a);
+            const int N = sl.n, K = a.K;
+            const uint32_t thr =
+                a.mut_rule == 0 ? (uint32_t)(0x100000000ull / (uint64_t)N) : a.p_mut;
+            const uint32_t wgen = (uint32_t)(g * B + b);
+            const ChildDraws<NW> cd = child_draws<NW>(sl, (uint32_t)g, wgen, b, B,
+                                                      65536u / (uint32_t)B + 1u, N, thr);
+            const Mask child = breed<NW>(
+                parents(cd.a, cd.b, a.p_comb, K), cd, N, [](int) { return 0; },
+                [&](int m, int) { return L.popE[m]; },
+                [&](int m, int) { return load_mask<NW>(L.pop[m]); });
+            const int replaces = (int)below(cd.b.w2, (uint32_t)K);
+            const WalkResult<NW> r = child_walk<NW>(N, child, a, sl, wgen, cd.len, lds);
+            store_mask<NW>(L.res[b], r.best);  // uniform values, every lane
+            L.resE[b] = r.best_e;
+            L.resSlot[b] = replaces;
+        }
+        __syncthreads();
+        for (int b = 0; b < B; ++b) {  // Alg. 1's merge, in order
+            const int slot = __builtin_amdgcn_readfirstlane(L.resSlot[b]);
+            const int e = __builtin_amdgcn_readfirstlane(L.resE[b]);
+            const bool better = e < be;
+            if (better) be = e;
+            if (wave == 0) {
+                const Mask m = load_mask<NW>(L.res[b]);
+                store_mask<NW>(L.pop[slot], m);
+                L.popE[slot] = e;
+                if (better) store_mask<NW>(L.best, m);
+            }
+        }
+        __syncthreads();
+    }
+    const MemeticLaunchArgs &a = fresh_args();
+    const int st = fresh_slot(a).state;
+    store_population<NW>(L.pop, L.popE, L.best, a.st, st, a.K);
+    if (threadIdx.x == 0) store_progress(a, st, be, g, hit, reached);
 }
 
 // The stop latch of a chunk boundary (see launch_memetic_latch).
@@ -483,6 +617,14 @@ hipError_t launch_memetic_nw(const MemeticLaunchArgs &a, hipStream_t s) {
     static_assert(sizeof(ReplicaLds<NW>) + kMaxMemeticWaves * WalkLds<NW>::BYTES <= 65536,
                   "dynamic LDS within the default limit");
     const int w = memetic_waves(NW, a.n_slots, a.K, a.children, a.gens, a.cus);
+    if (w == 1 || a.gens == 1) {
+        // one generation's children: at most kMaxChildren wavefronts
+        static_assert(sizeof(StepLds<NW>) + kMaxStepWaves * WalkLds<NW>::BYTES <= 65536,
+                      "dynamic LDS within the default limit");
+        hipLaunchKernelGGL(memetic_step_kernel<NW>, dim3((unsigned)a.n_slots), dim3(64 * w),
+                           sizeof(StepLds<NW>) + (size_t)w * WalkLds<NW>::BYTES, s, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(memetic_advance_kernel<NW>, dim3((unsigned)a.n_slots), dim3(64 * w),
                        sizeof(ReplicaLds<NW>) + (size_t)w * WalkLds<NW>::BYTES, s, a);
     return hipGetLastError();

@@ -90,3 +90,32 @@ def test_memetic_populations(lb, n, per_cu, K):
     assert np.array_equal(blob_a[at[0]:at[0] + size], blob_b[at[1]:at[1] + size])
     ref = _oracle_memetic([n] * 2, K, I.RULES_MEMETIC, 0, 11)
     assert [int(e) for e in a.best_e[:2]] == [st.bestE for st in ref]
+
+
+# launches of one generation, and of many on one wavefront per replica: more children than
+# wavefronts, targets reached on the way, generations past a replica's limit
+@pytest.mark.parametrize("mode,chunk", [(0, 5), (1, 5), (2, 1)])
+@pytest.mark.parametrize("K,children", [(2, 1), (3, 2), (100, 1), (100, 3), (128, 8)])
+def test_memetic_generations_one_at_a_time(lb, mode, chunk, K, children):
+    ns = np.array([3, 24, 64, 65, 128, 129, 193, 256], dtype=np.int32)
+    rules, gens = I.RULES_MEMETIC, 7
+    batch = 0 if children == 1 else children
+    ref = _oracle_memetic(ns, K, rules, gens, 91, children=batch)
+    kw = dict(ns=ns, out_stride=256, children=children, mode=mode, chunk=chunk)
+    res = lb.memetic_run(K, rules, gens, len(ns), 91, **kw)
+    for p, st in enumerate(ref):
+        assert (int(res.best_e[p]), int(res.gens_done[p])) == (st.bestE, gens)
+        assert np.array_equal(res.best_seq[p, :int(ns[p])].cpu().numpy(), st.best)
+    target = sorted(st.bestE for st in ref)[len(ns) // 2]
+    ref = _oracle_memetic(ns, K, rules, gens, 91, target=target, children=batch)
+    res = lb.memetic_run(K, rules, gens, len(ns), 91, target=target, **kw)
+    for p, st in enumerate(ref):
+        assert (int(res.best_e[p]), int(res.hit_gen[p]), int(res.gens_done[p])) == (
+            st.bestE, st.hit, st.gen)
+    # many replicas of a small population: one wavefront each, also in longer launches
+    pops = 16 * _cus() + 1
+    many = lb.memetic_run(2, rules, gens, pops, 91, n_uniform=65, out_stride=256, children=children,
+                          chunk=4)
+    one = lb.memetic_run(2, rules, gens, 8, 91, n_uniform=65, out_stride=256, children=children,
+                         mode=mode, chunk=chunk)
+    assert torch.equal(many.best_seq[:8], one.best_seq) and torch.equal(many.best_e[:8], one.best_e)
