@@ -269,8 +269,8 @@ int labs_tabu_batch_noalloc(labs_handle *h, const labs_tabu_params *p,
 int labs_set_launch(labs_handle *h, const labs_launch *launch);
 
 /* The launch configuration labs_tabu_batch would use for a batch whose
- * lengths span [n_min, n_max] (where the default depends on their number: for
- * a large batch). */
+ * lengths span [n_min, n_max] (where the choice depends on their number, that
+ * is for n_max <= 32: for a large batch). */
 int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *out);
 
 /*
@@ -284,8 +284,9 @@ int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *o
  * The default runs first until the GPU is at its steady clock (at least 16
  * calls and 25 ms), and stays unless a configuration is more than 2 % faster.
  * The choice is kept for batches whose shortest and longest lengths fall in
- * the length buckets (of 16) of n_min and n_max, so that tuning one range
- * leaves the others alone.  *tried (may be NULL) receives the number of
+ * the length buckets (of 16) of n_min and n_max and, for n_max <= 32, whose
+ * number of walks has the same default launch as `walks`, so that tuning one
+ * range leaves the others alone.  *tried (may be NULL) receives the number of
  * configurations timed.  Synchronous; results never depend on the choice
  * (only speed does).
  */

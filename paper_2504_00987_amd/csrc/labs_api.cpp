@@ -198,7 +198,16 @@ RuleParams to_rule(const labs_tabu_params &p) {
     return r;
 }
 
-int bucket_of(int n) { return std::min(LABS_MAX_N / 16 - 1, std::max(0, (n - 1) / 16)); }
+// Whether a batch of walks of N <= n_max has the several walks per wavefront
+// that fill the device.
+static bool many_short_walks(int n_max, int64_t walks) {
+    return n_max <= 16 ? walks > 2048 : n_max <= 32 && walks > 4096;
+}
+
+TunedKey tuned_key(int n_min, int n_max, int64_t walks) {
+    const auto bucket = [](int n) { return std::min(LABS_MAX_N / 16 - 1, std::max(0, (n - 1) / 16)); };
+    return {bucket(n_min), bucket(n_max), many_short_walks(n_max, walks)};
+}
 
 // One walk per wavefront and 64-lane workgroup up to N = 128, four walks per
 // 256-lane workgroup above; batches whose walks all have N <= 32 run four per
@@ -207,7 +216,7 @@ int bucket_of(int n) { return std::min(LABS_MAX_N / 16 - 1, std::max(0, (n - 1) 
 // ns at 1024 walks, 298 and 316 at 4096, 480 and 364 at 8192; N = 16 230 and
 // 241 ns at 2048 walks, 309 and 238 at 4096.
 labs_launch default_launch(int n_max, int64_t walks) {
-    const bool group = n_max <= 16 ? walks > 2048 : n_max <= 32 && walks > 4096;
+    const bool group = many_short_walks(n_max, walks);
     labs_launch l;
     l.group_lanes = n_max <= 128 ? 64 : 256;
     l.walks_per_group = group ? (n_max <= 16 ? 4 : 2) : n_max <= 128 ? 1 : 4;
@@ -531,7 +540,7 @@ namespace liblabs {
 
 labs_launch choose_launch(labs_handle *h, int n_min, int n_max, int64_t walks) {
     if (h->has_override) return h->override_launch;
-    const auto it = h->tuned.find({bucket_of(n_min), bucket_of(n_max)});
+    const auto it = h->tuned.find(tuned_key(n_min, n_max, walks));
     if (it != h->tuned.end()) return it->second;
     return default_launch(n_max, walks);
 }
@@ -811,7 +820,7 @@ extern "C" int labs_autotune(labs_handle *h, const labs_tabu_params *p, int32_t 
     hipFree(be);
     hipFree(fe);
     if (rc) return rc;
-    h->tuned[{bucket_of(n_min), bucket_of(n_max)}] = best;
+    h->tuned[tuned_key(n_min, n_max, walks)] = best;
     if (tried) *tried = n_tried;
     return LABS_OK;
 }

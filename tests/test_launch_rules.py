@@ -54,3 +54,20 @@ def test_memetic_wavefronts_have_children_to_walk(lines):
 def test_populations_of_a_full_device_are_drawn_once(lines):
     for classes, replicas, waves in lines["init"]:
         assert waves == (4 if replicas <= (4096 if classes & 4 else 1024) else 1)
+
+
+def test_tuned_launch_serves_its_own_batch_sizes(tmp_path):
+    # a launch tuned on few walks is not used by a batch whose default is another form, nor the
+    # reverse; nor is it lost where the default does not depend on the number
+    from paper_2504_00987_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        from paper_2504_00987_amd import build
+        build.build()
+    exe = str(tmp_path / "tuned_launch")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
+                           os.path.join(ROOT, "tests", "host", "tuned_launch.cpp"), _lib.LIB_PATH,
+                           "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH),
+                           "-Wl,-rpath,/opt/rocm/lib", "-L/opt/rocm/lib", "-lamdhip64", "-o", exe])
+    for line in subprocess.check_output([exe], text=True).splitlines():
+        n, tuned, walks, used, same_default = (int(x) for x in line.split()[1:])
+        assert used == same_default, line
