@@ -26,5 +26,16 @@ int main() {
         for (int64_t replicas : {1, 1024, 1025, 4096, 4097, 1 << 22})
             std::printf("init %d %lld %d\n", classes, (long long)replicas,
                         init_waves(replicas, classes, 256));
+    // every subset of present classes, as a batch of one walk per present class
+    for (int mask = 0; mask < (1 << kWalkClasses); ++mask)
+        for (int lanes : {64, 32, 16}) {
+            int64_t ce[kWalkClasses];
+            int64_t end = 0;
+            for (int c = 0; c < kWalkClasses; ++c) ce[c] = end += (mask >> c) & 1;
+            const WalkGroups g = tabu_launch_groups(ce, lanes);
+            for (int i = 0; i < g.n; ++i)
+                std::printf("launch %d %d %d %d %d %d\n", mask, lanes, g.first[i], g.last[i],
+                            g.kind[i], kClassMaxN[g.first[i]]);
+        }
     return 0;
 }

@@ -119,3 +119,32 @@ def test_memetic_generations_one_at_a_time(lb, mode, chunk, K, children):
     one = lb.memetic_run(2, rules, gens, 8, 91, n_uniform=65, out_stride=256, children=children,
                          mode=mode, chunk=chunk)
     assert torch.equal(many.best_seq[:8], one.best_seq) and torch.equal(many.best_e[:8], one.best_e)
+
+
+# the longest lengths of the exhaustive search: the roots' depth stops at 13 pairs, a node's halves
+# are full at n = 40; values of the plain enumeration of all 2^(n-1) codes
+@pytest.mark.parametrize("n,e,count,code", [
+    (36, 82, 8, 0x1f8c51252), (37, 86, 8, 0x13354b0f00), (38, 87, 8, 0x3c34aa66),
+    (39, 99, 8, 0x49a150179c), (40, 108, 8, 0x2223dc3a5a)])
+def test_exhaustive_minimum_longest(lb, n, e, count, code):
+    got_e, got_count, seq = lb.bruteforce_min(n)
+    assert (got_e, got_count) == (e, count) and O.energy(seq) == e
+    assert sum(1 << i for i, s in enumerate(seq) if s < 0) == code
+    # the smallest of its images with s_0 = +1
+    alternating = 1 - 2 * (np.arange(n) % 2)
+    for image in (seq, seq * alternating, seq[::-1], seq[::-1] * alternating):
+        image = image * image[0]
+        assert code <= sum(1 << i for i, s in enumerate(image) if s < 0)
+
+
+# both sides of the line from which walks of one length issue ahead, on any number of compute units
+@pytest.mark.parametrize("n", [40, 200])
+def test_issue_priority_line(lb, n):
+    rules = I.Rules(I.STEPS_FIXED, 70, I.TENURE_LINEAR, 1, 10, 0, 1, 5, 0, 1)
+    line = 8 * _cus()
+    few, many = (lb.tabu_batch(rules, w, 17, n_uniform=n, out_stride=256) for w in (line - 1, line))
+    for a, b in ((few.best_e, many.best_e), (few.final_e, many.final_e),
+                 (few.best_seq, many.best_seq)):
+        assert torch.equal(a, b[:line - 1])
+    assert np.array_equal(many.best_e.cpu().numpy()[:8],
+                          _oracle_walks(8, n, rules, 17, with_trace=False)[1])

@@ -71,3 +71,27 @@ def test_tuned_launch_serves_its_own_batch_sizes(tmp_path):
     for line in subprocess.check_output([exe], text=True).splitlines():
         n, tuned, walks, used, same_default = (int(x) for x in line.split()[1:])
         assert used == same_default, line
+
+
+@pytest.mark.parametrize("lanes", [64, 32, 16])
+def test_walk_launches(lines, lanes):
+    # what labs_tabu_batch launches: every present class in exactly one launch, in processing order;
+    # one launch of one walk per wavefront at most, whose first class names its longest walk
+    wave, short, shortest = 0, 2, 4  # kinds: one walk per wavefront, N <= 32, N <= 16
+    for mask in range(1 << 8):
+        present = [c for c in range(8) if mask >> c & 1]
+        launches = [x[2:] for x in lines["launch"] if x[:2] == [mask, lanes]]
+        covered = [c for f, z, _, _ in launches for c in range(f, z + 1) if c in present]
+        assert covered == present
+        assert all(f in present and z in present and f <= z for f, z, _, _ in launches)
+        waves = [x for x in launches if x[2] == wave]
+        assert len(waves) <= 1 and waves == launches[:len(waves)]
+        for f, z, _, max_n in waves:
+            assert f == present[0] and max_n == (256, 193, 128, 97, 64, 49, 32, 16)[f]
+            assert lanes == 64 or z <= 5  # N <= 32 has a launch of its own
+        kinds = [x[2] for x in launches[len(waves):]]
+        want = [] if lanes == 64 else [c for c in (6, 7) if c in present]
+        if lanes == 32:
+            assert kinds == ([short] if want else [])
+        else:
+            assert kinds == [short if c == 6 else shortest for c in want]
