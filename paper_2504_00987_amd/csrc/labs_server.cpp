@@ -17,6 +17,7 @@
 #include <functional>
 #include <map>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <queue>
 #include <thread>
@@ -240,14 +241,20 @@ extern "C" int labs_server_create(labs_handle *h, const labs_memetic_params *par
     if (params->resume) return fail(h, LABS_E_INVAL, "the server starts every request afresh (resume=0)");
     if (max_slots < 1 || max_slots > (1 << 20)) return fail(h, LABS_E_INVAL, "max_slots out of [1, 2^20]");
     DeviceGuard g(h->device);
-    labs_server *s = new labs_server();
+    labs_server *s = nullptr;
+    try {
+        s = new labs_server();
+        s->owner.assign(max_slots, -1);
+        std::vector<int> every(max_slots);
+        std::iota(every.begin(), every.end(), 0);
+        s->free_slots = labs_server::SlotHeap(std::greater<int>(), std::move(every));
+    } catch (const std::bad_alloc &) {
+        delete s;
+        return fail(h, LABS_E_NOMEM, "server tables of %d slots", max_slots);
+    }
     s->h = h;
     s->params = *params;
     s->max_slots = max_slots;
-    s->owner.assign(max_slots, -1);
-    std::vector<int> every(max_slots);
-    std::iota(every.begin(), every.end(), 0);
-    s->free_slots = labs_server::SlotHeap(std::greater<int>(), std::move(every));
     size_t state_bytes = 0;
     carve_state(nullptr, max_slots, params->K, &state_bytes);
     const size_t tbl = ((size_t)max_slots * sizeof(MemeticSlot) + 255) & ~(size_t)255;

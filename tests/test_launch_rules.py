@@ -26,6 +26,20 @@ def lines(tmp_path_factory):
     return out
 
 
+def _with_library(name, tmp_path):
+    """The lines a program linked with the library prints."""
+    from paper_2504_00987_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        from paper_2504_00987_amd import build
+        build.build()
+    exe = str(tmp_path / name)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
+                           os.path.join(ROOT, "tests", "host", name + ".cpp"), _lib.LIB_PATH,
+                           "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH),
+                           "-Wl,-rpath,/opt/rocm/lib", "-L/opt/rocm/lib", "-lamdhip64", "-o", exe])
+    return subprocess.check_output([exe], text=True).splitlines()
+
+
 def test_few_short_walks_take_one_neighbour_per_lane(lines):
     # a part-filled device is bound by a step's chain, which a second
     # neighbour per lane lengthens; only larger batches take two
@@ -59,16 +73,7 @@ def test_populations_of_a_full_device_are_drawn_once(lines):
 def test_tuned_launch_serves_its_own_batch_sizes(tmp_path):
     # a launch tuned on few walks is not used by a batch whose default is another form, nor the
     # reverse; nor is it lost where the default does not depend on the number
-    from paper_2504_00987_amd import _lib
-    if not os.path.exists(_lib.LIB_PATH):
-        from paper_2504_00987_amd import build
-        build.build()
-    exe = str(tmp_path / "tuned_launch")
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", ROCM_INCLUDE,
-                           os.path.join(ROOT, "tests", "host", "tuned_launch.cpp"), _lib.LIB_PATH,
-                           "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH),
-                           "-Wl,-rpath,/opt/rocm/lib", "-L/opt/rocm/lib", "-lamdhip64", "-o", exe])
-    for line in subprocess.check_output([exe], text=True).splitlines():
+    for line in _with_library("tuned_launch", tmp_path):
         n, tuned, walks, used, same_default = (int(x) for x in line.split()[1:])
         assert used == same_default, line
 
@@ -95,3 +100,8 @@ def test_walk_launches(lines, lanes):
             assert kinds == ([short] if want else [])
         else:
             assert kinds == [short if c == 6 else shortest for c in want]
+
+
+def test_server_tables_out_of_memory(tmp_path):
+    # LABS_E_NOMEM, no server, a message
+    assert _with_library("server_tables", tmp_path) == ["2 1 1"] * 2
