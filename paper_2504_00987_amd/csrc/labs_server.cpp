@@ -107,9 +107,13 @@ int labs_server::iterate(std::unique_lock<std::mutex> &lk) {
     // (1) admission: FIFO while the head fits in the free slots
     std::vector<int> fresh;
     for (;;) {
-        while (!waiting.empty() && reqs[waiting.front()].state == kCancelled) waiting.pop_front();
         if (waiting.empty()) break;
-        Request &r = reqs[waiting.front()];
+        const auto it = reqs.find(waiting.front());
+        if (it == reqs.end() || it->second.state == kCancelled) {
+            waiting.pop_front();  // cancelled; no longer known once polled
+            continue;
+        }
+        Request &r = it->second;
         if ((int)free_slots.size() < r.pops) break;
         for (int k = 0; k < r.pops; ++k) {
             const int s = take_slot();

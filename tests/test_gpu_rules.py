@@ -148,3 +148,32 @@ def test_issue_priority_line(lb, n):
         assert torch.equal(a, b[:line - 1])
     assert np.array_equal(many.best_e.cpu().numpy()[:8],
                           _oracle_walks(8, n, rules, 17, with_trace=False)[1])
+
+
+def test_server_forgets_a_cancelled_request_that_was_waiting(lb):
+    # cancelled and polled while another request holds the slots: nothing is admitted in its place
+    import time
+    from paper_2504_00987_amd import _lib
+    from paper_2504_00987_amd.labs import Server
+    srv = Server(lb, 16, I.RULES_MEMETIC, max_slots=4, chunk=8)
+    try:
+        first = srv.submit(120, 11, 4, 4000)
+        drop = srv.submit(41, 12, 4, 5)
+        srv.cancel(drop)
+        with pytest.raises(_lib.LabsError) as err:
+            srv.poll(drop, 41)
+        assert err.value.code == _lib.LABS_E_CANCELLED
+        last = srv.submit(40, 13, 3, 5)
+        got, t0 = {}, time.time()
+        while len(got) < 2 and time.time() - t0 < 60:
+            for rid, n in ((first, 120), (last, 40)):
+                if rid not in got and (r := srv.poll(rid, n)) is not None:
+                    got[rid] = r
+            assert sum(srv.stats()[:2]) <= 2
+            time.sleep(0.002)
+        assert len(got) == 2
+        assert srv.stats() == (0, 0, 2, 0)
+    finally:
+        srv.close()
+    ref = _oracle_memetic([40] * 3, 16, I.RULES_MEMETIC, 5, 13)
+    assert got[last][1] == min(st.bestE for st in ref)
