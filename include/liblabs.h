@@ -278,9 +278,10 @@ int labs_get_launch(labs_handle *h, int32_t n_min, int32_t n_max, labs_launch *o
  * [n_min, n_max] -- {64, 1}, {128, 2}, {256, 4} (one wavefront per walk);
  * when n_min <= 32, {64, 2} and {128, 4}, and when n_min <= 16 also {64, 4}
  * (several walks per wavefront) -- each as a grid of one walk per
- * wavefront and as a persistent queue at 4 to 64 wavefronts per CU -- on
- * `walks` random-start walks with lengths spread evenly over [n_min, n_max]
- * and parameters `p` (each: one warm-up call, then four calls back to back).
+ * wavefront and as a persistent queue at 4 to 16 (n_max > 64: to 64)
+ * wavefronts per CU -- on `walks` random-start walks with lengths spread
+ * evenly over [n_min, n_max] and parameters `p` (each: one warm-up call, then
+ * four calls back to back).
  * The default runs first until the GPU is at its steady clock (at least 16
  * calls and 25 ms), and stays unless a configuration is more than 2 % faster.
  * The choice is kept for batches whose shortest and longest lengths fall in

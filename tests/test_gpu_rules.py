@@ -177,3 +177,14 @@ def test_server_forgets_a_cancelled_request_that_was_waiting(lb):
         srv.close()
     ref = _oracle_memetic([40] * 3, 16, I.RULES_MEMETIC, 5, 13)
     assert got[last][1] == min(st.bestE for st in ref)
+
+
+@pytest.mark.parametrize("n_min,n_max,most", [(32, 32, 25), (3, 32, 30), (64, 64, 15)])
+def test_autotune_of_short_walks_is_short(n_min, n_max, most):
+    # a persistent grid of each size that fits, no larger ones
+    from paper_2504_00987_amd.labs import Labs
+    h = Labs(0)
+    try:
+        assert h.autotune(I.rules_tabu(2), n_min, n_max, 256) <= most
+    finally:
+        h.close()
