@@ -164,8 +164,7 @@ int labs_energy_batch(labs_handle *h, const int8_t *seqs, const int32_t *ns,
  *   ns        device int32 [count] per-row lengths, or NULL to use n_uniform
  *   d         device int32 [count] output
  * Asynchronous on `stream`; the caller guarantees LABS_MIN_N <= ns[b] <=
- * min(stride, LABS_MAX_N).  Work per row: N^2 (odd N) or N^3 (even N) / 2
- * pair tests.
+ * min(stride, LABS_MAX_N).  Work per row: N rotations of N / 2 pairs each.
  */
 int labs_skew_deviation_batch(labs_handle *h, const int8_t *seqs, const int32_t *ns,
                               int32_t n_uniform, int32_t stride, int64_t count, int32_t *d,

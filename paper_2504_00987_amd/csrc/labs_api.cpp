@@ -440,7 +440,7 @@ static int bruteforce_impl(labs_handle *h, int32_t n, bool skew, int32_t *min_e,
         a.final_e = a.best_e + kWalks;
         a.best_seq = (int8_t *)(a.final_e + kWalks);
         a.out_stride = kWalkStride;
-        a.n_uniform = a.n_max = n;
+        a.n_uniform = n;
         a.W = kWalks;
         const int cls = walk_class(n);
         for (int k = 0; k < kWalkClasses; ++k) a.class_end[k] = k >= cls ? kWalks : 0;
@@ -636,7 +636,7 @@ int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *sta
         int32_t *pn = (int32_t *)h->pin.ptr;
         int32_t *po = pn + W;
         std::memcpy(pn, ns_host, (size_t)W * sizeof(int32_t));
-        // Longest walks first (cost grows like N^3 at fixed steps per N):
+        // Longest walks first (cost grows like N^2 at fixed steps per N):
         // a counting sort by N, stable within equal N.
         int64_t start[LABS_MAX_N + 2] = {0};
         for (int64_t i = 0; i < W; ++i) ++start[LABS_MAX_N - ns_host[i] + 1];
@@ -661,7 +661,6 @@ int tabu_batch_impl(labs_handle *h, const labs_tabu_params *p, const int8_t *sta
     a.starts = starts;
     a.start_stride = start_stride;
     a.n_uniform = n_uniform;
-    a.n_max = n_max;
     a.W = W;
     a.k0 = (uint32_t)(seed & 0xffffffffu);
     a.k1 = (uint32_t)(seed >> 32);

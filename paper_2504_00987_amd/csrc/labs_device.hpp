@@ -149,7 +149,6 @@ __device__ __forceinline__ uint64_t m_and(uint64_t a, uint64_t b) { return a & b
 __device__ __forceinline__ uint64_t m_or(uint64_t a, uint64_t b) { return a | b; }
 __device__ __forceinline__ uint64_t m_xor(uint64_t a, uint64_t b) { return a ^ b; }
 __device__ __forceinline__ uint64_t m_not(uint64_t a) { return ~a; }
-__device__ __forceinline__ bool m_eq(uint64_t a, uint64_t b) { return a == b; }
 __device__ __forceinline__ int m_popc(uint64_t a) { return __popcll(a); }
 // a >> sh for 0 <= sh <= 64 (64 gives 0).
 __device__ __forceinline__ uint64_t m_shr(uint64_t a, int sh) {
@@ -160,13 +159,11 @@ __device__ __forceinline__ uint64_t m_low(uint64_t, int n) {
     return n >= 64 ? ~0ull : ((1ull << n) - 1ull);
 }
 __device__ __forceinline__ int m_bit(uint64_t a, int i) { return (int)((a >> i) & 1ull); }
-__device__ __forceinline__ uint64_t m_onebit(uint64_t, int i) { return 1ull << i; }
 
 __device__ __forceinline__ M128 m_and(M128 a, M128 b) { return {a.lo & b.lo, a.hi & b.hi}; }
 __device__ __forceinline__ M128 m_or(M128 a, M128 b) { return {a.lo | b.lo, a.hi | b.hi}; }
 __device__ __forceinline__ M128 m_xor(M128 a, M128 b) { return {a.lo ^ b.lo, a.hi ^ b.hi}; }
 __device__ __forceinline__ M128 m_not(M128 a) { return {~a.lo, ~a.hi}; }
-__device__ __forceinline__ bool m_eq(M128 a, M128 b) { return a.lo == b.lo && a.hi == b.hi; }
 __device__ __forceinline__ int m_popc(M128 a) { return __popcll(a.lo) + __popcll(a.hi); }
 // a >> sh for 0 <= sh <= 128.
 __device__ __forceinline__ M128 m_shr(M128 a, int sh) {
@@ -196,10 +193,6 @@ __device__ __forceinline__ M128 m_low(M128, int n) {
 __device__ __forceinline__ int m_bit(M128 a, int i) {
     return (int)(((i < 64 ? a.lo : a.hi) >> (i & 63)) & 1ull);
 }
-__device__ __forceinline__ M128 m_onebit(M128, int i) {
-    const uint64_t b = 1ull << (i & 63);
-    return {i < 64 ? b : 0ull, i < 64 ? 0ull : b};
-}
 
 // 256-bit masks for N <= 256 (four words, selected by value so that a
 // variable word index never forces the mask out of registers).
@@ -220,9 +213,6 @@ __device__ __forceinline__ M256 m_xor(M256 a, M256 b) {
     return {a.w0 ^ b.w0, a.w1 ^ b.w1, a.w2 ^ b.w2, a.w3 ^ b.w3};
 }
 __device__ __forceinline__ M256 m_not(M256 a) { return {~a.w0, ~a.w1, ~a.w2, ~a.w3}; }
-__device__ __forceinline__ bool m_eq(M256 a, M256 b) {
-    return a.w0 == b.w0 && a.w1 == b.w1 && a.w2 == b.w2 && a.w3 == b.w3;
-}
 __device__ __forceinline__ int m_popc(M256 a) {
     return __popcll(a.w0) + __popcll(a.w1) + __popcll(a.w2) + __popcll(a.w3);
 }
@@ -245,11 +235,6 @@ __device__ __forceinline__ M256 m_low(M256, int n) {
 __device__ __forceinline__ int m_bit(M256 a, int i) {
     return (int)((m_word(a, i >> 6) >> (i & 63)) & 1ull);
 }
-__device__ __forceinline__ M256 m_onebit(M256, int i) {
-    const int q = i >> 6;
-    const uint64_t b = 1ull << (i & 63);
-    return {q == 0 ? b : 0ull, q == 1 ? b : 0ull, q == 2 ? b : 0ull, q == 3 ? b : 0ull};
-}
 
 template <int NW> struct MaskOf;
 template <> struct MaskOf<1> { using type = uint64_t; };
@@ -263,10 +248,6 @@ __device__ __forceinline__ uint64_t mask_word(const M128 &a, int h) {
     return h == 0 ? a.lo : h == 1 ? a.hi : 0ull;
 }
 __device__ __forceinline__ uint64_t mask_word(const M256 &a, int h) { return m_word(a, h); }
-template <typename Mask>
-__device__ __forceinline__ uint64_t mask_lo(const Mask &a) { return mask_word(a, 0); }
-template <typename Mask>
-__device__ __forceinline__ uint64_t mask_hi(const Mask &a) { return mask_word(a, 1); }
 
 // A mask of NW words from four words (words past NW are ignored).
 template <int NW>
@@ -451,7 +432,8 @@ struct WalkResult {
 // int8 with zeros around it, SP[q] = 4 s_q for 0 <= q < N and 0 for the other
 // q in -SPAN .. 2 SPAN - 1, which covers every 2j - p and 2p - j of two
 // positions j, p < SPAN.  (With these factors one number, -s_p, scales every
-// term of a move.)  15 SPAN bytes: occupancy is never bound by LDS.  (Spins
+// term of a move.)  15 SPAN bytes: the registers bind occupancy, not the LDS (61
+// VGPRs at N <= 64, eight wavefronts per SIMD; 77 to 80 beyond, six).  (Spins
 // as whole words, with fewer loads for several neighbours per lane, cost 3
 // to 8 % on full devices: the stride-two reads of 2j - p meet in the banks.)
 template <int SPAN>
@@ -489,9 +471,6 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p) {
     return (uint32_t)(uintptr_t)(const lds_i8 *)p;
 }
 __device__ __forceinline__ int lds_load_i8(uint32_t a) { return *(const lds_i8 *)(uintptr_t)a; }
-__device__ __forceinline__ void lds_store_i8(uint32_t a, int v) {
-    *(lds_i8 *)(uintptr_t)a = (int8_t)v;
-}
 __device__ __forceinline__ int lds_load_i32(uint32_t a) { return *(const lds_i32 *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store_i32(uint32_t a, int v) {
     *(lds_i32 *)(uintptr_t)a = v;
@@ -549,8 +528,9 @@ __device__ __forceinline__ void set_moved(uint64_t bit, uint32_t za, int d_new, 
 // reads and writes exactly the entries C_|p-j| and Q_(p+j) (lanes j and
 // 2p - j write the same value to C_k).  The common -8 is left out of the
 // stored D_j and put back on the scalar unit.
-// Lanes past the sequence have s_j = 0: they write back what they read, and
-// their D never falls to an aspiration threshold.
+// Lanes past the sequence have s_j = 0: they write back the Q they read, and
+// the C they read or, where 2p - j lies in the sequence, what lane 2p - j
+// writes; their D never falls to an aspiration threshold.
 //
 // Bound: the instructions a wavefront issues and, with few wavefronts, one
 // chain of an LDS round trip, a wavefront minimum and the scalar pick.  So the

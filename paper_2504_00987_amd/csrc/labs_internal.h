@@ -34,7 +34,6 @@ struct TabuLaunchArgs {
     int32_t start_stride;
     const int32_t *ns;        // device [W] or null
     int32_t n_uniform;
-    int32_t n_max;            // longest walk in the batch
     const int32_t *order;     // device [W] walk ids in processing order, or null
     int64_t W;
     int64_t class_end[kWalkClasses];  // processing-order positions [class_end[c-1],
@@ -56,7 +55,7 @@ constexpr int kSideStreams = kWalkClasses - 1;
 // Kernel forms of a launch group.
 enum WalkKind : int {
     kKindWave = 0,    // one walk per wavefront
-    kKindSplit = 1,   // walks of 64 < N <= 128 apart from the shorter ones
+    kKindSplit = 1,   // walks of 64 < N <= 128 apart from the shorter ones (no launch asks for it)
     kKindGroup2 = 2,  // walks of N <= 32, two or four per wavefront (group2_form)
     kKindGroup4 = 4,  // walks of N <= 16, four per wavefront (16 lanes, one neighbour each)
 };
@@ -64,7 +63,8 @@ enum WalkKind : int {
 // Launch groups of a batch: runs of consecutive length classes (hence of
 // consecutive positions of the processing order).  The classes of N > 128,
 // when present, form one group and those of N <= 128 another -- or, with
-// `split`, classes 2..3 (64 < N <= 128) and the shorter classes one each.
+// `split` (which no launch asks for), classes 2..3 (64 < N <= 128) and the
+// shorter classes one each.
 // With several walks per wavefront (`lanes` = 32 or 16 lanes per walk) the
 // walks of N <= 32 leave the one-walk-per-wavefront group: with 32 lanes both
 // short classes form one group; with 16, N <= 16 and 16 < N <= 32 one each.
@@ -94,7 +94,7 @@ inline WalkGroups walk_launch_groups(const int64_t *class_end, bool split, int l
     const int short_end = lanes < 64 ? 5 : kWalkClasses - 1;
     range(0, 1, kKindWave);
     if (split) {
-        if (present(2) || present(3)) add(2, 3, kKindSplit);  // the two-wavefront kernel takes both
+        if (present(2) || present(3)) add(2, 3, kKindSplit);
         range(4, short_end, kKindWave);
     } else {
         range(2, short_end, kKindWave);
@@ -111,7 +111,8 @@ inline WalkGroups walk_launch_groups(const int64_t *class_end, bool split, int l
 // The launch groups of a walk batch: those above, with neighbouring
 // one-walk-per-wavefront groups in one launch (one kernel takes every length:
 // a walk's tables are 15 bytes per position, so the longest walk's scratch
-// costs the shorter ones no occupancy).
+// leaves room for all the wavefronts the registers do: six per SIMD, where a
+// launch of N <= 64 alone has eight).
 inline WalkGroups tabu_launch_groups(const int64_t *class_end, int lanes) {
     const WalkGroups all = walk_launch_groups(class_end, false, lanes);
     WalkGroups g;

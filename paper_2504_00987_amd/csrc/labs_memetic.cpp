@@ -125,7 +125,7 @@ extern "C" int labs_memetic_run(labs_handle *h, const labs_memetic_params *p,
     int rc = check_memetic(h, p);
     if (rc) return rc;
     if (pops < 0) return fail(h, LABS_E_INVAL, "pops < 0");
-    // one workgroup of up to 8 wavefronts per replica in one grid
+    // one workgroup of at most four wavefronts per replica in one grid of that many
     if (pops > LABS_MAX_REPLICAS) return fail(h, LABS_E_INVAL, "pops > %d", LABS_MAX_REPLICAS);
     if (pops == 0) return LABS_OK;
     if (!best_seq || !best_e) return fail(h, LABS_E_INVAL, "null output");

@@ -4,6 +4,8 @@
 //   memetic_advance_kernel memetic generations (Alg. 1 / Alg. 3), several
 //                          children of a replica in flight, population
 //                          resident in LDS
+//   memetic_step_kernel    the same one generation after another: launches of
+//                          one generation, small populations
 //   gather_best_kernel     best sequences and energies to caller buffers
 #include <algorithm>
 
@@ -237,8 +239,9 @@ __device__ __forceinline__ WalkResult<NW> child_walk(int N, const typename MaskO
 //
 // A generation is one walk, a serial chain that leaves most of a SIMD idle:
 // 64 generations of 256 replicas at N = 120 took 2452 us on one wavefront per
-// replica, 37.5 us a generation, and take 451 us with twelve; 16 generations
-// of eight children 899 us with a barrier after each generation, 633 us here.
+// replica, 37.5 us a generation, and take 460 to 480 us with twelve; 16
+// generations of eight children 899 us with a barrier after each generation, 635
+// here.
 constexpr int kRing = 64;
 static_assert(kRing >= 2 * (kLookback + 1) && 2 + kLookback < 32 && kMaxChildren <= kLookback,
               "a slot outlives its readers, its draws have a lane, no wait inside a generation");
@@ -471,8 +474,8 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
 // launches of one generation (PLAIN, GRAPH, chunk = 1) and populations too
 // small for children in flight, whose claims, ring and flags in LDS cost up to
 // a microsecond a launch: 48 launches of one generation of 3-step walks at
-// N = 12 on 16 replicas took 433 us with them and take 370 without; of four
-// such children, 447 and 400.
+// N = 12 on 16 replicas took 433 us with them and take 361 without; of four
+// such children, 447 and 374.
 constexpr int kMaxStepWaves = kMaxChildren;
 template <int NW>
 struct __attribute__((aligned(16))) StepLds {
