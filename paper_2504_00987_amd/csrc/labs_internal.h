@@ -219,8 +219,8 @@ inline int memetic_waves(int words, int64_t replicas, int K, int children, int g
     const int64_t some = (int64_t)(words == 4 ? 2 : 8) * cus;
     const bool spare = replicas <= some;
     const int device = replicas <= cus ? kMaxMemeticWaves : spare ? 8 : 4;
-    int useful = spare ? 2 + K / 8 : 1 + K / 6;
-    if (children > 1) useful = children + (spare ? K / 8 : K / 6);
+    int useful = (spare ? 2 : 1) + K / 8;
+    if (children > 1) useful = children + K / 8;
     const int64_t all = (int64_t)gens * children;
     const int w = device < useful || replicas <= 2 * (int64_t)cus ? device : useful;
     return (int)(w < all ? w : all);

@@ -57,7 +57,7 @@ def test_short_walk_forms(lb, launch, line, lengths, aspiration):
 # both sides of the lines where a replica gets fewer wavefronts: replicas per compute unit, and
 # populations too small to keep more of them busy
 @pytest.mark.parametrize("n,per_cu", [(24, 1), (24, 8), (70, 1), (70, 8), (130, 1), (130, 2)])
-@pytest.mark.parametrize("K,children", [(2, 1), (5, 1), (6, 1), (24, 1), (2, 3), (40, 2)])
+@pytest.mark.parametrize("K,children", [(2, 1), (7, 1), (8, 1), (24, 1), (2, 3), (40, 2)])
 def test_memetic_wavefronts(lb, n, per_cu, K, children):
     rules = I.RULES_MEMETIC
     gens = 13 if children == 1 else 5

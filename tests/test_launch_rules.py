@@ -57,7 +57,7 @@ def test_memetic_wavefronts_have_children_to_walk(lines):
             assert waves == min(12 if replicas <= 256 else 8, gens * children)
         elif children == 1:
             # small populations: nearly every child waits for the one before it
-            assert waves <= (1 + K // 6 if crowded else 2 + K // 8)
+            assert waves <= (1 + K // 8 if crowded else 2 + K // 8)
         else:
             # a generation's children walk side by side
             assert waves >= min(children, gens * children, 4)
