@@ -30,7 +30,8 @@ namespace liblabs {
 
 namespace {
 
-// Words 0 .. W - 1 of the bits from `at` on.
+// Words 0 .. W - 1 of the bits from `at` on, of bits in LDS or (the bits a
+// candidate of N <= 32 looks at) in a register.
 template <int W>
 __device__ __forceinline__ void bit_window(const uint32_t *bits, int at, uint32_t *out) {
     const uint32_t *p = bits + (at >> 5);
@@ -42,12 +43,16 @@ __device__ __forceinline__ void bit_window(const uint32_t *bits, int at, uint32_
         lo = hi;
     }
 }
+template <int W>
+__device__ __forceinline__ void bit_window(uint64_t bits, int at, uint32_t *out) {
+    static_assert(W == 1, "N <= 32");
+    out[0] = (uint32_t)(bits >> at);
+}
 
 // Least broken-pair count over this lane's rotations lane, lane + 64, ..; W
 // words hold the pairs i = 1 .. c of a candidate (bit i - 1).
-template <int W>
-__device__ __forceinline__ int least_broken(const uint32_t *S2, const uint32_t *R2, int N,
-                                            int lane) {
+template <int W, typename Bits>
+__device__ __forceinline__ int least_broken(Bits S2, Bits R2, int N, int lane) {
     constexpr uint32_t kOdd = 0x55555555u;  // bit i - 1, i odd
     const int c = (N - 1) / 2;              // odd N: pairs; even N: N / 2 - 1 likewise
     int best = N;
@@ -110,6 +115,15 @@ __global__ __launch_bounds__(64 * WPG) void skew_deviation_kernel(
     const int N = __builtin_amdgcn_readfirstlane(ns ? ns[b] : n_uniform);
     const int8_t *row = seqs + b * (int64_t)stride;
     uint32_t *S2 = bits[wave][0], *R2 = bits[wave][1];
+    // N <= 32: the doubled masks in scalar registers, the row read once
+    // (262144 rows of N = 8: 57 us a call; 75 through LDS and the loop below,
+    // whose second trip waits for the memory again)
+    if (N <= 32) {
+        const uint64_t s = ballot(lane < N && row[lane < N ? lane : 0] < 0);
+        const uint64_t r = __builtin_bitreverse64(s) >> (64 - N);
+        out[b] = wave_min(least_broken<1>(s | (s << N), r | (r << N), N, lane));  // every lane
+        return;
+    }
     for (int x0 = 0; x0 < 2 * N + 64; x0 += 64) {
         const int x = x0 + lane, k = x < N ? x : x - N;
         const bool in = x < 2 * N;
@@ -126,13 +140,13 @@ __global__ __launch_bounds__(64 * WPG) void skew_deviation_kernel(
     const int words = ((N - 1) / 2 + 31) / 32;
     int best;
     if (words <= 1)
-        best = least_broken<1>(S2, R2, N, lane);
+        best = least_broken<1, const uint32_t *>(S2, R2, N, lane);
     else if (words == 2)
-        best = least_broken<2>(S2, R2, N, lane);
+        best = least_broken<2, const uint32_t *>(S2, R2, N, lane);
     else if (words == 3)
-        best = least_broken<3>(S2, R2, N, lane);
+        best = least_broken<3, const uint32_t *>(S2, R2, N, lane);
     else
-        best = least_broken<4>(S2, R2, N, lane);
+        best = least_broken<4, const uint32_t *>(S2, R2, N, lane);
     out[b] = wave_min(best);  // uniform value, every lane
 }
 

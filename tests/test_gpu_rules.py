@@ -188,3 +188,14 @@ def test_autotune_of_short_walks_is_short(n_min, n_max, most):
         assert h.autotune(I.rules_tabu(2), n_min, n_max, 256) <= most
     finally:
         h.close()
+
+
+# up to N = 32 a row's rotations come from registers, beyond from LDS
+@pytest.mark.parametrize("n", [5, 6, 16, 17, 21, 22, 30, 31, 32, 33, 34])
+def test_skew_deviation_short_rows(lb, n):
+    rows = I.random_pm1(70, n, n + 3, seed=n)
+    rows[:, n:] = -1  # past the rows: not looked at
+    rows[0, :n] = 1
+    rows[1, :n] = 1 - 2 * (np.arange(n) % 2)
+    got = lb.skew_deviation(torch.from_numpy(rows).cuda(), n_uniform=n).cpu().numpy()
+    assert np.array_equal(got, [O.skew_deviation(r[:n]) for r in rows])
