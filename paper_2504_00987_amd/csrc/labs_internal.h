@@ -212,17 +212,18 @@ struct SideStreams {
 // replicas, 536, 622, 703, 831 and 1459 at 4096; K = 8 427, 339, 342, 403 and
 // 559 at 2048, 557, 516, 542, 588 and 939 at 4096; K = 32 422, 303, 291, 309
 // and 358 at 2048, 552, 468, 450, 445 and 575 at 4096.  4 generations of 4
-// children, K = 2: 422, 297, 289, 272 and 338 at 2048.
+// children, K = 2: 422, 297, 289, 272 and 338 at 2048.  N = 200: K = 6 1765,
+// 1500, 1471, 1516 and 2472 at 1024 replicas, 2169, 1838, 2390, 2574 and 4523 at
+// 2048.
 // And no more than the launch has children.
 constexpr int kMaxMemeticWaves = 12;
 inline int memetic_waves(int words, int64_t replicas, int K, int children, int gens, int cus) {
-    const int64_t some = (int64_t)(words == 4 ? 2 : 8) * cus;
-    const bool spare = replicas <= some;
-    const int device = replicas <= cus ? kMaxMemeticWaves : spare ? 8 : 4;
-    int useful = (spare ? 2 : 1) + K / 8;
+    const int64_t per_cu = (replicas + cus - 1) / cus;
+    const int device = per_cu <= 1 ? kMaxMemeticWaves : per_cu <= (words == 4 ? 2 : 8) ? 8 : 4;
+    int useful = (per_cu <= (words == 4 ? 4 : 8) ? 2 : 1) + K / 8;
     if (children > 1) useful = children + K / 8;
     const int64_t all = (int64_t)gens * children;
-    const int w = device < useful || replicas <= 2 * (int64_t)cus ? device : useful;
+    const int w = device < useful || per_cu <= 2 ? device : useful;
     return (int)(w < all ? w : all);
 }
 

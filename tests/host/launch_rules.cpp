@@ -15,7 +15,7 @@ int main() {
                         f.neighbours);
         }
     for (int words : {1, 2, 4})
-        for (int64_t replicas : {1, 256, 257, 512, 513, 2048, 2049, 1 << 22})
+        for (int64_t replicas : {1, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 1 << 22})
             for (int K = 2; K <= LABS_MAX_K; ++K)
                 for (int children = 1; children <= LABS_MAX_CHILDREN; ++children)
                     for (int gens : {1, 3, 1 << 20})

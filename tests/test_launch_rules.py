@@ -50,6 +50,7 @@ def test_few_short_walks_take_one_neighbour_per_lane(lines):
 
 def test_memetic_wavefronts_have_children_to_walk(lines):
     for words, replicas, K, children, gens, waves in lines["memetic"]:
+        full = replicas > (1024 if words == 4 else 2048)
         assert 1 <= waves <= min(12, gens * children)
         crowded = replicas > (512 if words == 4 else 2048)
         assert waves <= (12 if replicas <= 256 else 4 if crowded else 8)
@@ -57,7 +58,7 @@ def test_memetic_wavefronts_have_children_to_walk(lines):
             assert waves == min(12 if replicas <= 256 else 8, gens * children)
         elif children == 1:
             # small populations: nearly every child waits for the one before it
-            assert waves <= (1 + K // 8 if crowded else 2 + K // 8)
+            assert waves <= (1 + K // 8 if full else 2 + K // 8)
         else:
             # a generation's children walk side by side
             assert waves >= min(children, gens * children, 4)
