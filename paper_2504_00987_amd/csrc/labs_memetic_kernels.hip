@@ -258,7 +258,6 @@ struct __attribute__((aligned(16))) ReplicaLds {
     int bestE;
     uint32_t total;  // children of this launch
     int64_t g0;      // generations done before it
-    int64_t hit0;    // the hit generation before it
 };
 
 // The launch's arguments and a slot, read again where they are used (scalar
@@ -403,7 +402,6 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
             L.bestE = bestE0;
             L.total = (uint32_t)left * (uint32_t)a.children;
             L.g0 = g0;
-            L.hit0 = hit0;
         }
         __syncthreads();
     }
@@ -465,7 +463,7 @@ __attribute__((amdgpu_waves_per_eu(NW == 4 ? 5 : 7))) void memetic_advance_kerne
     const int st = fresh_slot(a).state;
     store_population<NW>(L.pop, L.popE, L.best, a.st, st, a.K);
     if (threadIdx.x == 0)
-        store_progress(a, st, L.bestE, L.g0 + (int64_t)(L.merged / (uint32_t)a.children), L.hit0,
+        store_progress(a, st, L.bestE, L.g0 + (int64_t)(L.merged / (uint32_t)a.children), a.st.hit[st],
                        L.stopped != 0u);
 }
 
