@@ -151,10 +151,12 @@ __global__ __launch_bounds__(256) void skew_bruteforce_kernel(int N, uint64_t pe
 // takes 64 root nodes of depth m0 at a time from a queue and runs their
 // subtrees in LDS: a stack per depth, always the deepest one that fills the
 // wavefront, so every lane has a node until the queue is empty.  A node's
-// children cost about ten instructions each.  Bound: VALU, most of it the last
-// lags of the leaves.  Against evaluating every code (a call): n = 26 235 ->
-// 68 us, n = 30 3.3 -> 0.14 ms, n = 33 41 -> 0.33 ms; n = 36 takes 2.3 ms,
-// n = 40 54 ms.
+// children cost about ten vector instructions each.  Bound: the instructions of
+// few wavefronts, as many scalar as vector ones: the stacks (15 KB at n = 33)
+// leave two wavefronts per SIMD, each issuing on half of its cycles and waiting
+// on 0.4, the VALU on 0.38 (0.43 at n = 36).  Against evaluating every code (a
+// call): n = 26 235 -> 68 us, n = 30 3.3 -> 0.14 ms, n = 33 41 -> 0.33 ms; n = 36
+// takes 2.3 ms, n = 40 54 ms.
 constexpr uint32_t kTwice = 1u << 31;     // in a node's second word: x' is not searched
 constexpr int kFirstLags = 2;              // evaluated before the leaves are gathered again
 constexpr int kStackNodes = 64 + 4 * 64;  // below 64 when a batch's children come on top
